@@ -112,12 +112,36 @@ struct Plan {
     std::vector<void *> cpr;  // colour-restricted tables, one block per node
     std::vector<void *> root_list;    // per template
     std::vector<void *> root_list16;  // (x | y << 16), when every index fits 16 bits
+    // vertex-relative tables: per node the split's pair list, the aggregation's
+    // maps (colour maps followed by the output lists); per template the root list
+    std::vector<void *> rel_pairs, rel_map, rel_root;
     // SpMM colour-skip masks per (node, colourings per pass, chunk width)
     std::map<std::tuple<int, int, int>, void *> chunks;
   };
   mutable std::mutex mu;
   mutable std::vector<DeviceTables> dev;
 };
+
+// Vertex-relative tables: the q-sets of the k-1 colours other than a vertex's
+// own, numbered in increasing order without it.
+struct RelMap {
+  int w_in = 0, w_out = 0;    // columns of a gathered and of an aggregated row
+  int cw = 0, wout4 = 0;      // absolute sets and output columns, padded to 4
+  int zero = 0;               // w_in padded to 4: position of a staged zero
+  // [k][cw]: column of the absolute set without colour c in a row of colour c
+  // (zero if it lacks c); then [k][wout4]: absolute set of each output position;
+  // then [k][zero]: absolute set of each column plus c (cw: padding)
+  std::vector<uint16_t> map;
+};
+// whether every table of the plan has a vertex-relative form, with elements of
+// es bytes and multiply-add tiles of at most `lds` bytes
+bool rel_ok(const Plan &P, int es, size_t lds);
+// maps of the aggregation of an m-vertex passive child, m >= 2
+RelMap rel_map(int k, int m);
+// pairs [np][ws] (x | y << 16) of a split (m vertices, ma of them active, 1 < ma < m)
+std::vector<uint32_t> rel_pairs(int k, int m, int ma);
+// root list (x | y << 16) of a template of t vertices, ma in the active child
+std::vector<uint32_t> rel_root_list(int k, int t, int ma);
 
 sg2v_status plan_build(const int32_t *parent, int t, int k, Plan &out);
 // Several templates over the same k, sharing isomorphic rooted sub-templates.

@@ -286,6 +286,119 @@ void launch_single_bound(const int32_t *drop, int k, int Cs, int Cb, int b, cons
 void launch_zero_pad(int dtype, void *X, int64_t n, int64_t ld, int64_t c_from, hipStream_t s);
 
 // ---------------------------------------------------------------------------
+// Vertex-relative tables (rel.hip).  Planes per colouring: element (j, i, p)
+// of a table at j * plane + i * ld + p.  e / mx: per colouring exponent and
+// largest mantissa (float bits) of a table, FP32S only.
+
+struct RelHistArgs {
+  const int64_t *row_ptr;
+  const int32_t *col_idx;
+  const float *w;          // nullable
+  const uint8_t *colors;   // colouring-major
+  int64_t n;
+  int32_t k, j0, b, R;     // R: rows per wave
+  int32_t tlong;           // rows of at least this many entries are segments
+  void *H;
+  int64_t ldh, hplane;
+  void *partial;           // [b][slots][ldh]
+  int64_t pplane;
+  const int32_t *seg_row, *seg_len, *seg_slot;  // slot -1: writes its row
+  const int64_t *seg_beg;
+  int32_t n_seg;
+};
+
+struct RelSpmmArgs {
+  const int64_t *row_ptr;
+  const int32_t *col_idx;
+  const float *w;          // nullable
+  const uint8_t *colors;
+  int64_t n;
+  int32_t k, j0;
+  const void *M;           // gathered table
+  int64_t ldm, mplane;
+  void *B;
+  int64_t ldb, bplane;
+  void *partial;           // [b][slots][ldb]
+  int64_t pplane;
+  const uint16_t *map;     // [k][cw]: column of (absolute set - colour) in a row of that colour, or sr - 4
+  const uint16_t *olist;   // [k][wout4]: absolute set of each output position
+  const uint16_t *smap;    // [k][wmap]: absolute set of (column + colour) in a row of that colour, or cw
+  int32_t wmap;
+  int32_t add;             // 1: sums of absolute sets in LDS (k_rel_spmm_add)
+  int32_t cw, wout, wout4; // absolute sets and output columns, padded
+  int32_t sr;              // stride of a staged row; its element sr - 4 is zero
+  int32_t lp, streams;     // lanes per gathered row, rows gathered at a time
+  int32_t gw;              // lanes of an output group (64: the whole wave)
+  int32_t R;               // rows per wave, at most 63
+  int32_t tlong;
+  const int32_t *seg_row, *seg_len, *seg_slot;
+  const int64_t *seg_beg;
+  int32_t n_seg;
+  const int *e_in;
+  const unsigned *mx_in;
+  int *e_out;
+  unsigned *mx_out;
+  int *ovf;
+};
+
+struct RelCombineArgs {
+  const void *partial;
+  int64_t pplane;
+  void *B;
+  int64_t ld, bplane;
+  int32_t w;               // valid columns
+  const int32_t *long_row, *long_slot0, *long_nslot;
+  int32_t n_long;
+  unsigned *mx;            // nullable
+  int *ovf;
+};
+
+struct RelEmaArgs {
+  const void *X, *Y;       // active table, aggregation of the passive one
+  int64_t ldx, xplane, ldy, yplane;
+  void *M;
+  int64_t ldm, mplane;
+  int32_t wa, wb, ws, np;
+  const uint32_t *pairs;   // [np][ws]: x | y << 16
+  int64_t n;
+  const int *ex, *ey;
+  const unsigned *mxx, *mxy;
+  int *e_out;
+  unsigned *mx_out;
+  int *ovf;
+};
+
+struct RelRootArgs {
+  const void *X, *Y;       // Y nullable
+  int64_t ldx, xplane, ldy, yplane;
+  const uint32_t *list;    // [L]: x | y << 16
+  int64_t L;
+  int32_t lp;              // lanes per vertex (a power of two)
+  int64_t n;
+  const unsigned *mxx, *mxy;
+  void *partial;           // [b][blocks]
+  int *ovf;
+};
+
+struct RelFinalArgs {
+  const void *partial;
+  int32_t nblk;
+  void *out;
+  int *E;                  // nullable
+  const int *ex, *ey;
+  const unsigned *mxx, *mxy;  // mxy nullable
+  int *ovf;
+};
+
+void launch_rel_init(int *e, unsigned *mx, int ntab, int b, unsigned hist_bits, hipStream_t s);
+void launch_rel_hist(int dtype, const RelHistArgs &a, dim3 grid, hipStream_t s);
+int launch_rel_spmm(int dtype, const RelSpmmArgs &a, dim3 grid, size_t lds, hipStream_t s);
+void launch_rel_combine(int dtype, const RelCombineArgs &a, int b, hipStream_t s);
+int launch_rel_ema(int dtype, const RelEmaArgs &a, int R, int nt, dim3 grid, size_t lds, hipStream_t s);
+void launch_rel_root(int dtype, const RelRootArgs &a, dim3 grid, hipStream_t s);
+void launch_rel_final(int dtype, const RelFinalArgs &a, int b, hipStream_t s);
+
+// ---------------------------------------------------------------------------
 // Persistent schedule.  While t_prec is set on a thread, the launchers above
 // append their launch (kernel body, grid, dynamic LDS and a copy of the
 // arguments) to it instead of issuing it; k_persist then runs the recorded

@@ -496,6 +496,97 @@ sg2v_status plan_build_multi(const int32_t *const *parents, const int32_t *ts, i
 
 
 // ---------------------------------------------------------------------------
+// Vertex-relative tables.  A vertex of colour c numbers the other k-1 colours
+// 0..k-2 in increasing order; a relative set of size q has the colexicographic
+// rank among the C(k-1, q) sets as its column.
+
+namespace {
+// absolute set of a relative one of a vertex of colour c
+uint32_t abs_of(uint32_t rel, int c) { return (rel & ((1u << c) - 1)) | (rel >> c << (c + 1)); }
+}  // namespace
+
+bool rel_ok(const Plan &P, int es, size_t lds) {
+  const int pad = 16 / es;
+  for (size_t q = 0; q < P.nodes.size(); ++q) {
+    const Node &nd = P.nodes[q];
+    if (nd.size == 1) continue;
+    // an aggregation: three output columns per lane, maps of 256 absolute sets,
+    // and a gathered row that one wave reads
+    if (nd.n_passive_uses > 0 && (nd.cols > 256 || binom(P.k - 1, nd.size) > 192 ||
+                                  binom(P.k - 1, nd.size - 1) * es > 64 * 16)) return false;
+    const int ma = P.nodes[nd.active].size, mp = P.nodes[nd.passive].size;
+    const int64_t wa = binom(P.k - 1, ma - 1), wb = binom(P.k - 1, mp), ws = binom(P.k - 1, nd.size - 1);
+    if (wa >= 0xFFFF || wb >= 0xFFFF || (double)ws * binom(nd.size - 1, ma - 1) > (double)(1 << 26)) return false;
+    // rows of the multiply-add staged in LDS, four at least
+    if (ma > 1 && P.root_index[q] < 0 && (size_t)((wa + wb) * (4 + pad) * es) > lds) return false;
+  }
+  return true;
+}
+
+RelMap rel_map(int k, int m) {
+  RelMap r;
+  const int64_t C = binom(k, m);
+  r.w_in = (int)binom(k - 1, m - 1);
+  r.w_out = (int)binom(k - 1, m);
+  r.cw = (int)((C + 3) / 4 * 4);
+  r.wout4 = (r.w_out + 3) / 4 * 4;
+  r.zero = (r.w_in + 3) / 4 * 4;
+  r.map.assign((size_t)k * r.cw, (uint16_t)r.zero);
+  r.map.resize((size_t)k * (r.cw + r.wout4), 0);
+  r.map.resize((size_t)k * (r.cw + r.wout4 + r.zero), (uint16_t)r.cw);
+  for (int c = 0; c < k; ++c) {
+    for (int p = 0; p < r.w_in; ++p) {
+      const int64_t set = colex_rank(abs_of(colex_unrank(p, m - 1, k - 1), c) | (1u << c));
+      r.map[(size_t)c * r.cw + set] = (uint16_t)p;
+      r.map[(size_t)k * (r.cw + r.wout4) + (size_t)c * r.zero + p] = (uint16_t)set;
+    }
+    for (int p = 0; p < r.w_out; ++p)
+      r.map[(size_t)k * r.cw + (size_t)c * r.wout4 + p] =
+          (uint16_t)colex_rank(abs_of(colex_unrank(p, m, k - 1), c));
+  }
+  return r;
+}
+
+namespace {
+// every split of set Q into a part of size qa and the rest, as column pairs
+template <typename F>
+void rel_splits(uint32_t Q, int qa, F f) {
+  uint32_t s = Q;
+  for (;;) {  // subsets of Q in decreasing order
+    if (__builtin_popcount(s) == qa) f(colex_rank(s), colex_rank(Q & ~s));
+    if (s == 0) break;
+    s = (s - 1) & Q;
+  }
+}
+}  // namespace
+
+std::vector<uint32_t> rel_pairs(int k, int m, int ma) {
+  const int64_t ws = binom(k - 1, m - 1);
+  const int np = (int)binom(m - 1, ma - 1);
+  std::vector<uint32_t> out((size_t)ws * np);
+  for (int64_t C = 0; C < ws; ++C) {
+    int q = 0;
+    rel_splits(colex_unrank(C, m - 1, k - 1), ma - 1, [&](int64_t x, int64_t y) {
+      out[(size_t)q++ * ws + C] = (uint32_t)x | ((uint32_t)y << 16);
+    });
+  }
+  return out;
+}
+
+std::vector<uint32_t> rel_root_list(int k, int t, int ma) {
+  std::vector<uint32_t> out;
+  const int64_t ws = binom(k - 1, t - 1);
+  for (int64_t C = 0; C < ws; ++C) {
+    const uint32_t Q = colex_unrank(C, t - 1, k - 1);
+    if (ma == 1) out.push_back((uint32_t)colex_rank(Q));
+    else rel_splits(Q, ma - 1, [&](int64_t x, int64_t y) { out.push_back((uint32_t)x | ((uint32_t)y << 16)); });
+  }
+  if (ma > 1) std::sort(out.begin(), out.end(), [](uint32_t a, uint32_t b) { return (a & 0xFFFF) != (b & 0xFFFF) ? (a & 0xFFFF) < (b & 0xFFFF) : a < b; });
+  return out;
+}
+
+
+// ---------------------------------------------------------------------------
 // Choice of root and cut order (Sec. 2.3.2).  The colourful count sums the
 // rooted counts over every image of the root, so it is the number of
 // colourful injective maps of T and does not depend on which vertex is the

@@ -1,0 +1,976 @@
+// Kernels of the count in vertex-relative tables for gfx950.
+//
+// A sub-template's table M_s(i, C) is zero unless the colour set C holds the
+// colour of vertex i (the sub-template's root is i), and an aggregation
+// B(i, P) is only ever multiplied by entries whose set holds that colour, so
+// only sets P without it are read.  A table row therefore needs C(k-1, q)
+// columns instead of C(k, q) or C(k, q+1): the q-sets of the k-1 colours other
+// than the vertex's own, numbered 0..k-2 in increasing order (own colour left
+// out), in colexicographic order:
+//   M_s(i, C), |C| = m   ->  q = m - 1, the set C without the own colour;
+//   B_p(i, P), |P| = m   ->  q = m, the set P.
+// In these coordinates
+//   - a split with a one-vertex active child is the identity: M_s = B_p;
+//   - every other multiply-add and the root reduction use one pair table for
+//     all vertices, whatever their colours, on rows in their natural order;
+//   - the aggregation moves an entry of neighbour j (colour c) from set Q to
+//     the set Q + {c} of the row's vertex, dropped when it holds the row's
+//     colour.
+// Tables are planes per colouring: element (j, i, p) at j * plane + i * ld + p.
+#include <algorithm>
+
+#include "kernels.h"
+#include "launch.h"
+
+namespace sg2v {
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+// LDS add whose order is fixed for a given address: the adds of one wave are
+// issued in program order and those of one instruction in lane order.
+template <typename T>
+__device__ __forceinline__ void rel_add(T *p, T v, bool valid, bool &ovf) {
+  if constexpr (is_u64<T>) {
+    const T old = atomicAdd((unsigned long long *)p, (unsigned long long)v);
+    ovf |= valid && old + v < old;
+  } else {
+    __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+  }
+}
+
+// FP32S frame of a table of one colouring: exponent E and factor 2^(e - E)
+// from its exponent and the bits of its largest mantissa (0: a zero table)
+__device__ __forceinline__ int rel_frame(int e, unsigned mx) { return mx ? e + ilog2_bits(mx) + 1 : 0; }
+__device__ __forceinline__ float rel_factor(unsigned mx) { return mx ? exp2_int(-(ilog2_bits(mx) + 1)) : 0.f; }
+
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+__device__ __forceinline__ float wave_max(float m) {
+  for (int off = 1; off < WAVE; off <<= 1) m = fmaxf(m, shfl_xor(m, off));
+  return m;
+}
+
+// Start of a pass: exponents and largest mantissas of every table (the
+// histogram's, table 0, is bounded by the largest weighted degree).
+__global__ void __launch_bounds__(BLOCK) k_rel_init(int *e, unsigned *mx, int ntab, int b, unsigned hist_bits) {
+  for (int q = threadIdx.x; q < ntab * b; q += BLOCK) {
+    e[q] = 0;
+    mx[q] = q < b ? hist_bits : 0u;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Neighbour-colour histogram H(i, c'), c' the relative colours of i.  A wave
+// takes R consecutive rows, lanes over their entries; counts go to LDS (32-bit
+// integers without weights, T with them).  JG colourings share the index loads.
+// Rows of at least tlong entries are segments taken by whole blocks.
+// Bound by the colour bytes' gathers (one address per lane).  LDS adds instead
+// of a ballot or a butterfly per colour: 10M entries x 8 colourings 850 -> 369
+// us, 4M weighted entries in FP64 363 -> 50 us.
+
+template <typename T, bool WEIGHTED, int JG>
+__global__ void __launch_bounds__(BLOCK) k_rel_hist(RelHistArgs a) {
+  using C = typename std::conditional<WEIGHTED, T, unsigned>::type;
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
+  const int R = a.R, k = a.k, per = JG * R * k;
+  C *accb = (C *)smem;
+  C *acc = accb + (size_t)wv * per;
+  T *H = (T *)a.H;
+  T *Pt = (T *)a.partial;
+  const int jg0 = blockIdx.y * JG;
+  const int nj = min(JG, a.b - jg0);
+  const uint8_t *col = a.colors + (int64_t)(a.j0 + jg0) * a.n;
+  for (int q = lane; q < per; q += WAVE) acc[q] = C(0);
+  wave_lds_fence();
+  bool ovf = false;
+
+  // entries [first, cnt) with the given stride of a range starting at beg
+  auto walk = [&](int64_t beg, int first, int stride, int cnt, const int *ro, int nr) {
+    for (int base = first; base < cnt; base += 2 * stride) {
+      int j[2], loc[2], c[2][JG];
+      float wt[2];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const int e = base + q * stride + lane;
+        const bool ok = e < cnt && base + q * stride < cnt;
+        j[q] = ok ? a.col_idx[beg + e] : -1;
+        wt[q] = 1.0f;
+        if constexpr (WEIGHTED) wt[q] = ok ? a.w[beg + e] : 0.0f;
+        loc[q] = 0;
+        for (int r = 1; r < nr; ++r) loc[q] += e >= __builtin_amdgcn_readlane(*ro, r) ? 1 : 0;
+      }
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int u = 0; u < JG; ++u)
+          c[q][u] = j[q] >= 0 && u < nj ? (int)col[(int64_t)u * a.n + j[q]] : -1;
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int u = 0; u < JG; ++u)
+          if (c[q][u] >= 0) {
+            C *p = acc + ((size_t)u * R + loc[q]) * k + c[q][u];
+            if constexpr (WEIGHTED) rel_add<C>(p, (C)wt[q], true, ovf);
+            else __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+          }
+    }
+  };
+
+  // segments of long rows: the block's waves share the entries
+  for (int s = blockIdx.x; s < a.n_seg; s += gridDim.x) {
+    const int row = a.seg_row[s], len = a.seg_len[s], slot = a.seg_slot[s];
+    const int none = 0;
+    walk(a.seg_beg[s], wv * WAVE, WAVE * WAVES_PER_BLOCK, len, &none, 1);
+    __syncthreads();
+    for (int q = threadIdx.x; q < nj * (int)a.ldh; q += BLOCK) {
+      const int u = q / (int)a.ldh, rc = q - u * (int)a.ldh;
+      const int r = col[(int64_t)u * a.n + row];
+      const int cc = rc < r ? rc : rc + 1;
+      T v = T(0);
+      if (rc < k - 1)
+        for (int w2 = 0; w2 < WAVES_PER_BLOCK; ++w2) v += (T)accb[(size_t)w2 * per + (size_t)u * R * k + cc];
+      T *dst = slot < 0 ? H + (jg0 + u) * a.hplane + (int64_t)row * a.ldh
+                        : Pt + (jg0 + u) * a.pplane + (int64_t)slot * a.ldh;
+      dst[rc] = v;
+    }
+    __syncthreads();
+    for (int u = 0; u < JG; ++u)
+      if (lane < k) acc[(size_t)u * R * k + lane] = C(0);
+    wave_lds_fence();
+  }
+
+  const int64_t groups = (a.n + R - 1) / R;
+  for (int64_t g = (int64_t)blockIdx.x * WAVES_PER_BLOCK + wv; g < groups; g += (int64_t)gridDim.x * WAVES_PER_BLOCK) {
+    const int64_t row0 = g * R;
+    const int nr = (int)min<int64_t>(R, a.n - row0);
+    const int64_t rp = a.row_ptr[row0 + min(lane, nr)];
+    const int64_t beg = __shfl(rp, 0), end = __shfl(rp, nr);
+    const int64_t nxt = __shfl(rp, min(lane + 1, nr));
+    const uint64_t lm = __ballot(lane < nr && nxt - rp >= a.tlong);
+    if (lm == 0) {
+      const int ro = (int)(rp - beg);
+      walk(beg, 0, WAVE, (int)(end - beg), &ro, nr);
+    } else {
+      for (int r = 0; r < nr; ++r) {
+        if (lm >> r & 1) continue;
+        const int64_t b0 = __shfl(rp, r), b1 = __shfl(rp, r + 1);
+        // every entry of this row is at or past its own start and before the next
+        const int ro = lane <= r ? 0 : INT32_MAX;
+        walk(b0, 0, WAVE, (int)(b1 - b0), &ro, nr);
+      }
+    }
+    wave_lds_fence();
+    for (int q = lane; q < nj * nr * (int)a.ldh; q += WAVE) {
+      const int u = q / (nr * (int)a.ldh), q2 = q - u * nr * (int)a.ldh;
+      const int loc = q2 / (int)a.ldh, rc = q2 - loc * (int)a.ldh;
+      if (lm >> loc & 1) continue;
+      const int r = col[(int64_t)u * a.n + row0 + loc];
+      const int cc = rc < r ? rc : rc + 1;
+      H[(jg0 + u) * a.hplane + (row0 + loc) * a.ldh + rc] =
+          rc < k - 1 ? (T)acc[((size_t)u * R + loc) * k + cc] : T(0);
+    }
+    wave_lds_fence();
+    for (int q = lane; q < per; q += WAVE) acc[q] = C(0);
+    wave_lds_fence();
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Aggregation.  A wave takes R consecutive rows of one colouring (blockIdx.y)
+// and walks their entries: streams of LP lanes read whole neighbour rows with
+// 16-byte loads, UNR per lane in flight, and put them in the wave's LDS stage;
+// while the next ones are in flight, lane p adds to output position p (NP per
+// lane) the staged element its set takes from each row, through a map from
+// (neighbour colour, absolute set) to the neighbour's column (a staged zero
+// where the set lacks the colour).  Outputs of at most 32 columns are shared by
+// SW = 64 / (columns, rounded up to a power of two) lane groups that take every
+// SW-th entry and are summed by a butterfly at the end of the row.  Rows of at
+// least tlong entries are segments taken by whole blocks, longest first, the
+// four waves' sums added in wave order.
+// Bound by the 128-byte lines gathered from beyond the L2: 70 columns of FP32
+// (three lines) over 10M entries x 8 colourings take 4.3 ms, 7.1 TB/s of lines
+// (random 256-byte rows: 8.6 TB/s from a 24 MB table, 7.2 from 128 MB, 6.0 from
+// 4 GB).  Whole rows instead of column chunks read every index once per
+// colouring and need no chunk's worth of row descriptors per row: 1.3M entries,
+// 3 colourings, five aggregations with k = 9: 3.58 -> 1.19 ms.
+
+template <typename T, bool WEIGHTED, int NP, bool SPLIT>
+__global__ void __launch_bounds__(BLOCK) k_rel_spmm(RelSpmmArgs a) {
+  constexpr int N = V16<T>::N;
+  constexpr int UNR = 4, UA = 4;
+  using A = Arith<T>;
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
+  const int jj = blockIdx.y;
+  const int CW = a.cw, SR = a.sr;
+  uint16_t *lmap = (uint16_t *)smem;   // [k][CW]
+  uint16_t *lout = lmap + a.k * CW;    // [k][wout4]
+  T *stg0 = (T *)(smem + ((a.k * (CW + a.wout4) * 2 + 15) & ~15));
+  const int streams = a.streams, E = UNR * streams;
+  T *stg = stg0 + (size_t)wv * E * SR;
+  for (int q = threadIdx.x; q < a.k * CW / 2; q += BLOCK) ((unsigned *)lmap)[q] = ((const unsigned *)a.map)[q];
+  for (int q = threadIdx.x; q < a.k * a.wout4 / 2; q += BLOCK) ((unsigned *)lout)[q] = ((const unsigned *)a.olist)[q];
+  for (int q = lane; q < E; q += WAVE) stg[q * SR + SR - 4] = T(0);  // the staged zeros
+  __syncthreads();
+  const uint8_t *col = a.colors + (int64_t)(a.j0 + jj) * a.n;
+  const T *__restrict__ M = (const T *)a.M + jj * a.mplane;
+  T *__restrict__ B = (T *)a.B + jj * a.bplane;
+  T *__restrict__ Pt = (T *)a.partial + jj * a.pplane;
+  T f = T(1);
+  if constexpr (sizeof(T) == 4) {
+    f = rel_factor(a.mx_in[jj]);
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.e_out[jj] = rel_frame(a.e_in[jj], a.mx_in[jj]);
+  }
+  const int stream = lane / a.lp, vec = lane - stream * a.lp;
+  const bool act = stream < streams;
+  // output position and entry group of this lane
+  const int gw = SPLIT ? a.gw : WAVE;      // lanes of a group
+  const int p0 = SPLIT ? lane & (gw - 1) : lane, grp = SPLIT ? lane / gw : 0;
+  const int SW = SPLIT ? WAVE / gw : 1;
+  float cmax = 0.f;
+  bool ovf = false;
+  T acc[NP];
+  int pabs[NP];  // absolute sets of the current row's positions (0: past the end)
+  bool pok[NP];
+#pragma unroll
+  for (int u = 0; u < NP; ++u) pok[u] = p0 + u * WAVE < a.wout;
+
+  auto open_row = [&](int r) {
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+      acc[u] = T(0);
+      pabs[u] = pok[u] ? lout[r * a.wout4 + p0 + u * WAVE] : 0;
+    }
+  };
+  // entries [pos, stop) of the stage, whose first entry is t0
+  auto add_staged = [&](int t0, int pos, int stop, int inf, float wt) {
+    for (int i = pos; i < stop; i += UA * SW) {
+      T x[UA][NP];
+      int o[UA][NP];
+#pragma unroll
+      for (int u = 0; u < UA; ++u) {
+        const int idx = min(SPLIT ? i + u * SW + grp : i + u, stop - 1);
+        const int c = CW * (SPLIT ? shfl_i32(inf, idx) : __builtin_amdgcn_readlane(inf, idx));
+#pragma unroll
+        for (int v = 0; v < NP; ++v) o[u][v] = lmap[c + pabs[v]];
+      }
+#pragma unroll
+      for (int u = 0; u < UA; ++u) {
+        const int idx = min(SPLIT ? i + u * SW + grp : i + u, stop - 1);
+#pragma unroll
+        for (int v = 0; v < NP; ++v) x[u][v] = stg[(idx - t0) * SR + o[u][v]];
+      }
+#pragma unroll
+      for (int u = 0; u < UA; ++u) {
+        const int idx = SPLIT ? i + u * SW + grp : i + u;
+        float w = 1.f;  // every lane is active here
+        if constexpr (WEIGHTED) w = SPLIT ? shfl(wt, idx) : __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wt), idx & (WAVE - 1)));
+        if (idx < stop) {
+          if constexpr (WEIGHTED) {
+#pragma unroll
+            for (int v = 0; v < NP; ++v) acc[v] = A::fma((T)w, x[u][v], acc[v], ovf);
+          } else if constexpr (is_u64<T>) {
+#pragma unroll
+            for (int v = 0; v < NP; ++v) {
+              bool o2 = false;
+              acc[v] = A::add(acc[v], x[u][v], o2);
+              ovf |= o2 && pok[v];
+            }
+          } else {
+#pragma unroll
+            for (int v = 0; v < NP; ++v) acc[v] = A::add(acc[v], x[u][v], ovf);
+          }
+        }
+      }
+    }
+  };
+  auto sum_groups = [&]() {
+    if constexpr (SPLIT) {
+      for (int off = gw; off < WAVE; off <<= 1)
+#pragma unroll
+        for (int v = 0; v < NP; ++v) {
+          bool o2 = false;
+          acc[v] = A::add(acc[v], shfl_xor(acc[v], off), o2);
+          ovf |= o2 && pok[v];
+        }
+    }
+  };
+  // Walk the entries [beg, beg + cnt) whose rows are cut at ro (lane q: offset
+  // of row q); rows r0 .. r1-1 are opened and, except in a segment, written.
+  // first / stride: the 64-entry blocks this wave takes.
+  auto walk = [&](int64_t beg, int first, int stride, int cnt, int ro, int r0, int r1, int rcol, int64_t row0, bool seg) {
+    int cur = r0;
+    open_row(__builtin_amdgcn_readlane(rcol, cur));
+    auto flush = [&]() {
+      sum_groups();
+      if (!SPLIT || grp == 0) {
+        T *dst = B + (row0 + cur) * a.ldb;
+#pragma unroll
+        for (int v = 0; v < NP; ++v)
+          if (pok[v]) {
+            T x = acc[v];
+            if constexpr (sizeof(T) == 4) {
+              x *= f;
+              cmax = fmaxf(cmax, x);
+            }
+            dst[p0 + v * WAVE] = x;
+          }
+      }
+    };
+    // Loads are unconditional (lanes past the end repeat the last entry): a load
+    // under a condition is waited for where the branches meet.
+    int nx_j = 0;
+    float nx_w = 0.f;
+    auto fetch = [&](int base) {
+      const int64_t e = beg + min(base + lane, cnt - 1);
+      nx_j = a.col_idx[e];
+      if constexpr (WEIGHTED) nx_w = a.w[e];
+    };
+    if (first < cnt) fetch(first);
+    for (int base = first; base < cnt; base += stride) {
+      const int nb = min(WAVE, cnt - base);
+      const int my_j = nx_j;
+      const float my_w = nx_w;
+      u32x4 v[UNR];
+      auto issue = [&](int t0) {
+#pragma unroll
+        for (int q = 0; q < UNR; ++q) {
+          const int jq = shfl_i32(my_j, min(t0 + q * streams + stream, nb - 1));
+          v[q] = *(const u32x4 *)(M + (int64_t)jq * a.ldm + vec * N);
+        }
+      };
+      issue(0);
+      const int inf = col[my_j];
+      fetch(base + stride);
+      for (int t0 = 0; t0 < nb; t0 += E) {
+        wave_lds_fence();  // the previous batch has been read
+#pragma unroll
+        for (int q = 0; q < UNR; ++q) {
+          const int sl = q * streams + stream;
+          if (act) *(u32x4 *)(stg + sl * SR + vec * N) = v[q];
+        }
+        issue(t0 + E);
+        wave_lds_fence();
+        int pos = t0;
+        const int lim = min(t0 + E, nb);
+        while (pos < lim) {
+          if (!seg)
+            while (cur < r1 - 1 && __builtin_amdgcn_readlane(ro, cur + 1) <= base + pos) {
+              flush();
+              ++cur;
+              open_row(__builtin_amdgcn_readlane(rcol, cur));
+            }
+          const int stop = seg || cur == r1 - 1 ? lim : min(lim, __builtin_amdgcn_readlane(ro, cur + 1) - base);
+          add_staged(t0, pos, stop, inf, my_w);
+          pos = stop;
+        }
+      }
+    }
+    if (!seg)
+      for (;;) {
+        flush();
+        if (++cur == r1) break;
+        open_row(__builtin_amdgcn_readlane(rcol, cur));
+      }
+  };
+
+  for (int s = blockIdx.x; s < a.n_seg; s += gridDim.x) {
+    const int row = a.seg_row[s], slot = a.seg_slot[s], len = a.seg_len[s];
+    const int r = col[row];
+    walk(a.seg_beg[s], wv * WAVE, WAVE * WAVES_PER_BLOCK, len, 0, 0, 1, r, row, true);
+    sum_groups();
+    __syncthreads();  // every wave is done with its stage
+    T *red = stg0;    // [waves][wout]
+    if (!SPLIT || grp == 0)
+#pragma unroll
+      for (int v = 0; v < NP; ++v)
+        if (pok[v]) red[wv * a.wout + p0 + v * WAVE] = acc[v];
+    __syncthreads();
+    T *dst = slot < 0 ? B + (int64_t)row * a.ldb : Pt + (int64_t)slot * a.ldb;
+    for (int p = threadIdx.x; p < a.wout; p += BLOCK) {
+      T x = red[p];
+      for (int w2 = 1; w2 < WAVES_PER_BLOCK; ++w2) x = A::add(x, red[w2 * a.wout + p], ovf);
+      if constexpr (sizeof(T) == 4) {
+        x *= f;
+        if (slot < 0) cmax = fmaxf(cmax, x);
+      }
+      dst[p] = x;
+    }
+    __syncthreads();
+    for (int q = lane; q < E; q += WAVE) stg[q * SR + SR - 4] = T(0);
+    wave_lds_fence();
+  }
+
+  const int R = a.R;
+  const int64_t groups = (a.n + R - 1) / R;
+  for (int64_t g = (int64_t)blockIdx.x * WAVES_PER_BLOCK + wv; g < groups; g += (int64_t)gridDim.x * WAVES_PER_BLOCK) {
+    const int64_t row0 = g * R;
+    const int nr = __builtin_amdgcn_readfirstlane((int)min<int64_t>(R, a.n - row0));
+    const int64_t rp = a.row_ptr[row0 + min(lane, nr)];
+    const int rcol = lane < nr ? (int)col[row0 + lane] : 0;
+    const int64_t nxt = __shfl(rp, min(lane + 1, nr));
+    const uint64_t lm = __ballot(lane < nr && nxt - rp >= a.tlong);
+    // runs of consecutive rows below tlong
+    for (int r0 = 0; r0 < nr;) {
+      if (lm >> r0 & 1) {
+        ++r0;
+        continue;
+      }
+      const uint64_t rest = lm >> r0;
+      const int r1 = rest ? min(nr, r0 + (int)__builtin_ctzll(rest)) : nr;
+      const int64_t beg = __shfl(rp, r0);
+      const int cnt = __builtin_amdgcn_readfirstlane((int)(__shfl(rp, r1) - beg));
+      // rows of the run are below tlong, so their offsets fit 32 bits
+      walk(beg, 0, WAVE, cnt, (int)(rp - beg), r0, r1, rcol, row0, false);
+      r0 = r1;
+    }
+  }
+  if constexpr (is_u64<T>) {
+    if (ovf) atomicOr(a.ovf, 1);
+  }
+  if constexpr (sizeof(T) == 4) {
+    cmax = wave_max(cmax);
+    if (lane == 0 && cmax > 0.f) atomicMax(a.mx_out + jj, __float_as_uint(cmax));
+  }
+}
+
+// The same aggregation for narrow outputs: a lane adds the elements it has read
+// to the row's absolute sets in LDS, through the neighbour colour's map.  The
+// sums are doubles for FP32 and FP64 tables (float LDS adds run at a fraction
+// of the rate of 8-byte ones), 64-bit integers in U64.  R rows per wave have
+// their sums in LDS at a time; a row's output positions pick its sets.
+
+template <typename T, bool WEIGHTED>
+__global__ void __launch_bounds__(BLOCK) k_rel_spmm_add(RelSpmmArgs a) {
+  constexpr int N = V16<T>::N;
+  constexpr int UNR = 4;
+  using C = typename std::conditional<is_u64<T>, uint64_t, double>::type;
+  struct alignas(2 * N) M16 { uint16_t x[N]; };
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
+  const int jj = blockIdx.y;
+  const int S = a.cw + 4, R = a.R;  // the element cw takes the padding of a gathered row
+  uint16_t *lmap = (uint16_t *)smem;        // [k][wmap]
+  uint16_t *lout = lmap + a.k * a.wmap;     // [k][wout4]
+  C *acc0 = (C *)(smem + ((a.k * (a.wmap + a.wout4) * 2 + 15) & ~15));
+  C *acc = acc0 + (size_t)wv * R * S;
+  for (int q = threadIdx.x; q < a.k * a.wmap / 2; q += BLOCK) ((unsigned *)lmap)[q] = ((const unsigned *)a.smap)[q];
+  for (int q = threadIdx.x; q < a.k * a.wout4 / 2; q += BLOCK) ((unsigned *)lout)[q] = ((const unsigned *)a.olist)[q];
+  for (int q = lane; q < R * S; q += WAVE) acc[q] = C(0);
+  __syncthreads();
+  const uint8_t *col = a.colors + (int64_t)(a.j0 + jj) * a.n;
+  const T *__restrict__ M = (const T *)a.M + jj * a.mplane;
+  T *__restrict__ B = (T *)a.B + jj * a.bplane;
+  T *__restrict__ Pt = (T *)a.partial + jj * a.pplane;
+  T f = T(1);
+  if constexpr (sizeof(T) == 4) {
+    f = rel_factor(a.mx_in[jj]);
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.e_out[jj] = rel_frame(a.e_in[jj], a.mx_in[jj]);
+  }
+  const int streams = a.streams, E = UNR * streams;
+  const int stream = lane / a.lp, vec = lane - stream * a.lp;
+  const bool act = stream < streams;
+  float cmax = 0.f;
+  bool ovf = false;
+
+  // entries first, first + stride, ... (64 at a time) of [beg, beg + cnt), whose
+  // rows r0 .. r1-1 are cut at ro (lane q: offset of row q)
+  auto walk = [&](int64_t beg, int first, int stride, int cnt, int ro, int r0, int r1) {
+    int nx_j = 0;
+    float nx_w = 0.f;
+    auto fetch = [&](int base) {
+      const int64_t e = beg + min(base + lane, cnt - 1);
+      nx_j = a.col_idx[e];
+      if constexpr (WEIGHTED) nx_w = a.w[e];
+    };
+    if (first < cnt) fetch(first);
+    for (int base = first; base < cnt; base += stride) {
+      const int nb = min(WAVE, cnt - base);
+      const int my_j = nx_j;
+      const float my_w = nx_w;
+      u32x4 v[UNR];
+      auto issue = [&](int q, int t0) {
+        const int jq = shfl_i32(my_j, min(t0 + q * streams + stream, nb - 1));
+        v[q] = *(const u32x4 *)(M + (int64_t)jq * a.ldm + vec * N);
+      };
+#pragma unroll
+      for (int q = 0; q < UNR; ++q) issue(q, 0);
+      const int mc = col[my_j];
+      fetch(base + stride);
+      int loc = r0;
+      for (int r = r0 + 1; r < r1; ++r) loc += base + lane >= __builtin_amdgcn_readlane(ro, r) ? 1 : 0;
+      // LDS offsets of the colour's map and of the row's sums
+      const int inf = mc * a.wmap | (loc * S) << 16;
+      for (int t0 = 0; t0 < nb; t0 += E) {
+#pragma unroll
+        for (int q = 0; q < UNR; ++q) {
+          const int sq = t0 + q * streams + stream;
+          const int iq = shfl_i32(inf, min(sq, nb - 1));
+          T wq = T(1);
+          if constexpr (WEIGHTED) wq = (T)shfl(my_w, min(sq, nb - 1));
+          const V16<T> x = __builtin_bit_cast(V16<T>, v[q]);
+          issue(q, t0 + E);
+          if (act && sq < nb) {
+            const M16 mp = *(const M16 *)(lmap + (iq & 0xFFFF) + vec * N);
+            C *row = acc + ((unsigned)iq >> 16);
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+              C y = (C)x.x[u];
+              if constexpr (WEIGHTED) y *= (C)wq;
+              rel_add<C>(row + mp.x[u], y, mp.x[u] != a.cw, ovf);
+            }
+          }
+        }
+      }
+    }
+  };
+
+  for (int s = blockIdx.x; s < a.n_seg; s += gridDim.x) {
+    const int row = a.seg_row[s], slot = a.seg_slot[s];
+    const int r = col[row];
+    walk(a.seg_beg[s], wv * WAVE, WAVE * WAVES_PER_BLOCK, a.seg_len[s], 0, 0, 1);
+    __syncthreads();
+    T *dst = slot < 0 ? B + (int64_t)row * a.ldb : Pt + (int64_t)slot * a.ldb;
+    for (int p = threadIdx.x; p < a.wout; p += BLOCK) {
+      const C *q = acc0 + lout[r * a.wout4 + p];
+      C x = q[0];
+      for (int w2 = 1; w2 < WAVES_PER_BLOCK; ++w2) x = Arith<C>::add(x, q[(size_t)w2 * R * S], ovf);
+      T y = (T)x;
+      if constexpr (sizeof(T) == 4) {
+        y *= f;
+        if (slot < 0) cmax = fmaxf(cmax, y);
+      }
+      dst[p] = y;
+    }
+    __syncthreads();
+    for (int q = lane; q < S; q += WAVE) acc[q] = C(0);
+    wave_lds_fence();
+  }
+
+  const int64_t groups = (a.n + R - 1) / R;
+  const int dl = WAVE / a.wout, dp = WAVE - dl * a.wout;
+  const int l0 = lane / a.wout, p0 = lane - l0 * a.wout;
+  for (int64_t g = (int64_t)blockIdx.x * WAVES_PER_BLOCK + wv; g < groups; g += (int64_t)gridDim.x * WAVES_PER_BLOCK) {
+    const int64_t row0 = g * R;
+    const int nr = __builtin_amdgcn_readfirstlane((int)min<int64_t>(R, a.n - row0));
+    const int64_t rp = a.row_ptr[row0 + min(lane, nr)];
+    const int rcol = lane < nr ? (int)col[row0 + lane] : 0;
+    const int64_t nxt = __shfl(rp, min(lane + 1, nr));
+    const uint64_t lm = __ballot(lane < nr && nxt - rp >= a.tlong);
+    for (int r0 = 0; r0 < nr;) {
+      if (lm >> r0 & 1) {
+        ++r0;
+        continue;
+      }
+      const uint64_t rest = lm >> r0;
+      const int r1 = rest ? min(nr, r0 + (int)__builtin_ctzll(rest)) : nr;
+      const int64_t beg = __shfl(rp, r0);
+      const int cnt = __builtin_amdgcn_readfirstlane((int)(__shfl(rp, r1) - beg));
+      walk(beg, 0, WAVE, cnt, (int)(rp - beg), r0, r1);
+      r0 = r1;
+    }
+    wave_lds_fence();
+    int loc = l0, p = p0;
+    while (__ballot(loc < nr)) {
+      const int r = shfl_i32(rcol, loc & (WAVE - 1));
+      if (loc < nr && !(lm >> loc & 1)) {
+        T y = (T)acc[loc * S + lout[r * a.wout4 + p]];
+        if constexpr (sizeof(T) == 4) {
+          y *= f;
+          cmax = fmaxf(cmax, y);
+        }
+        B[(row0 + loc) * a.ldb + p] = y;
+      }
+      p += dp;
+      loc += dl;
+      if (p >= a.wout) {
+        p -= a.wout;
+        ++loc;
+      }
+    }
+    wave_lds_fence();
+    for (int q = lane; q < R * S; q += WAVE) acc[q] = C(0);
+    wave_lds_fence();
+  }
+  if constexpr (is_u64<T>) {
+    if (ovf) atomicOr(a.ovf, 1);
+  }
+  if constexpr (sizeof(T) == 4) {
+    cmax = wave_max(cmax);
+    if (lane == 0 && cmax > 0.f) atomicMax(a.mx_out + jj, __float_as_uint(cmax));
+  }
+}
+
+// Partial rows of a long row summed in slot order.
+template <typename T>
+__global__ void __launch_bounds__(BLOCK) k_rel_combine(RelCombineArgs a) {
+  constexpr int N = V16<T>::N;
+  const int jj = blockIdx.y;
+  const int64_t nvec = (a.w + N - 1) / N, total = nvec * a.n_long;
+  const T *P = (const T *)a.partial + jj * a.pplane;
+  T *B = (T *)a.B + jj * a.bplane;
+  bool ovf = false;
+  float cmax = 0.f;
+  for (int64_t q = (int64_t)blockIdx.x * BLOCK + threadIdx.x; q < total; q += (int64_t)gridDim.x * BLOCK) {
+    const int64_t h = q / nvec, v = q - h * nvec;
+    const int64_t s0 = a.long_slot0[h];
+    const int ns = a.long_nslot[h];
+    V16<T> acc = *(const V16<T> *)(P + s0 * a.ld + v * N);
+    for (int s = 1; s < ns; ++s) {
+      const V16<T> x = *(const V16<T> *)(P + (s0 + s) * a.ld + v * N);
+#pragma unroll
+      for (int u = 0; u < N; ++u) {
+        bool o = false;
+        acc.x[u] = Arith<T>::add(acc.x[u], x.x[u], o);
+        ovf |= o && v * N + u < a.w;  // padding may hold anything
+      }
+    }
+    *(V16<T> *)(B + (int64_t)a.long_row[h] * a.ld + v * N) = acc;
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+      if (v * N + u < a.w) cmax = fmaxf(cmax, (float)acc.x[u]);
+  }
+  if constexpr (is_u64<T>) {
+    if (ovf) atomicOr(a.ovf, 1);
+  }
+  if (a.mx) {
+    cmax = wave_max(cmax);
+    if ((threadIdx.x & (WAVE - 1)) == 0 && cmax > 0.f) atomicMax(a.mx + jj, __float_as_uint(cmax));
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Multiply-add of a split whose active child has several vertices:
+//   M_s(i, Q) = sum over the pairs (x, y) of Q of M_a(i, x) B(i, y).
+// A block stages R consecutive rows of both tables in LDS, transposed (R rows
+// plus one 16-byte vector per column, so that lanes on different columns
+// spread over the banks); a thread owns output columns and keeps R sums.  Half
+// the columns of the absolute tables and rows in order: 1.42 -> 0.78 ms on
+// average over the splits of the nine-vertex trees (4M rows of about 60 columns
+// three times, 2.9 GB: 3.7 TB/s).
+
+template <typename T, int R, int NT>
+__global__ void __launch_bounds__(NT) k_rel_ema(RelEmaArgs a) {
+  constexpr int N = V16<T>::N;
+  constexpr int RP = R + N;
+  constexpr bool SC = sizeof(T) == 4;
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int jj = blockIdx.y;
+  T *la = (T *)smem;
+  T *lb = la + (size_t)RP * a.wa;
+  const T *X = (const T *)a.X + jj * a.xplane;
+  const T *Y = (const T *)a.Y + jj * a.yplane;
+  T *Ms = (T *)a.M + jj * a.mplane;
+  T fx = T(1), fy = T(1);
+  if constexpr (SC) {
+    fx = rel_factor(a.mxx[jj]);
+    fy = rel_factor(a.mxy[jj]);
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+      a.e_out[jj] = rel_frame(a.ex[jj], a.mxx[jj]) + rel_frame(a.ey[jj], a.mxy[jj]);
+  }
+  bool ovf = false;
+  float cmax = 0.f;
+  // eight 16-byte loads in flight per thread
+  auto stage = [&](const T *src, int64_t ld, int w, int64_t i0, int nrow, T f, T *dst) {
+    const int nv = (w + N - 1) / N, total = nrow * nv;
+    for (int x0 = threadIdx.x; x0 < total; x0 += 4 * NT) {
+      V16<T> v[4];
+      int r[4], q[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int x = min(x0 + u * NT, total - 1);
+        r[u] = x / nv;
+        q[u] = x - r[u] * nv;
+        v[u] = *(const V16<T> *)(src + (i0 + r[u]) * ld + q[u] * N);
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (x0 + u * NT < total) {
+#pragma unroll
+          for (int e = 0; e < N; ++e)
+            if (q[u] * N + e < w) dst[(q[u] * N + e) * RP + r[u]] = v[u].x[e] * f;
+        }
+      }
+    }
+  };
+  const int64_t ntiles = (a.n + R - 1) / R;
+  for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+    const int64_t i0 = t * R;
+    const int nrow = (int)min<int64_t>(R, a.n - i0);
+    __syncthreads();
+    stage(X, a.ldx, a.wa, i0, nrow, fx, la);
+    stage(Y, a.ldy, a.wb, i0, nrow, fy, lb);
+    __syncthreads();
+    for (int C = threadIdx.x; C < a.ws; C += NT) {
+      T acc[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) acc[r] = T(0);
+      for (int q0 = 0; q0 < a.np; q0 += 8) {
+        uint32_t p[8];
+#pragma unroll
+        for (int qq = 0; qq < 8; ++qq) p[qq] = a.pairs[(int64_t)min(q0 + qq, a.np - 1) * a.ws + C];
+#pragma unroll
+        for (int qq = 0; qq < 8; ++qq) {
+          if (q0 + qq >= a.np) break;  // uniform
+          const V16<T> *xa = (const V16<T> *)(la + (int)(p[qq] & 0xFFFFu) * RP);
+          const V16<T> *yb = (const V16<T> *)(lb + (int)(p[qq] >> 16) * RP);
+#pragma unroll
+          for (int v = 0; v < R / N; ++v) {
+            const V16<T> xv = xa[v], yv = yb[v];
+            if constexpr (is_u64<T>) {
+              // rows past the end hold stale values: they may not raise the flag
+#pragma unroll
+              for (int e = 0; e < N; ++e) {
+                bool o = false;
+                acc[v * N + e] = Arith<T>::fma(xv.x[e], yv.x[e], acc[v * N + e], o);
+                ovf |= o && v * N + e < nrow;
+              }
+            } else {
+#pragma unroll
+              for (int e = 0; e < N; ++e) acc[v * N + e] = Arith<T>::fma(xv.x[e], yv.x[e], acc[v * N + e], ovf);
+            }
+          }
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        if (r < nrow) {
+          Ms[(i0 + r) * a.ldm + C] = acc[r];
+          if constexpr (SC) cmax = fmaxf(cmax, (float)acc[r]);
+        }
+      }
+    }
+  }
+  if constexpr (is_u64<T>) {
+    if (ovf) atomicOr(a.ovf, 1);
+  }
+  if constexpr (SC) {
+    cmax = wave_max(cmax);
+    if ((threadIdx.x & (WAVE - 1)) == 0 && cmax > 0.f) atomicMax(a.mx_out + jj, __float_as_uint(cmax));
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Root reduction: sum over vertices of sum over the list of X(i, x) Y(i, y)
+// (Y absent: sum of X(i, x)).  LP lanes per vertex stride over the list, U
+// vertices per lane group in flight; a lane sums its share of a vertex in T
+// and its vertices in double (uint64 in U64); fixed-order block reduction.  The
+// list's partners are complements when k = t, so both reads are coalesced and
+// nothing is staged: 0.97 -> 0.18 ms for the nine-vertex trees (4M rows, 1 GB).
+
+template <typename T, bool HASY>
+__global__ void __launch_bounds__(BLOCK) k_rel_root(RelRootArgs a) {
+  using A = Arith<T>;
+  using Acc = typename std::conditional<is_u64<T>, uint64_t, double>::type;
+  constexpr int U = 4;
+  constexpr bool SC = sizeof(T) == 4;
+  __shared__ Acc red[WAVES_PER_BLOCK];
+  const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
+  const int jj = blockIdx.y;
+  const T *X = (const T *)a.X + jj * a.xplane;
+  const T *Y = HASY ? (const T *)a.Y + jj * a.yplane : nullptr;
+  T fx = T(1), fy = T(1);
+  if constexpr (SC) {
+    fx = rel_factor(a.mxx[jj]);
+    if constexpr (HASY) fy = rel_factor(a.mxy[jj]);
+  }
+  bool ovf = false;
+  Acc tot = Acc(0);
+  const int LP = a.lp, rw = WAVE / LP;
+  const int sub = lane / LP, l = lane - sub * LP;
+  const int64_t step = (int64_t)rw * U;
+  const int64_t nwaves = (int64_t)gridDim.x * WAVES_PER_BLOCK;
+  for (int64_t i0 = ((int64_t)blockIdx.x * WAVES_PER_BLOCK + wv) * step; i0 < a.n; i0 += nwaves * step) {
+    T s[U];
+    const T *xr[U], *yr[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      s[u] = T(0);
+      const int64_t i = min(i0 + u * rw + sub, a.n - 1);
+      xr[u] = X + i * a.ldx;
+      yr[u] = HASY ? Y + i * a.ldy : nullptr;
+    }
+    for (int64_t q = l; q < a.L; q += LP) {
+      const uint32_t p = a.list[q];
+      T x[U], y[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        x[u] = xr[u][p & 0xFFFFu];
+        if constexpr (HASY) y[u] = yr[u][p >> 16];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        T xv = x[u];
+        if constexpr (SC) xv *= fx;
+        bool o = false;
+        if constexpr (HASY) {
+          T yv = y[u];
+          if constexpr (SC) yv *= fy;
+          s[u] = A::fma(xv, yv, s[u], o);
+        } else {
+          s[u] = A::add(s[u], xv, o);
+        }
+        ovf |= o;  // rows past the end repeat the last vertex
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (i0 + u * rw + sub < a.n) {
+        if constexpr (is_u64<Acc>) tot = A::add(tot, s[u], ovf);
+        else tot += (double)s[u];
+      }
+    }
+  }
+  for (int off = 1; off < WAVE; off <<= 1) {
+    if constexpr (is_u64<Acc>) tot = A::add(tot, shfl_xor(tot, off), ovf);
+    else tot += shfl_xor(tot, off);
+  }
+  if (lane == 0) red[wv] = tot;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    Acc b = red[0];
+    for (int q = 1; q < WAVES_PER_BLOCK; ++q) {
+      if constexpr (is_u64<Acc>) b = A::add(b, red[q], ovf);
+      else b += red[q];
+    }
+    ((Acc *)a.partial)[(int64_t)jj * gridDim.x + blockIdx.x] = b;
+  }
+  if constexpr (is_u64<T>) {
+    if (ovf) atomicOr(a.ovf, 1);
+  }
+}
+
+// Block partials of each colouring in a fixed order (one wave per colouring),
+// and in FP32S the exponent of the result.
+template <typename Acc>
+__global__ void __launch_bounds__(WAVE) k_rel_final(RelFinalArgs a) {
+  const int j = blockIdx.x, lane = threadIdx.x;
+  const Acc *pj = (const Acc *)a.partial + (int64_t)j * a.nblk;
+  Acc s = Acc(0);
+  bool o = false;
+  for (int q = lane; q < a.nblk; q += WAVE) {
+    if constexpr (is_u64<Acc>) s = Arith<Acc>::add(s, pj[q], o);
+    else s += pj[q];
+  }
+  for (int off = 1; off < WAVE; off <<= 1) {
+    if constexpr (is_u64<Acc>) s = Arith<Acc>::add(s, shfl_xor(s, off), o);
+    else s += shfl_xor(s, off);
+  }
+  if (o) atomicOr(a.ovf, 1);
+  if (lane == 0) {
+    ((Acc *)a.out)[j] = s;
+    if (a.E) a.E[j] = rel_frame(a.ex[j], a.mxx[j]) + (a.mxy ? rel_frame(a.ey[j], a.mxy[j]) : 0);
+  }
+}
+
+// ===========================================================================
+// launchers
+
+template <typename K, typename A>
+static void rel_go(K kern, const A &a, dim3 grid, int nt, size_t lds, hipStream_t s) {
+  if (lds > 65536) (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  kern<<<grid, nt, lds, s>>>(a);
+}
+
+void launch_rel_init(int *e, unsigned *mx, int ntab, int b, unsigned hist_bits, hipStream_t s) {
+  k_rel_init<<<1, BLOCK, 0, s>>>(e, mx, ntab, b, hist_bits);
+}
+
+template <typename T>
+static void rel_hist_t(const RelHistArgs &a, dim3 grid, hipStream_t s) {
+  const int JG = a.b == 1 ? 1 : 4;
+  const size_t lds = (size_t)WAVES_PER_BLOCK * JG * a.R * a.k * (a.w ? sizeof(T) : 4);
+  if (a.b == 1) {
+    if (a.w) rel_go(k_rel_hist<T, true, 1>, a, grid, BLOCK, lds, s);
+    else rel_go(k_rel_hist<T, false, 1>, a, grid, BLOCK, lds, s);
+  } else {
+    if (a.w) rel_go(k_rel_hist<T, true, 4>, a, grid, BLOCK, lds, s);
+    else rel_go(k_rel_hist<T, false, 4>, a, grid, BLOCK, lds, s);
+  }
+}
+
+void launch_rel_hist(int dtype, const RelHistArgs &a, dim3 grid, hipStream_t s) {
+  if (dtype == DT_F32) rel_hist_t<float>(a, grid, s);
+  else if (dtype == DT_F64) rel_hist_t<double>(a, grid, s);
+  else rel_hist_t<uint64_t>(a, grid, s);
+}
+
+template <typename T, bool WEIGHTED>
+static int rel_spmm_t(const RelSpmmArgs &a, dim3 grid, size_t lds, hipStream_t s) {
+  if (a.add) {
+    rel_go(k_rel_spmm_add<T, WEIGHTED>, a, grid, BLOCK, lds, s);
+    return 0;
+  }
+  if (a.gw < WAVE) {
+    rel_go(k_rel_spmm<T, WEIGHTED, 1, true>, a, grid, BLOCK, lds, s);
+    return 0;
+  }
+  switch ((a.wout + WAVE - 1) / WAVE) {
+    case 1: rel_go(k_rel_spmm<T, WEIGHTED, 1, false>, a, grid, BLOCK, lds, s); return 0;
+    case 2: rel_go(k_rel_spmm<T, WEIGHTED, 2, false>, a, grid, BLOCK, lds, s); return 0;
+    case 3: rel_go(k_rel_spmm<T, WEIGHTED, 3, false>, a, grid, BLOCK, lds, s); return 0;
+    default: return -1;
+  }
+}
+
+int launch_rel_spmm(int dtype, const RelSpmmArgs &a, dim3 grid, size_t lds, hipStream_t s) {
+  if (dtype == DT_F32) return a.w ? rel_spmm_t<float, true>(a, grid, lds, s) : rel_spmm_t<float, false>(a, grid, lds, s);
+  if (dtype == DT_F64) return a.w ? rel_spmm_t<double, true>(a, grid, lds, s) : rel_spmm_t<double, false>(a, grid, lds, s);
+  return a.w ? -1 : rel_spmm_t<uint64_t, false>(a, grid, lds, s);
+}
+
+void launch_rel_combine(int dtype, const RelCombineArgs &a, int b, hipStream_t s) {
+  const int N = dtype == DT_F32 ? 4 : 2;
+  const int64_t blocks = (a.n_long * (a.ld / N) + BLOCK - 1) / BLOCK;
+  const dim3 grid((unsigned)std::min<int64_t>(blocks, 4096), (unsigned)b);
+  if (dtype == DT_F32) k_rel_combine<float><<<grid, BLOCK, 0, s>>>(a);
+  else if (dtype == DT_F64) k_rel_combine<double><<<grid, BLOCK, 0, s>>>(a);
+  else k_rel_combine<uint64_t><<<grid, BLOCK, 0, s>>>(a);
+}
+
+template <typename T, int NT>
+static int rel_ema_nt(const RelEmaArgs &a, int R, dim3 grid, size_t lds, hipStream_t s) {
+  switch (R) {
+    case 4: rel_go(k_rel_ema<T, 4, NT>, a, grid, NT, lds, s); return 0;
+    case 8: rel_go(k_rel_ema<T, 8, NT>, a, grid, NT, lds, s); return 0;
+    case 16: rel_go(k_rel_ema<T, 16, NT>, a, grid, NT, lds, s); return 0;
+    default: return -1;
+  }
+}
+
+template <typename T>
+static int rel_ema_t(const RelEmaArgs &a, int R, int nt, dim3 grid, size_t lds, hipStream_t s) {
+  if (nt == 512) return rel_ema_nt<T, 512>(a, R, grid, lds, s);
+  if (nt == 256) return rel_ema_nt<T, 256>(a, R, grid, lds, s);
+  if (nt == 128) return rel_ema_nt<T, 128>(a, R, grid, lds, s);
+  return -1;
+}
+
+int launch_rel_ema(int dtype, const RelEmaArgs &a, int R, int nt, dim3 grid, size_t lds, hipStream_t s) {
+  if (dtype == DT_F32) return rel_ema_t<float>(a, R, nt, grid, lds, s);
+  if (dtype == DT_F64) return rel_ema_t<double>(a, R, nt, grid, lds, s);
+  return rel_ema_t<uint64_t>(a, R, nt, grid, lds, s);
+}
+
+template <typename T>
+static void rel_root_t(const RelRootArgs &a, dim3 grid, hipStream_t s) {
+  if (a.Y) k_rel_root<T, true><<<grid, BLOCK, 0, s>>>(a);
+  else k_rel_root<T, false><<<grid, BLOCK, 0, s>>>(a);
+}
+
+void launch_rel_root(int dtype, const RelRootArgs &a, dim3 grid, hipStream_t s) {
+  if (dtype == DT_F32) rel_root_t<float>(a, grid, s);
+  else if (dtype == DT_F64) rel_root_t<double>(a, grid, s);
+  else rel_root_t<uint64_t>(a, grid, s);
+}
+
+void launch_rel_final(int dtype, const RelFinalArgs &a, int b, hipStream_t s) {
+  if (dtype == DT_U64) k_rel_final<uint64_t><<<b, WAVE, 0, s>>>(a);
+  else k_rel_final<double><<<b, WAVE, 0, s>>>(a);
+}
+
+}  // namespace sg2v

@@ -77,6 +77,10 @@ constexpr int kXsplitBlocks = 4096;
 constexpr int kRootBlocks = 2048;    // most root blocks (per-block partial sums)
 constexpr int kXsplit = 8;          // neighbour ranges (one per XCD)
 constexpr int64_t kXsplitMin = 512; // tasks at least this long are split by range
+// vertex-relative count: rows this long are walked by whole blocks instead of
+// one wave, in segments of this many entries
+constexpr int64_t kRelLong = 256;
+constexpr int64_t kRelSegment = 1024;
 constexpr double kXpartBytes = 8.0 * (1 << 30);  // range-partial rows of one chunk group
 // graphs whose 128-byte column chunk (n rows) reaches 32 MB: wider chunks and
 // the neighbour-range split by default
@@ -87,6 +91,8 @@ int64_t fl_launch_chunks() {
   const sg2v_tuning_t tu = tuning();
   return tu.launch_chunks > 0 ? std::min<int64_t>(tu.launch_chunks, 65535) : 65535;
 }
+
+constexpr size_t kRelLds = 64 * 1024;  // LDS of a vertex-relative multiply-add tile
 
 int dtype_of(sg2v_mode m) { return m == SG2V_FP32S ? DT_F32 : (m == SG2V_FP64 ? DT_F64 : DT_U64); }
 int esize_of(int dt) { return dt == DT_F32 ? 4 : 8; }
@@ -267,6 +273,13 @@ struct sg2v_graph {
   double long_share = 0.0;          // share of the entries in tasks of >= kXsplitMin neighbours
   int32_t *long_row = nullptr, *long_slot0 = nullptr, *long_nslot = nullptr;
   int32_t n_long = 0;
+  // vertex-relative count: rows of at least kRelLong entries in segments of at
+  // most kRelSegment, longest first; rows of several segments have slots
+  int32_t *seg_row = nullptr, *seg_len = nullptr, *seg_slot = nullptr;
+  int64_t *seg_beg = nullptr;
+  int32_t n_seg = 0, n_rlong = 0;
+  int64_t n_rslots = 0;
+  int32_t *rlong_row = nullptr, *rlong_slot0 = nullptr, *rlong_nslot = nullptr;
   std::map<int, UnitTable> units;  // by G (lanes per neighbour row segment)
   uint16_t *tsplit = nullptr;      // [n_tasks][kXsplit + 1] neighbour-range split offsets
   int64_t *xbounds = nullptr;      // device, kXsplit + 1 range starts (renumbered graphs), or null
@@ -432,6 +445,47 @@ sg2v_status build_panels(sg2v_graph *g, hipStream_t s, sg2v_graph::Panels **out)
   return SG2V_OK;
 }
 
+sg2v_status rel_segments(sg2v_graph *g, const std::vector<int64_t> &rp, hipStream_t s) {
+  std::vector<int32_t> rows;
+  for (int64_t i = 0; i < g->n; ++i)
+    if (rp[i + 1] - rp[i] >= kRelLong) rows.push_back((int32_t)i);
+  std::stable_sort(rows.begin(), rows.end(), [&](int32_t a, int32_t b) {
+    return rp[a + 1] - rp[a] > rp[b + 1] - rp[b];
+  });
+  std::vector<int32_t> row, len, slot, lrow, lslot0, lnslot;
+  std::vector<int64_t> beg;
+  int64_t slots = 0;
+  for (int32_t i : rows) {
+    const int64_t d = rp[i + 1] - rp[i], ns = (d + kRelSegment - 1) / kRelSegment;
+    if (ns > 1) {
+      lrow.push_back(i);
+      lslot0.push_back((int32_t)slots);
+      lnslot.push_back((int32_t)ns);
+    }
+    for (int64_t q = 0; q < ns; ++q) {
+      const int64_t b0 = rp[i] + d * q / ns, b1 = rp[i] + d * (q + 1) / ns;
+      row.push_back(i);
+      beg.push_back(b0);
+      len.push_back((int32_t)(b1 - b0));
+      slot.push_back(ns > 1 ? (int32_t)(slots + q) : -1);
+    }
+    if (ns > 1) slots += ns;
+  }
+  g->n_seg = (int32_t)row.size();
+  g->n_rlong = (int32_t)lrow.size();
+  g->n_rslots = slots;
+  void *p;
+  ST_TRY(upload(row, &p, s)); g->seg_row = (int32_t *)p; g->allocs.push_back(p);
+  ST_TRY(upload(len, &p, s)); g->seg_len = (int32_t *)p; g->allocs.push_back(p);
+  ST_TRY(upload(slot, &p, s)); g->seg_slot = (int32_t *)p; g->allocs.push_back(p);
+  ST_TRY(upload(beg, &p, s)); g->seg_beg = (int64_t *)p; g->allocs.push_back(p);
+  ST_TRY(upload(lrow, &p, s)); g->rlong_row = (int32_t *)p; g->allocs.push_back(p);
+  ST_TRY(upload(lslot0, &p, s)); g->rlong_slot0 = (int32_t *)p; g->allocs.push_back(p);
+  ST_TRY(upload(lnslot, &p, s)); g->rlong_nslot = (int32_t *)p; g->allocs.push_back(p);
+  HIP_TRY(hipStreamSynchronize(s));
+  return SG2V_OK;
+}
+
 sg2v_status graph_tasks(sg2v_graph *g, const std::vector<int64_t> &rp, hipStream_t s) {
   const int64_t n = g->n;
   std::vector<int32_t> row, len, slot;
@@ -495,7 +549,7 @@ sg2v_status graph_tasks(sg2v_graph *g, const std::vector<int64_t> &rp, hipStream
   ST_TRY(upload(lslot0, &p, s)); g->long_slot0 = (int32_t *)p; g->allocs.push_back(p);
   ST_TRY(upload(lnslot, &p, s)); g->long_nslot = (int32_t *)p; g->allocs.push_back(p);
   HIP_TRY(hipStreamSynchronize(s));
-  return SG2V_OK;
+  return rel_segments(g, rp, s);
 }
 
 }  // namespace
@@ -743,6 +797,8 @@ struct DevPlan {
   std::vector<int32_t *> root_list;     // per template
   std::vector<uint32_t *> root_list16;
   std::vector<char *> cpr;  // colour-restricted tables per node
+  std::vector<uint32_t *> rel_pairs, rel_root;  // vertex-relative: per node, per template
+  std::vector<uint16_t *> rel_map;              // per node
 };
 
 // pair-major copy ([q][col]) of a [col][np] x 2 table
@@ -777,6 +833,12 @@ void fill_devplan(const Plan::DeviceTables &d, DevPlan *out) {
   for (void *p : d.root_list16) out->root_list16.push_back((uint32_t *)p);
   out->cpr.assign(nn, nullptr);
   for (size_t i = 0; i < nn && i < d.cpr.size(); ++i) out->cpr[i] = (char *)d.cpr[i];
+  out->rel_pairs.clear();
+  out->rel_map.clear();
+  out->rel_root.clear();
+  for (void *p : d.rel_pairs) out->rel_pairs.push_back((uint32_t *)p);
+  for (void *p : d.rel_map) out->rel_map.push_back((uint16_t *)p);
+  for (void *p : d.rel_root) out->rel_root.push_back((uint32_t *)p);
 }
 
 sg2v_status plan_device(const Plan &P, int device, hipStream_t s, DevPlan *out) {
@@ -838,6 +900,21 @@ sg2v_status plan_device(const Plan &P, int device, hipStream_t s, DevPlan *out) 
       l16[q] = (uint32_t)x | ((uint32_t)(y < 0 ? 0xFFFF : y) << 16);
     }
     if (fits) ST_TRY(upload(l16, &D.root_list16[r], s));
+  }
+  if (rel_ok(P, 4, kRelLds)) {
+    D.rel_pairs.assign(nn, nullptr);
+    D.rel_map.assign(nn, nullptr);
+    D.rel_root.assign(P.roots.size(), nullptr);
+    for (size_t i = 0; i < nn; ++i) {
+      const Node &nd = P.nodes[i];
+      if (nd.size == 1) continue;
+      if (nd.n_passive_uses > 0) ST_TRY(upload(rel_map(P.k, nd.size).map, &D.rel_map[i], s));
+      const int ma = P.nodes[nd.active].size;
+      if (P.root_index[i] >= 0)
+        ST_TRY(upload(rel_root_list(P.k, nd.size, ma), &D.rel_root[P.root_index[i]], s));
+      else if (ma > 1)
+        ST_TRY(upload(rel_pairs(P.k, nd.size, ma), &D.rel_pairs[i], s));
+    }
   }
   HIP_TRY(hipStreamSynchronize(s));
   P.dev.push_back(D);
@@ -911,6 +988,29 @@ struct PassOpts {
   bool no_fuse = false;                   // materialise every non-root table
 };
 
+// greedy placement: largest first, lowest offset free over the lifetime;
+// returns the end of the placed tables
+int64_t place_tables(std::vector<Tab *> &all) {
+  std::sort(all.begin(), all.end(), [](Tab *a, Tab *c) { return a->bytes > c->bytes; });
+  std::vector<Tab *> placed;
+  int64_t top = 0;
+  for (Tab *t : all) {
+    std::vector<std::pair<int64_t, int64_t>> busy;
+    for (Tab *q : placed)
+      if (!(q->last < t->first || t->last < q->first)) busy.push_back({q->off, q->off + q->bytes});
+    std::sort(busy.begin(), busy.end());
+    int64_t off = 0;
+    for (auto &bz : busy) {
+      if (off + t->bytes <= bz.first) break;
+      off = std::max(off, bz.second);
+    }
+    t->off = off;
+    top = std::max(top, off + t->bytes);
+    placed.push_back(t);
+  }
+  return top;
+}
+
 // Build the step list and table lifetimes for a pass over b colourings.
 void build_pass(const Plan &P, int64_t n, int b, int dt, int G, int64_t n_slots, PassPlan &pp,
                 const PassOpts &opt) {
@@ -982,24 +1082,7 @@ void build_pass(const Plan &P, int64_t n, int b, int dt, int G, int64_t n_slots,
       all.push_back(&t);
     }
   }
-  // greedy placement: largest first, lowest offset free over the lifetime
-  std::sort(all.begin(), all.end(), [](Tab *a, Tab *c) { return a->bytes > c->bytes; });
-  std::vector<Tab *> placed;
-  int64_t top = 0;
-  for (Tab *t : all) {
-    std::vector<std::pair<int64_t, int64_t>> busy;
-    for (Tab *q : placed)
-      if (!(q->last < t->first || t->last < q->first)) busy.push_back({q->off, q->off + q->bytes});
-    std::sort(busy.begin(), busy.end());
-    int64_t off = 0;
-    for (auto &bz : busy) {
-      if (off + t->bytes <= bz.first) break;
-      off = std::max(off, bz.second);
-    }
-    t->off = off;
-    top = std::max(top, off + t->bytes);
-    placed.push_back(t);
-  }
+  const int64_t top = place_tables(all);
   int64_t widest = 0;
   for (size_t s = 0; s < nn; ++s)
     if (pp.B[s].last >= 0) widest = std::max(widest, pp.B[s].ld);  // the histogram too
@@ -1010,6 +1093,93 @@ void build_pass(const Plan &P, int64_t n, int b, int dt, int G, int64_t n_slots,
   int64_t small = 0;
   for (Tab *t : all) small += round_up(t->cols * b * 12 + b * 4, 256);
   pp.small_bytes = small + 256;
+}
+
+// Vertex-relative pass: one table per distinct passive child (its aggregation)
+// and one per multiply-add; a split with a one-vertex active child shares the
+// table of its passive child's aggregation.
+struct RelTab {
+  Tab t;           // cols = C(k-1, q); ld, bytes, lifetime and offset
+  int64_t plane = 0;
+  int id = -1;     // index of its exponent and largest mantissa
+};
+
+struct RelPass {
+  std::vector<Step> steps;
+  std::vector<RelTab> M, B;  // by node (M: multiply-adds only)
+  std::vector<int> m_alias;  // node whose B holds M of this node, or -1
+  int64_t arena = 0, partial_off = 0;
+  int64_t small_bytes = 0;
+  int ntab = 0;
+};
+
+// Row stride of w columns: whole 16-byte vectors; rows below 64 bytes a power
+// of two of them, longer ones whole 64-byte lines, so that no gathered row
+// touches more lines than it needs
+int64_t rel_ld(int64_t w, int es) {
+  int64_t bytes = round_up(w * es, 16);
+  if (bytes >= 64) return round_up(bytes, 64) / es;
+  int64_t p = 16;
+  while (p < bytes) p *= 2;
+  return p / es;
+}
+
+void build_rel(const Plan &P, const sg2v_graph *g, int b, int dt, RelPass &rp) {
+  const int es = esize_of(dt);
+  const size_t nn = P.nodes.size();
+  rp.steps.clear();
+  rp.M.assign(nn, RelTab());
+  rp.B.assign(nn, RelTab());
+  rp.m_alias.assign(nn, -1);
+  std::vector<char> haveB(nn, 0);
+  auto needB = [&](int p) {
+    if (haveB[p]) return;
+    haveB[p] = 1;
+    rp.steps.push_back({P.nodes[p].size == 1 ? S_HIST : S_SPMM, p});
+  };
+  for (size_t s = 0; s < nn; ++s) {
+    const Node &nd = P.nodes[s];
+    if (nd.size == 1) continue;
+    needB(nd.passive);
+    if (P.root_index[s] >= 0) rp.steps.push_back({S_ROOT, (int)s});
+    else if (P.nodes[nd.active].size == 1) rp.m_alias[s] = nd.passive;
+    else rp.steps.push_back({S_EMA_GENERAL, (int)s});
+  }
+  auto Mtab = [&](int s) -> RelTab & { return rp.m_alias[s] >= 0 ? rp.B[rp.m_alias[s]] : rp.M[s]; };
+  auto touch = [](RelTab &t, int step) {
+    t.t.first = std::min(t.t.first, step);
+    t.t.last = std::max(t.t.last, step);
+  };
+  for (int x = 0; x < (int)rp.steps.size(); ++x) {
+    const Step &st = rp.steps[x];
+    const Node &nd = P.nodes[st.node];
+    if (st.kind == S_HIST) touch(rp.B[st.node], x);
+    else if (st.kind == S_SPMM) { touch(Mtab(st.node), x); touch(rp.B[st.node], x); }
+    else {
+      if (P.nodes[nd.active].size > 1) touch(Mtab(nd.active), x);
+      touch(rp.B[nd.passive], x);
+      if (st.kind == S_EMA_GENERAL) touch(rp.M[st.node], x);
+    }
+  }
+  std::vector<Tab *> all;
+  rp.ntab = 0;
+  int64_t widest = 1;
+  for (int kind = 0; kind < 2; ++kind)  // the histogram's table is number 0 (single vertices come first)
+    for (size_t s = 0; s < nn; ++s) {
+      RelTab &r = kind == 0 ? rp.B[s] : rp.M[s];
+      if (r.t.last < 0) continue;
+      const int q = P.nodes[s].size - (kind == 0 ? 0 : 1);
+      r.t.cols = binom(P.k - 1, q);
+      r.t.ld = rel_ld(r.t.cols, es);
+      r.plane = g->n * r.t.ld;
+      r.t.bytes = round_up(r.plane * b * es, 256);
+      r.id = rp.ntab++;
+      if (kind == 0) widest = std::max(widest, r.t.ld);
+      all.push_back(&r.t);
+    }
+  rp.partial_off = place_tables(all);
+  rp.arena = rp.partial_off + round_up(std::max<int64_t>(g->n_rslots, 1) * widest * b * es, 256);
+  rp.small_bytes = (int64_t)rp.ntab * b * 8 + 256;
 }
 
 }  // namespace
@@ -1048,6 +1218,8 @@ struct Ctx {
   int nbr_j0 = -1;     // pass whose neighbour colours are in ws->nbrcol
   int nbr_b = 0;
   int64_t res_stride = 0;  // results per template (plans of several templates)
+  bool rel = false;        // vertex-relative tables (rp) instead of absolute ones (pp)
+  RelPass rp;
   // sg2v_count_noalloc: colour-skip masks copied into the scratch area
   std::map<std::tuple<int, int, int>, void *> tmp_masks;
   std::vector<std::vector<uint32_t>> tmp_host;
@@ -1055,6 +1227,16 @@ struct Ctx {
 
 sg2v_status bind_tables(Ctx &x) {
   char *base = (char *)x.ws->arena.p;
+  if (x.rel) {
+    for (size_t s = 0; s < x.rp.B.size(); ++s)
+      for (RelTab *r : {&x.rp.M[s], &x.rp.B[s]}) {
+        if (r->t.last < 0) continue;
+        r->t.p = base + r->t.off;
+        r->t.e = (int *)x.ws->small.p + (int64_t)r->id * x.b;
+        r->t.mx = (unsigned *)x.ws->small.p + (int64_t)(x.rp.ntab + r->id) * x.b;
+      }
+    return SG2V_OK;
+  }
   char *small = (char *)x.ws->small.p;
   int64_t so = 0;
   for (size_t s = 0; s < x.pp.M.size(); ++s) {
@@ -1743,7 +1925,286 @@ sg2v_status copy_capture(Ctx &x, const Capture &cap) {
   return SG2V_OK;
 }
 
+// ---------------------------------------------------------------------------
+// Steps of the vertex-relative pass (rel.hip)
+
+// blocks along the rows of a launch over `groups` wave-sized pieces and ny
+// planes: enough for several rounds of every CU, none empty
+unsigned rel_blocks(const Ctx &x, int64_t groups, int64_t ny) {
+  const int64_t most = std::max<int64_t>((int64_t)x.cu_count * 16 / std::max<int64_t>(ny, 1), x.cu_count);
+  return (unsigned)std::max<int64_t>(1, std::min<int64_t>((groups + 3) / 4, most));
+}
+
+// rows per wave: a power of two, at most `most`, about 128 entries, and no
+// fewer waves than the chip holds
+int rel_rows(const Ctx &x, int64_t most, int64_t planes) {
+  const double deg = (double)x.g->nnz / (double)x.g->n;
+  int R = 1;
+  while (2 * R <= most && 2 * R * deg <= 192.0 && x.g->n / (2 * R) * planes >= (int64_t)x.cu_count * 16) R *= 2;
+  return R;
+}
+
+void rel_combine(Ctx &x, RelTab &t, bool track) {
+  if (x.g->n_rlong == 0) return;
+  RelCombineArgs c{};
+  c.partial = (char *)x.ws->arena.p + x.rp.partial_off;
+  c.pplane = x.g->n_rslots * t.t.ld;
+  c.B = t.t.p;
+  c.ld = t.t.ld;
+  c.bplane = t.plane;
+  c.w = (int32_t)t.t.cols;
+  c.long_row = x.g->rlong_row;
+  c.long_slot0 = x.g->rlong_slot0;
+  c.long_nslot = x.g->rlong_nslot;
+  c.n_long = x.g->n_rlong;
+  c.mx = x.dt == DT_F32 && track ? t.t.mx : nullptr;
+  c.ovf = x.ovf;
+  const double el = (double)x.b * t.t.ld;
+  ProfScope ps(SG2V_K_SPMM_COMBINE, (double)(x.g->n_rslots + x.g->n_rlong) * el * x.es,
+               (double)x.g->n_rslots * el, x.s);
+  launch_rel_combine(x.dt, c, x.b, x.s);
+}
+
+sg2v_status rel_hist(Ctx &x, int node) {
+  RelTab &H = x.rp.B[node];
+  RelHistArgs a{};
+  a.row_ptr = x.g->row_ptr;
+  a.col_idx = x.g->col_idx;
+  a.w = x.g->w;
+  a.colors = x.c->d;
+  a.n = x.g->n;
+  a.k = x.P->k;
+  a.j0 = x.j0;
+  a.b = x.b;
+  a.tlong = (int32_t)kRelLong;
+  a.H = H.t.p;
+  a.ldh = H.t.ld;
+  a.hplane = H.plane;
+  a.partial = (char *)x.ws->arena.p + x.rp.partial_off;
+  a.pplane = x.g->n_rslots * H.t.ld;
+  a.seg_row = x.g->seg_row;
+  a.seg_len = x.g->seg_len;
+  a.seg_slot = x.g->seg_slot;
+  a.seg_beg = x.g->seg_beg;
+  a.n_seg = x.g->n_seg;
+  const int64_t ny = x.b == 1 ? 1 : (x.b + 3) / 4;
+  a.R = rel_rows(x, 8, ny);
+  {
+    const double nnz = (double)x.g->nnz;
+    ProfScope ps(SG2V_K_HIST,
+                 nnz * (4.0 + (x.g->w ? 4.0 : 0.0) + x.b) + (double)x.g->n * (8.0 + x.b * H.t.ld * x.es),
+                 nnz * x.b, x.s);
+    const int64_t groups = std::max<int64_t>((x.g->n + a.R - 1) / a.R, 4 * (int64_t)a.n_seg);
+    launch_rel_hist(x.dt, a, dim3(rel_blocks(x, groups, ny), (unsigned)ny), x.s);
+  }
+  rel_combine(x, H, false);
+  return SG2V_OK;
+}
+
+sg2v_status rel_spmm(Ctx &x, int node) {
+  const int k = x.P->k, m = x.P->nodes[node].size;
+  RelTab &Mt = x.rp.m_alias[node] >= 0 ? x.rp.B[x.rp.m_alias[node]] : x.rp.M[node];
+  RelTab &B = x.rp.B[node];
+  const int N = 16 / x.es;
+  RelSpmmArgs a{};
+  a.row_ptr = x.g->row_ptr;
+  a.col_idx = x.g->col_idx;
+  a.w = x.g->w;
+  a.colors = x.c->d;
+  a.n = x.g->n;
+  a.k = k;
+  a.j0 = x.j0;
+  a.M = Mt.t.p;
+  a.ldm = Mt.t.ld;
+  a.mplane = Mt.plane;
+  a.B = B.t.p;
+  a.ldb = B.t.ld;
+  a.bplane = B.plane;
+  a.partial = (char *)x.ws->arena.p + x.rp.partial_off;
+  a.pplane = x.g->n_rslots * B.t.ld;
+  a.cw = (int32_t)round_up(binom(k, m), 4);
+  a.wout = (int32_t)B.t.cols;
+  a.wout4 = (int32_t)round_up(B.t.cols, 4);
+  a.map = x.dp.rel_map[node];
+  a.olist = a.map + (size_t)k * a.cw;
+  a.smap = a.olist + (size_t)k * a.wout4;
+  a.wmap = (int32_t)round_up(Mt.t.cols, 4);
+  a.sr = (int32_t)round_up(Mt.t.cols, 4) + 4;
+  a.lp = (int32_t)((Mt.t.cols + N - 1) / N);
+  if (a.lp > 64 || a.wout < 1 || a.wout > 192) {
+    set_error("sg2v_count: aggregated rows of %d columns have no vertex-relative kernel", (int)Mt.t.cols);
+    return SG2V_EINVAL;
+  }
+  a.streams = 64 / a.lp;
+  a.gw = 1;
+  while (a.gw < 64 && a.gw < a.wout) a.gw *= 2;
+  a.tlong = (int32_t)kRelLong;
+  a.seg_row = x.g->seg_row;
+  a.seg_len = x.g->seg_len;
+  a.seg_slot = x.g->seg_slot;
+  a.seg_beg = x.g->seg_beg;
+  a.n_seg = x.g->n_seg;
+  a.e_in = Mt.t.e;
+  a.mx_in = Mt.t.mx;
+  a.e_out = B.t.e;
+  a.mx_out = B.t.mx;
+  a.ovf = x.ovf;
+  // Few absolute sets: sums in LDS, whose lane groups are never idle.  FP32
+  // elements are doubled in width by it, so the line lies lower for them
+  // (path5 on ER n=1000, FP64: 21.7 against 43.3 ms for 11,700 colourings;
+  // path8 on RMAT scale 16 with four, U64: 70 sets 1.47 against 1.58 ms; all
+  // 47 nine-vertex trees, FP32S: with 84 sets added 132.9, staged 127.7 ms).
+  a.add = binom(k, m) <= (x.es == 8 ? 100 : 64);
+  size_t lds;
+  if (a.add) {
+    // maps, then R rows of 8-byte sums per wave (8 KB)
+    a.R = rel_rows(x, std::min<int64_t>(16, std::max<int64_t>(1, 1024 / (a.cw + 4))), x.b);
+    lds = (size_t)round_up((int64_t)k * (a.wmap + a.wout4) * 2, 16) + (size_t)4 * a.R * (a.cw + 4) * 8;
+  } else {
+    // maps, then per wave 4 * streams staged rows (or the waves' sums of a segment)
+    a.R = rel_rows(x, 32, x.b);
+    lds = (size_t)round_up((int64_t)k * (a.cw + a.wout4) * 2, 16) +
+          (size_t)4 * std::max(4 * a.streams * a.sr, (int)a.wout) * x.es;
+  }
+  {
+    const double n = (double)x.g->n, nnz = (double)x.g->nnz;
+    ProfScope ps(SG2V_K_SPMM,
+                 x.b * (n * (Mt.t.cols + B.t.cols) * x.es + nnz * (5.0 + (x.g->w ? 4.0 : 0.0)) + 9.0 * n),
+                 nnz * (double)binom(k, m) * x.b, x.s);
+    const int64_t groups = std::max<int64_t>((x.g->n + a.R - 1) / a.R, 4 * (int64_t)a.n_seg);
+    if (launch_rel_spmm(x.dt, a, dim3(rel_blocks(x, groups, x.b), (unsigned)x.b), lds, x.s)) {
+      set_error("sg2v_count: no vertex-relative SpMM variant for %d columns", a.wout);
+      return SG2V_EINVAL;
+    }
+  }
+  rel_combine(x, B, true);
+  return SG2V_OK;
+}
+
+sg2v_status rel_ema(Ctx &x, int node) {
+  const Node &nd = x.P->nodes[node];
+  auto Mtab = [&](int s) -> RelTab & { return x.rp.m_alias[s] >= 0 ? x.rp.B[x.rp.m_alias[s]] : x.rp.M[s]; };
+  RelTab &X = Mtab(nd.active), &Y = x.rp.B[nd.passive], &O = x.rp.M[node];
+  RelEmaArgs a{};
+  a.X = X.t.p;
+  a.ldx = X.t.ld;
+  a.xplane = X.plane;
+  a.Y = Y.t.p;
+  a.ldy = Y.t.ld;
+  a.yplane = Y.plane;
+  a.M = O.t.p;
+  a.ldm = O.t.ld;
+  a.mplane = O.plane;
+  a.wa = (int32_t)X.t.cols;
+  a.wb = (int32_t)Y.t.cols;
+  a.ws = (int32_t)O.t.cols;
+  a.np = (int32_t)binom(nd.size - 1, x.P->nodes[nd.active].size - 1);
+  a.pairs = x.dp.rel_pairs[node];
+  a.n = x.g->n;
+  a.ex = X.t.e;
+  a.ey = Y.t.e;
+  a.mxx = X.t.mx;
+  a.mxy = Y.t.mx;
+  a.e_out = O.t.e;
+  a.mx_out = O.t.mx;
+  a.ovf = x.ovf;
+  const int Nv = 16 / x.es;
+  auto lds_for = [&](int R) { return (size_t)(a.wa + a.wb) * (R + Nv) * x.es; };
+  int R = 16;
+  while (R > 4 && lds_for(R) > kRelLds) R /= 2;
+  const size_t lds = lds_for(R);
+  // wide outputs: 512 threads share each staged tile; narrow ones 128
+  const int nt = a.ws >= 4 * 512 ? 512 : a.ws <= 256 ? 128 : 256;
+  const int64_t ntiles = (x.g->n + R - 1) / R;
+  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>((int64_t)(160 * 1024 / lds), 8 * 256 / nt));
+  const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(ntiles, (int64_t)x.cu_count * per_cu));
+  ProfScope ps(SG2V_K_EMA_GENERAL, (double)x.g->n * x.b * (double)(a.wa + a.wb + a.ws) * x.es,
+               (double)x.g->n * x.b * (double)a.ws * a.np, x.s);
+  if (launch_rel_ema(x.dt, a, R, nt, dim3((unsigned)blocks, (unsigned)x.b), lds, x.s)) {
+    set_error("sg2v_count: no vertex-relative eMA variant for R=%d", R);
+    return SG2V_EINVAL;
+  }
+  return SG2V_OK;
+}
+
+sg2v_status rel_root(Ctx &x, int node, void *result, int *Eout) {
+  const Plan &P = *x.P;
+  const Node &nd = P.nodes[node];
+  const int ri = P.root_index[node], ma = P.nodes[nd.active].size;
+  result = (char *)result + (size_t)ri * x.res_stride * 8;
+  Eout += (size_t)ri * x.res_stride;
+  RelTab &B = x.rp.B[nd.passive];
+  RelTab *X = &B, *Y = nullptr;
+  if (ma > 1) {
+    X = x.rp.m_alias[nd.active] >= 0 ? &x.rp.B[x.rp.m_alias[nd.active]] : &x.rp.M[nd.active];
+    Y = &B;
+  }
+  RelRootArgs a{};
+  a.X = X->t.p;
+  a.ldx = X->t.ld;
+  a.xplane = X->plane;
+  a.mxx = X->t.mx;
+  if (Y) {
+    a.Y = Y->t.p;
+    a.ldy = Y->t.ld;
+    a.yplane = Y->plane;
+    a.mxy = Y->t.mx;
+  }
+  a.list = x.dp.rel_root[ri];
+  a.L = binom(P.k - 1, nd.size - 1) * (Y ? binom(nd.size - 1, ma - 1) : 1);
+  a.lp = 1;
+  while (a.lp < 64 && a.lp < a.L) a.lp *= 2;
+  a.n = x.g->n;
+  a.partial = x.ws->partial.p;
+  a.ovf = x.ovf;
+  const int64_t per_wave = 4 * (64 / a.lp);  // vertices of a wave step
+  const int nblk = (int)std::max<int64_t>(1, std::min<int64_t>((x.g->n + 4 * per_wave - 1) / (4 * per_wave), kRootBlocks));
+  {
+    ProfScope ps(SG2V_K_ROOT, (double)x.g->n * x.b * (double)(X->t.cols + (Y && Y != X ? Y->t.cols : 0)) * x.es,
+                 (double)x.g->n * x.b * (double)a.L, x.s);
+    launch_rel_root(x.dt, a, dim3((unsigned)nblk, (unsigned)x.b), x.s);
+  }
+  RelFinalArgs f{};
+  f.partial = a.partial;
+  f.nblk = nblk;
+  f.out = (char *)result + (size_t)x.j0 * 8;
+  f.ovf = x.ovf;
+  if (x.dt == DT_F32) {
+    f.E = Eout + x.j0;
+    f.ex = X->t.e;
+    f.mxx = X->t.mx;
+    if (Y) {
+      f.ey = Y->t.e;
+      f.mxy = Y->t.mx;
+    }
+  }
+  launch_rel_final(x.dt, f, x.b, x.s);
+  return SG2V_OK;
+}
+
+sg2v_status run_rel(Ctx &x, void *result, int *Eout) {
+  if (x.dt == DT_F32) {
+    const float mw = (float)std::max(1.0, x.g->max_wdeg);
+    unsigned bits;
+    std::memcpy(&bits, &mw, 4);
+    launch_rel_init((int *)x.ws->small.p, (unsigned *)x.ws->small.p + (int64_t)x.rp.ntab * x.b, x.rp.ntab, x.b,
+                    bits, x.s);
+  }
+  for (const Step &st : x.rp.steps) {
+    switch (st.kind) {
+      case S_HIST: ST_TRY(rel_hist(x, st.node)); break;
+      case S_SPMM: ST_TRY(rel_spmm(x, st.node)); break;
+      case S_EMA_SINGLE: break;  // the passive child's aggregation is its table
+      case S_EMA_GENERAL: ST_TRY(rel_ema(x, st.node)); break;
+      case S_ROOT: ST_TRY(rel_root(x, st.node, result, Eout)); break;
+    }
+    HIP_TRY(hipGetLastError());
+  }
+  return SG2V_OK;
+}
+
 sg2v_status run_pass(Ctx &x, void *result, int *Eout, const Capture *cap, int stop_node = -1) {
+  if (x.rel) return run_rel(x, result, Eout);
   for (size_t q = 0; q < x.pp.steps.size(); ++q) {
     const Step &st = x.pp.steps[q];
     if (st.node == stop_node && (st.kind == S_EMA_SINGLE || st.kind == S_EMA_GENERAL ||
@@ -1814,6 +2275,12 @@ int choose_batch(const Plan &P, int ncol, int dt, int64_t n, int64_t n_slots) {
   return b;
 }
 
+// Flags that ask for kernels or layouts of the absolute tables keep them; the
+// widths, tile rows and split sizes of the tuning apply to those only.
+bool rel_wanted(const sg2v_tuning_t &t) {
+  return (t.flags & ~(SG2V_TUNE_BATCH_SERIAL | SG2V_TUNE_GRAD_RECOMPUTE)) == 0;
+}
+
 sg2v_status prepare(Ctx &x, const sg2v_plan *plan, sg2v_graph *g, const sg2v_colorings *c,
                     sg2v_mode mode, int b, hipStream_t s, const PassOpts &opt, Workspace *wsp = nullptr) {
   x.P = &plan->p;
@@ -1849,10 +2316,32 @@ sg2v_status prepare(Ctx &x, const sg2v_plan *plan, sg2v_graph *g, const sg2v_col
               (long long)x.pp.arena, (long long)tu.budget_bytes);
     return SG2V_ENOMEM;
   }
-  ST_TRY(x.ws->arena.ensure(x.pp.arena));
-  ST_TRY(x.ws->small.ensure(x.pp.small_bytes));
+  // Vertex-relative tables unless the settings ask for kernels or layouts of the
+  // absolute ones, a table is wanted as it is (kept or copied out), or a table
+  // of the plan has no relative form.  They take less memory than the pass
+  // above; where the partial rows of long rows make them larger, they are not
+  // used.
+  x.rel = false;
+  if (Carver *cv = x.ws->arena.cv) {
+    // sg2v_count_noalloc takes what the absolute tables would fit
+    const size_t need = round_up(x.pp.arena, 256) + round_up(x.pp.small_bytes, 256) + round_up((size_t)kRootBlocks * b * 8, 256) +
+                        round_up((size_t)b * (64 + g->n) * 4 + 256, 256) + round_up((size_t)b * std::max<int64_t>(g->nnz, 1) + 256, 256) + 512;
+    if (need > cv->cap) {
+      cv->exhausted = true;
+      set_error("sg2v_count_noalloc: the count needs more than the %zu-byte scratch area (%zu bytes)", cv->cap, need);
+      return SG2V_ENOMEM;
+    }
+  }
+  if (opt.keep.empty() && !opt.no_fuse && rel_wanted(tu) && rel_ok(plan->p, x.es, std::min(kRelLds, x.lds_max))) {
+    build_rel(plan->p, g, b, x.dt, x.rp);
+    x.rel = x.rp.arena <= std::max<int64_t>(x.pp.arena, (int64_t)1 << 20) && x.rp.small_bytes <= x.pp.small_bytes + 4096;
+  }
+  ST_TRY(x.ws->arena.ensure(x.rel ? x.rp.arena : x.pp.arena));
+  ST_TRY(x.ws->small.ensure(x.rel ? x.rp.small_bytes : x.pp.small_bytes));
   ST_TRY(x.ws->partial.ensure((size_t)kRootBlocks * b * 8));
   ST_TRY(x.ws->ovf.ensure(256));
+  x.ovf = (int *)x.ws->ovf.p;
+  if (x.rel) return bind_tables(x);
   ST_TRY(x.ws->bucket.ensure((size_t)b * (64 + g->n) * 4 + 256));
   if (!(tuning().flags & SG2V_TUNE_NO_COLOR_SKIP))
     ST_TRY(x.ws->nbrcol.ensure((size_t)b * std::max<int64_t>(g->nnz, 1) + 256));
@@ -1865,7 +2354,7 @@ sg2v_status prepare(Ctx &x, const sg2v_plan *plan, sg2v_graph *g, const sg2v_col
 // Upload everything a pass over b colourings needs (SpMM units, colour-skip
 // masks) so that the pass itself only enqueues kernels.
 sg2v_status prewarm(Ctx &x, int b) {
-  if (b < 1) return SG2V_OK;
+  if (b < 1 || x.rel) return SG2V_OK;
   PassPlan pp;
   build_pass(*x.P, x.g->n, b, x.dt, x.pp.G, x.g->n_slots, pp, PassOpts());
   UnitTable *U = nullptr;
@@ -1904,7 +2393,8 @@ sg2v_status enqueue_count(Ctx &x, int ncol, int b, void *res, int *Ed) {
     if (bb != x.b) {
       // last, smaller pass: tables of the full batch still fit
       x.b = bb;
-      build_pass(*x.P, x.g->n, bb, x.dt, x.pp.G, x.g->n_slots, x.pp, PassOpts());
+      if (x.rel) build_rel(*x.P, x.g, bb, x.dt, x.rp);
+      else build_pass(*x.P, x.g->n, bb, x.dt, x.pp.G, x.g->n_slots, x.pp, PassOpts());
       ST_TRY(bind_tables(x));
     }
     x.j0 = j0;
@@ -3248,6 +3738,9 @@ extern "C" void sg2v_plan_destroy(sg2v_plan *plan) {
     for (void *q : d.add) (void)hipFree(q);
     for (auto &kv : d.chunks) (void)hipFree(kv.second);
     for (void *q : d.cpr) (void)hipFree(q);
+    for (void *q : d.rel_pairs) (void)hipFree(q);
+    for (void *q : d.rel_map) (void)hipFree(q);
+    for (void *q : d.rel_root) (void)hipFree(q);
     (void)hipSetDevice(cur);
   }
   delete plan;

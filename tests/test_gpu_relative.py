@@ -1,0 +1,98 @@
+"""Counts in vertex-relative tables (the default) against the oracle and
+against the absolute tables, at the sizes where their kernels change: one to
+three output columns per lane, sums in LDS or staged rows, colour sets of one
+to nearly all colours, rows of no entries, of several segments and in between,
+vertex numbers around the rows of a wave, one and several colourings."""
+import sys
+
+import numpy as np
+import pytest
+
+import graphgen as gg
+import oracle as O
+import paper_2009_11665_amd as sg
+
+pytestmark = pytest.mark.gpu
+
+# bounds of the library's modes: FP64 rounding over the sums of a count, FP32
+# with power-of-two frames
+TOL = {"fp64": 1e-12, "fp32s": 1e-5}
+
+TEMPLATES = [
+    ([-1, 0], 2), ([-1, 0], 20),                       # histogram and root only
+    ([-1, 0, 1], 3), ([-1, 0, 1], 20),                 # one aggregation; 190 sets
+    ([-1, 0, 1, 2], 4), ([-1, 0, 1, 2], 12),           # widths 1..3; 220 sets
+    ([-1, 0, 0, 0, 0], 6), (gg.PATH5, 9), (gg.BINTREE7, 7), (gg.BINTREE7, 9),
+    (gg.PATH8, 8), (gg.CATERPILLAR10, 10),
+    ([-1, 0, 1, 2, 3, 4], 12),                         # 495 sets: absolute tables
+]
+
+
+def hubs(n, seed, weighted):
+    """Hubs of n - 1, 300 and 255 neighbours, a ring, and isolated vertices at
+    the end when there is room."""
+    edges = set()
+    last = n - max(0, min(7, n - 8))
+    for v in range(1, last):
+        edges.add((0, v))
+        edges.add((min(v, (v % (last - 1)) + 1), max(v, (v % (last - 1)) + 1)))
+    for hub, d in ((1, 300), (2, 255)):
+        for v in range(last):
+            if v > hub and v < hub + d:
+                edges.add((hub, v))
+    e = np.array([x for x in sorted(edges) if x[0] != x[1]])
+    rng = np.random.default_rng(seed)
+    perm = rng.permutation(n)
+    w = rng.uniform(0.5, 1.5, len(e)) if weighted else None
+    return gg.from_edge_list(n, [(int(perm[a]), int(perm[b])) for a, b in e], w)
+
+
+@pytest.mark.parametrize("n", [5, 33, 1500])
+@pytest.mark.parametrize("par,k", TEMPLATES)
+def test_relative_tables_against_oracle_and_absolute(par, k, n):
+    for weighted in (False, True):
+        G = hubs(n, 11 * n + k, weighted)
+        g = sg.Graph.from_csr(G)
+        plan = sg.Plan(par, k)
+        for ncol in (1, 6):
+            c = sg.Colorings(g, k, 5, ncol, first=3)
+            for mode in ("fp64", "fp32s") + (() if weighted else ("u64",)):
+                print("relative", n, par, k, weighted, ncol, mode, flush=True)
+                sys.stdout.flush()
+                r = sg.count(plan, g, c, mode)
+                with sg.tuned(flags=sg.TUNE_NO_COLOR_SKIP):
+                    full = sg.count(plan, g, c, mode)
+                for j in range(ncol):
+                    col = O.colors(n, k, 5, 3 + j)
+                    f, u, _ = O.count(G, par, k, col, mode=O.U64 if mode == "u64" else O.FP64)
+                    if mode == "u64":
+                        assert int(r["colorful_u64"][j]) == u == int(full["colorful_u64"][j])
+                    else:
+                        assert r["colorful"][j] == pytest.approx(f, rel=TOL[mode])
+                        assert r["colorful"][j] == pytest.approx(full["colorful"][j], rel=2 * TOL[mode])
+
+
+def test_relative_tables_partial_pass_and_several_templates():
+    """A last pass of fewer colourings, and templates that share tables."""
+    G = hubs(700, 3, False)
+    g = sg.Graph.from_csr(G, relabel=True)
+    ts = sg.trees(6)
+    plan = sg.Plan.multi(ts, 7)
+    c = sg.Colorings(g, 7, 9, 5)
+    with sg.tuned(batch=2):
+        r = sg.count_multi(plan, g, c, "u64")
+    for t, par in enumerate(ts):
+        for j in range(5):
+            assert int(r["colorful_u64"][t][j]) == O.count(G, par, 7, O.colors(700, 7, 9, j), mode=O.U64)[1]
+
+
+def test_relative_overflow_flag():
+    """Sums past 2^64 are flagged, and only those."""
+    n = 1400
+    G = hubs(n, 4, False)
+    g = sg.Graph.from_csr(G)
+    for par, k in (([-1, 0, 0, 0, 0, 0, 0], 7), (gg.PATH5, 5)):
+        r = sg.count(sg.Plan(par, k), g, sg.Colorings(g, k, 1, 2), "u64")
+        ref = [O.count(G, par, k, O.colors(n, k, 1, j), mode=O.U64) for j in range(2)]
+        assert [int(x) for x in r["colorful_u64"]] == [x[1] for x in ref]
+        assert r["overflow"] == any(x[2] for x in ref)
