@@ -115,6 +115,9 @@ struct Plan {
     // vertex-relative tables: per node the split's pair list, the aggregation's
     // maps (colour maps followed by the output lists); per template the root list
     std::vector<void *> rel_pairs, rel_map, rel_root;
+    // output columns where they are not the ranks (per node: multiply-adds,
+    // aggregations); chunk tables of wide aggregations
+    std::vector<void *> rel_mpos, rel_bpos, rel_hdr, rel_info, rel_tab;
     // SpMM colour-skip masks per (node, colourings per pass, chunk width)
     std::map<std::tuple<int, int, int>, void *> chunks;
   };
@@ -133,15 +136,47 @@ struct RelMap {
   // then [k][zero]: absolute set of each column plus c (cw: padding)
   std::vector<uint16_t> map;
 };
+// Aggregations too wide for one row per wave go in chunks.  The k colours are
+// cut into the l = rel_low(k) lowest and the others; a chunk holds the sets P with
+// one choice of high colours PH, its columns the choices of s = m - |PH| low
+// ones.  In a gathered row of a vertex of colour c these are one run: the sets
+// without c, of PH if c is low and of PH - {c} if it is high.
+bool rel_wide(int k, int m);
+int rel_low(int k);
+// Columns of the q-sets: their ranks, or (tables gathered in chunks) each choice
+// of high relative colours at a multiple of 32 columns.
+struct RelLayout {
+  int64_t width = 0;
+  std::vector<int32_t> pos;  // by rank
+};
+RelLayout rel_layout(int k, int q, bool wide);
+struct RelWide {
+  int l = 0, nchunk = 0;
+  // [nchunk][1 + 2k]: s, then per colour the first column of its run in a gathered
+  // row (-1: none), then per colour the first output column (-1: none)
+  std::vector<int32_t> hdr;
+  // [l + 1][9], by s: columns padded to 4, offsets of inv and out in `tab`, run
+  // lengths of low and high colours (with the gap inside), output columns of low
+  // and high colours, and where and by how much the latter's have a gap
+  std::vector<int32_t> info;
+  // inv [l + 1][cw]: column within the run of each choice of low colours (row c: low
+  // colour c, 0xFFFF if it lacks c; row l: any high colour); out [l + 1][cw]: choice
+  // of each output column
+  std::vector<uint16_t> tab;
+};
+// (also, with out_wide false, of an aggregation that is not wide: all colours low)
+RelWide rel_wide_tables(int k, int m, bool out_wide);
+// tables gathered in chunks, by node: its multiply-add's, its aggregation's
+void rel_wide_nodes(const Plan &P, std::vector<char> &wide_m, std::vector<char> &wide_b);
 // whether every table of the plan has a vertex-relative form, with elements of
 // es bytes and multiply-add tiles of at most `lds` bytes
 bool rel_ok(const Plan &P, int es, size_t lds);
-// maps of the aggregation of an m-vertex passive child, m >= 2
+// maps of the aggregation of an m-vertex passive child, m >= 2, not wide
 RelMap rel_map(int k, int m);
 // pairs [np][ws] (x | y << 16) of a split (m vertices, ma of them active, 1 < ma < m)
-std::vector<uint32_t> rel_pairs(int k, int m, int ma);
+std::vector<uint32_t> rel_pairs(int k, int m, int ma, const RelLayout &X, const RelLayout &Y);
 // root list (x | y << 16) of a template of t vertices, ma in the active child
-std::vector<uint32_t> rel_root_list(int k, int t, int ma);
+std::vector<uint32_t> rel_root_list(int k, int t, int ma, const RelLayout &X, const RelLayout &Y);
 
 sg2v_status plan_build(const int32_t *parent, int t, int k, Plan &out);
 // Several templates over the same k, sharing isomorphic rooted sub-templates.

@@ -322,6 +322,7 @@ struct RelSpmmArgs {
   int64_t pplane;
   const uint16_t *map;     // [k][cw]: column of (absolute set - colour) in a row of that colour, or sr - 4
   const uint16_t *olist;   // [k][wout4]: absolute set of each output position
+  const uint16_t *opos;    // column of each output position (null: the position)
   const uint16_t *smap;    // [k][wmap]: absolute set of (column + colour) in a row of that colour, or cw
   int32_t wmap;
   int32_t add;             // 1: sums of absolute sets in LDS (k_rel_spmm_add)
@@ -338,6 +339,68 @@ struct RelSpmmArgs {
   const unsigned *mx_in;
   int *e_out;
   unsigned *mx_out;
+  int *ovf;
+};
+
+struct RelSortArgs {
+  const int32_t *col_idx;
+  const float *w;          // nullable
+  const uint8_t *colors;
+  int64_t n, nnz;
+  int32_t k, j0;
+  const int64_t *task_beg;
+  const int32_t *task_len;
+  const uint16_t *tsplit;  // [tasks][xsplit + 1]
+  int64_t x_tasks;         // tasks taken per neighbour range
+  int32_t xsplit;
+  int64_t n_items;         // x_tasks * xsplit + the other tasks
+  int32_t *out;            // [b][nnz]
+  float *wout;             // [b][nnz], with weights
+  uint16_t *off;           // [b][n_items][32]
+};
+
+struct RelWideArgs {
+  const int32_t *scol;     // [b][nnz] entries by colour within each task
+  const float *sw;         // their weights, or null
+  const uint16_t *off;     // [b][n_items][32]
+  int64_t n_items, nnz;
+  const uint8_t *colors;
+  int64_t n;
+  int32_t k, j0, l;
+  int32_t nchunk;
+  const int32_t *hdr, *info;
+  const uint16_t *tab;
+  const int32_t *task_row, *task_slot;
+  const int64_t *task_beg;
+  const uint16_t *tsplit;
+  int64_t x_tasks, n_tasks;
+  int32_t xsplit;
+  int32_t stage;           // LDS elements of a wave's stage
+  int32_t nout_max;
+  const void *M;
+  int64_t ldm, mplane;
+  void *B;
+  int64_t ldb, bplane;
+  void *partial;           // [b][slots][ldb]
+  int64_t pplane;
+  void *partial8;          // [b][xsplit][x_tasks][ldb]
+  int64_t p8plane;
+  const int *e_in;
+  const unsigned *mx_in;
+  int *e_out;
+  unsigned *mx_out;
+  int *ovf;
+};
+
+struct RelXsumArgs {
+  const void *partial8;
+  int64_t p8plane;
+  const int32_t *task_row, *task_slot;
+  int64_t n_tasks;
+  void *B, *partial;
+  int64_t ld, bplane, pplane;
+  int32_t w;
+  unsigned *mx;
   int *ovf;
 };
 
@@ -360,6 +423,7 @@ struct RelEmaArgs {
   int64_t ldm, mplane;
   int32_t wa, wb, ws, np;
   const uint32_t *pairs;   // [np][ws]: x | y << 16
+  const uint16_t *opos;    // column of each output (null: its rank)
   int64_t n;
   const int *ex, *ey;
   const unsigned *mxx, *mxy;
@@ -393,6 +457,9 @@ struct RelFinalArgs {
 void launch_rel_init(int *e, unsigned *mx, int ntab, int b, unsigned hist_bits, hipStream_t s);
 void launch_rel_hist(int dtype, const RelHistArgs &a, dim3 grid, hipStream_t s);
 int launch_rel_spmm(int dtype, const RelSpmmArgs &a, dim3 grid, size_t lds, hipStream_t s);
+void launch_rel_sort(const RelSortArgs &a, int b, hipStream_t s);
+int launch_rel_wide(int dtype, const RelWideArgs &a, dim3 grid, size_t lds, hipStream_t s);
+void launch_rel_xsum(int dtype, const RelXsumArgs &a, int b, hipStream_t s);
 void launch_rel_combine(int dtype, const RelCombineArgs &a, int b, hipStream_t s);
 int launch_rel_ema(int dtype, const RelEmaArgs &a, int R, int nt, dim3 grid, size_t lds, hipStream_t s);
 void launch_rel_root(int dtype, const RelRootArgs &a, dim3 grid, hipStream_t s);

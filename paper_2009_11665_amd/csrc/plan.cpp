@@ -10,6 +10,7 @@
 #include <functional>
 #include <map>
 #include <new>
+#include <numeric>
 
 #include "internal.h"
 
@@ -505,20 +506,154 @@ namespace {
 uint32_t abs_of(uint32_t rel, int c) { return (rel & ((1u << c) - 1)) | (rel >> c << (c + 1)); }
 }  // namespace
 
+bool rel_wide(int k, int m) {
+  // one row per wave: six output columns per lane, maps of 512 sets, 128 gathered
+  return m >= 2 && (binom(k, m) > 512 || binom(k - 1, m) > 384 || binom(k - 1, m - 1) > 128);
+}
+
+// Ten low colours: a run is up to 126 columns of a low colour's row, 252 of a
+// high one's (15-vertex tree, RMAT scale 20, FP32: the aggregation of 6435 sets
+// takes 178 ms; nine: 228, shorter runs leave more of a line and of a wave unused;
+// eight: 265).
+int rel_low(int k) { return std::min(10, k - 1); }
+
+namespace {
+constexpr int kRelAlign = 32;
+int64_t pad_to(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
+
+// first column of every choice of high relative colours (-1: none), and the width
+std::vector<int32_t> rel_blocks(int k, int q, int64_t *width) {
+  const int l = rel_low(k), h = k - l;  // l - 1 low and h high relative colours
+  std::vector<int32_t> base((size_t)1 << h, -1);
+  int64_t top = 0;
+  for (uint32_t H = 0; H < (1u << h); ++H) {
+    const int64_t c = binom(l - 1, q - __builtin_popcount(H));
+    if (c == 0) continue;
+    base[H] = (int32_t)top;
+    top += pad_to(c, kRelAlign);
+  }
+  *width = top;
+  return base;
+}
+}  // namespace
+
+RelLayout rel_layout(int k, int q, bool wide) {
+  RelLayout L;
+  L.width = binom(k - 1, q);
+  L.pos.resize((size_t)L.width);
+  std::iota(L.pos.begin(), L.pos.end(), 0);
+  if (!wide) return L;
+  const int lo = rel_low(k) - 1;
+  const std::vector<int32_t> base = rel_blocks(k, q, &L.width);
+  for (size_t r = 0; r < L.pos.size(); ++r) {
+    const uint32_t Q = colex_unrank((int64_t)r, q, k - 1);
+    L.pos[r] = base[Q >> lo] + (int32_t)colex_rank(Q & ((1u << lo) - 1));
+  }
+  return L;
+}
+
+void rel_wide_nodes(const Plan &P, std::vector<char> &wide_m, std::vector<char> &wide_b) {
+  wide_m.assign(P.nodes.size(), 0);
+  wide_b.assign(P.nodes.size(), 0);
+  for (size_t q = 0; q < P.nodes.size(); ++q) {
+    const Node &nd = P.nodes[q];
+    if (nd.size == 1 || nd.n_passive_uses == 0 || !rel_wide(P.k, nd.size)) continue;
+    if (P.nodes[nd.active].size == 1) wide_b[nd.passive] = 1;
+    else wide_m[q] = 1;
+  }
+}
+
+RelWide rel_wide_tables(int k, int m, bool out_wide) {
+  RelWide w;
+  // all colours low: one chunk
+  const int l = rel_wide(k, m) ? rel_low(k) : k, h = k - l;
+  w.l = l;
+  const uint16_t none = 0xFFFF;
+  int64_t width;
+  const std::vector<int32_t> bin = h ? rel_blocks(k, m - 1, &width) : std::vector<int32_t>(1, 0);
+  const std::vector<int32_t> bout = h ? rel_blocks(k, m, &width) : std::vector<int32_t>(1, 0);
+  // output column of relative set (H, low), H over the high relative colours
+  auto out_pos = [&](uint32_t H, uint32_t low) -> int32_t {
+    if (out_wide) return bout[H] + (int32_t)colex_rank(low);
+    return (int32_t)colex_rank((H << (l - 1)) | low);
+  };
+  w.info.assign((size_t)(l + 1) * 9, 0);
+  for (int s = std::max(0, m - h); s <= std::min(l, m); ++s) {
+    int32_t *I = &w.info[(size_t)s * 9];
+    const int64_t C = binom(l, s), first = binom(l - 1, s), second = s > 0 ? binom(l - 1, s - 1) : 0;
+    const int cw = (int)pad_to(C, 4);
+    // a high colour's run: the choices without low colour l - 1, then those with it
+    const int64_t igap = first && second ? pad_to(first, kRelAlign) - first : 0;
+    I[0] = cw;
+    I[1] = (int32_t)w.tab.size();
+    I[2] = I[1] + (l + 1) * cw;
+    I[3] = (int32_t)second;
+    I[4] = (int32_t)(C + igap);
+    I[5] = (int32_t)first;
+    I[6] = (int32_t)C;
+    I[7] = (int32_t)first;
+    I[8] = out_wide ? (int32_t)igap : 0;
+    w.tab.resize(w.tab.size() + (size_t)2 * (l + 1) * cw, none);
+    uint16_t *inv = &w.tab[I[1]], *out = &w.tab[I[2]];
+    for (int64_t x = 0; x < C; ++x) {
+      const uint32_t L = colex_unrank(x, s, l);
+      for (int c = 0; c < l; ++c) {
+        const uint32_t rest = (L & ((1u << c) - 1)) | (L >> (c + 1) << c);
+        if (L >> c & 1u) inv[(size_t)c * cw + x] = (uint16_t)colex_rank(rest);
+        else out[(size_t)c * cw + colex_rank(rest)] = (uint16_t)x;
+      }
+      inv[(size_t)l * cw + x] = (uint16_t)(x < first ? x : x + igap);
+      out[(size_t)l * cw + x] = (uint16_t)x;
+    }
+  }
+  for (uint32_t PH = 0; PH < (1u << h); ++PH) {
+    const int s = m - __builtin_popcount(PH);
+    if (s < 0 || s > l) continue;
+    ++w.nchunk;
+    const size_t o = w.hdr.size();
+    w.hdr.resize(o + 1 + 2 * k, -1);
+    w.hdr[o] = s;
+    int32_t *in = &w.hdr[o + 1], *out = in + k;
+    for (int c = 0; c < k; ++c) {
+      if (c < l) {
+        if (s > 0) in[c] = bin[PH];
+        if (s < l) out[c] = out_pos(PH, s ? (1u << s) - 1 : 0);
+        continue;
+      }
+      const int b = c - l;
+      const uint32_t rest = (PH & ((1u << b) - 1)) | (PH >> (b + 1) << b);
+      // low colour l - 1 is the lowest high relative colour; sets without it first
+      const uint32_t H = s < l ? rest << 1 : rest << 1 | 1;
+      if (PH >> b & 1u) in[c] = bin[H];
+      else out[c] = out_pos(H, (1u << (s < l ? s : s - 1)) - 1);
+    }
+  }
+  return w;
+}
+
 bool rel_ok(const Plan &P, int es, size_t lds) {
   const int pad = 16 / es;
+  std::vector<char> wm, wb;
+  rel_wide_nodes(P, wm, wb);
   for (size_t q = 0; q < P.nodes.size(); ++q) {
     const Node &nd = P.nodes[q];
     if (nd.size == 1) continue;
-    // an aggregation: three output columns per lane, maps of 256 absolute sets,
-    // and a gathered row that one wave reads
-    if (nd.n_passive_uses > 0 && (nd.cols > 256 || binom(P.k - 1, nd.size) > 192 ||
-                                  binom(P.k - 1, nd.size - 1) * es > 64 * 16)) return false;
-    const int ma = P.nodes[nd.active].size, mp = P.nodes[nd.passive].size;
-    const int64_t wa = binom(P.k - 1, ma - 1), wb = binom(P.k - 1, mp), ws = binom(P.k - 1, nd.size - 1);
-    if (wa >= 0xFFFF || wb >= 0xFFFF || (double)ws * binom(nd.size - 1, ma - 1) > (double)(1 << 26)) return false;
+    const Node &A = P.nodes[nd.active];
+    const int ma = A.size, mp = P.nodes[nd.passive].size;
+    // columns fit 16 bits; the pair lists stay below 2^26 entries
+    const int64_t ws = binom(P.k - 1, nd.size - 1), wp = binom(P.k - 1, mp), wx = binom(P.k - 1, ma - 1);
+    // a table gathered in chunks pads each choice of high colours to whole lines:
+    // with many small ones the absolute table's chunks move less
+    if (wb[q] && rel_layout(P.k, nd.size, true).width * 5 > binom(P.k - 1, nd.size) * 8) return false;
+    if (wm[q] && rel_layout(P.k, nd.size - 1, true).width * 5 > binom(P.k - 1, nd.size - 1) * 8) return false;
+    if (ws > 40000 || wp > 40000 || wx > 40000 || (double)ws * binom(nd.size - 1, ma - 1) > (double)(1 << 26))
+      return false;
+    if (ma == 1) continue;
+    const bool xw = P.nodes[A.active >= 0 ? A.active : 0].size == 1 ? wb[A.passive] : wm[nd.active];
+    const int64_t wa = rel_layout(P.k, ma - 1, xw).width, wy = rel_layout(P.k, mp, wb[nd.passive]).width;
+    if (wa >= 0xFFFF || wy >= 0xFFFF || rel_layout(P.k, nd.size - 1, wm[q]).width >= 0xFFFF) return false;
     // rows of the multiply-add staged in LDS, four at least
-    if (ma > 1 && P.root_index[q] < 0 && (size_t)((wa + wb) * (4 + pad) * es) > lds) return false;
+    if (P.root_index[q] < 0 && (size_t)((wa + wy) * (4 + pad) * es) > lds) return false;
   }
   return true;
 }
@@ -560,28 +695,34 @@ void rel_splits(uint32_t Q, int qa, F f) {
 }
 }  // namespace
 
-std::vector<uint32_t> rel_pairs(int k, int m, int ma) {
+std::vector<uint32_t> rel_pairs(int k, int m, int ma, const RelLayout &X, const RelLayout &Y) {
   const int64_t ws = binom(k - 1, m - 1);
   const int np = (int)binom(m - 1, ma - 1);
   std::vector<uint32_t> out((size_t)ws * np);
   for (int64_t C = 0; C < ws; ++C) {
     int q = 0;
     rel_splits(colex_unrank(C, m - 1, k - 1), ma - 1, [&](int64_t x, int64_t y) {
-      out[(size_t)q++ * ws + C] = (uint32_t)x | ((uint32_t)y << 16);
+      out[(size_t)q++ * ws + C] = (uint32_t)X.pos[x] | ((uint32_t)Y.pos[y] << 16);
     });
   }
   return out;
 }
 
-std::vector<uint32_t> rel_root_list(int k, int t, int ma) {
+std::vector<uint32_t> rel_root_list(int k, int t, int ma, const RelLayout &X, const RelLayout &Y) {
   std::vector<uint32_t> out;
   const int64_t ws = binom(k - 1, t - 1);
   for (int64_t C = 0; C < ws; ++C) {
     const uint32_t Q = colex_unrank(C, t - 1, k - 1);
-    if (ma == 1) out.push_back((uint32_t)colex_rank(Q));
-    else rel_splits(Q, ma - 1, [&](int64_t x, int64_t y) { out.push_back((uint32_t)x | ((uint32_t)y << 16)); });
+    if (ma == 1) out.push_back((uint32_t)Y.pos[colex_rank(Q)]);
+    else
+      rel_splits(Q, ma - 1, [&](int64_t x, int64_t y) {
+        out.push_back((uint32_t)X.pos[x] | ((uint32_t)Y.pos[y] << 16));
+      });
   }
-  if (ma > 1) std::sort(out.begin(), out.end(), [](uint32_t a, uint32_t b) { return (a & 0xFFFF) != (b & 0xFFFF) ? (a & 0xFFFF) < (b & 0xFFFF) : a < b; });
+  // in the order of X, so that consecutive lanes read consecutive columns
+  std::sort(out.begin(), out.end(), [](uint32_t a, uint32_t b) {
+    return (a & 0xFFFFu) != (b & 0xFFFFu) ? (a & 0xFFFFu) < (b & 0xFFFFu) : a < b;
+  });
   return out;
 }
 

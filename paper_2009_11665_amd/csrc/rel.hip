@@ -236,8 +236,13 @@ __global__ void __launch_bounds__(BLOCK) k_rel_spmm(RelSpmmArgs a) {
   T acc[NP];
   int pabs[NP];  // absolute sets of the current row's positions (0: past the end)
   bool pok[NP];
+  int opos[NP];  // columns of those positions
 #pragma unroll
-  for (int u = 0; u < NP; ++u) pok[u] = p0 + u * WAVE < a.wout;
+  for (int u = 0; u < NP; ++u) {
+    const int p = p0 + u * WAVE;
+    pok[u] = p < a.wout;
+    opos[u] = pok[u] && a.opos ? a.opos[p] : p;
+  }
 
   auto open_row = [&](int r) {
 #pragma unroll
@@ -317,7 +322,7 @@ __global__ void __launch_bounds__(BLOCK) k_rel_spmm(RelSpmmArgs a) {
               x *= f;
               cmax = fmaxf(cmax, x);
             }
-            dst[p0 + v * WAVE] = x;
+            dst[opos[v]] = x;
           }
       }
     };
@@ -398,7 +403,7 @@ __global__ void __launch_bounds__(BLOCK) k_rel_spmm(RelSpmmArgs a) {
         x *= f;
         if (slot < 0) cmax = fmaxf(cmax, x);
       }
-      dst[p] = x;
+      dst[a.opos ? a.opos[p] : p] = x;
     }
     __syncthreads();
     for (int q = lane; q < E; q += WAVE) stg[q * SR + SR - 4] = T(0);
@@ -544,7 +549,7 @@ __global__ void __launch_bounds__(BLOCK) k_rel_spmm_add(RelSpmmArgs a) {
         y *= f;
         if (slot < 0) cmax = fmaxf(cmax, y);
       }
-      dst[p] = y;
+      dst[a.opos ? a.opos[p] : p] = y;
     }
     __syncthreads();
     for (int q = lane; q < S; q += WAVE) acc[q] = C(0);
@@ -583,7 +588,7 @@ __global__ void __launch_bounds__(BLOCK) k_rel_spmm_add(RelSpmmArgs a) {
           y *= f;
           cmax = fmaxf(cmax, y);
         }
-        B[(row0 + loc) * a.ldb + p] = y;
+        B[(row0 + loc) * a.ldb + (a.opos ? a.opos[p] : p)] = y;
       }
       p += dp;
       loc += dl;
@@ -602,6 +607,316 @@ __global__ void __launch_bounds__(BLOCK) k_rel_spmm_add(RelSpmmArgs a) {
   if constexpr (sizeof(T) == 4) {
     cmax = wave_max(cmax);
     if (lane == 0 && cmax > 0.f) atomicMax(a.mx_out + jj, __float_as_uint(cmax));
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Wide aggregations, in chunks of the colour sets with one choice of high
+// colours (blockIdx.y; the planner's rel_wide_tables).  The entries of every
+// task are sorted by neighbour colour once per colouring, so that a wave adds a
+// colour's runs in registers, lane by lane as they are read, and permutes the
+// sum once per colour (through its LDS stage) instead of each run.  Tasks of the
+// neighbour-range split are taken once per range by the blocks of one XCD.
+
+// Entries of each task (of each range of the first x_tasks ones) by colour, in
+// their order within a colour; off: where each colour starts.
+template <bool WEIGHTED>
+__global__ void __launch_bounds__(BLOCK) k_rel_sort(RelSortArgs a) {
+  const int lane = threadIdx.x & (WAVE - 1);
+  const int64_t wave = ((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE;
+  const int64_t nwaves = (int64_t)gridDim.x * WAVES_PER_BLOCK;
+  const int jj = blockIdx.y, k = a.k;
+  const uint8_t *col = a.colors + (int64_t)(a.j0 + jj) * a.n;
+  int32_t *out = a.out + jj * a.nnz;
+  float *wout = WEIGHTED ? a.wout + jj * a.nnz : nullptr;
+  uint16_t *off = a.off + jj * a.n_items * 32;
+  for (int64_t it = wave; it < a.n_items; it += nwaves) {
+    const int64_t xs = a.x_tasks * a.xsplit;
+    const int64_t t = it < xs ? it / a.xsplit : it - xs + a.x_tasks;
+    int64_t beg = a.task_beg[t];
+    int len = a.task_len[t];
+    if (it < xs) {
+      const int xr = (int)(it - t * a.xsplit);
+      const uint16_t *sp = a.tsplit + t * (a.xsplit + 1);
+      beg += sp[xr];
+      len = sp[xr + 1] - sp[xr];
+    }
+    len = __builtin_amdgcn_readfirstlane(len);
+    int cnt = 0;  // of colour `lane`
+    for (int base = 0; base < len; base += WAVE) {
+      const int c = base + lane < len ? (int)col[a.col_idx[beg + base + lane]] : 255;
+      for (int cc = 0; cc < k; ++cc) {
+        const int m = __popcll(__ballot(c == cc));
+        if (lane == cc) cnt += m;
+      }
+    }
+    int at = 0;  // exclusive prefix over the colours
+    for (int cc = 0; cc < k; ++cc) {
+      const int m = __builtin_amdgcn_readlane(cnt, cc);
+      if (lane > cc) at += m;
+    }
+    if (lane <= k) off[it * 32 + lane] = (uint16_t)at;
+    const uint64_t lt = (1ull << lane) - 1ull;
+    for (int base = 0; base < len; base += WAVE) {
+      const bool in = base + lane < len;
+      const int j = in ? a.col_idx[beg + base + lane] : 0;
+      const int c = in ? (int)col[j] : 255;
+      int pos = 0;
+      for (int cc = 0; cc < k; ++cc) {
+        const uint64_t m = __ballot(c == cc);
+        if (c == cc) pos = __builtin_amdgcn_readlane(at, cc) + __popcll(m & lt);
+        if (lane == cc) at += __popcll(m);
+      }
+      if (in) {
+        out[beg + pos] = j;
+        if constexpr (WEIGHTED) wout[beg + pos] = a.w[beg + base + lane];
+      }
+    }
+  }
+}
+
+// Bound by the lines in flight per CU: 82 lines per entry and table of 3003
+// columns, half of them from beyond the L2 (6.3 TB/s), about 71 in flight per CU
+// at 452 cycles.  Six waves per SIMD (five without the launch bound): 214 -> 199
+// ms for the whole count of the 15-vertex tree on RMAT scale 20 in FP32, seven
+// (spills in FP64): 205.  The absolute tables' k_spmm took 252 of 298 ms.
+template <typename T, bool WEIGHTED, int NP>
+__global__ void __launch_bounds__(BLOCK, 6) k_rel_wide(RelWideArgs a) {
+  constexpr int N = V16<T>::N;
+  constexpr int UNR = 4;
+  using A = Arith<T>;
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
+  const int k = a.k, l = a.l;
+  const int jj = blockIdx.y / a.nchunk, chunk = blockIdx.y - jj * a.nchunk;
+  const int32_t *hdr = a.hdr + (int64_t)chunk * (1 + 2 * k);
+  const int32_t *I = a.info + hdr[0] * 9;
+  const int cw = I[0], lin_low = I[3], lin_high = I[4], lout_low = I[5], lout_high = I[6];
+  const int osplit = I[7], ogap = I[8];
+  uint16_t *linv = (uint16_t *)smem;
+  uint16_t *lout = linv + (l + 1) * cw;
+  T *stg = (T *)(smem + ((2 * (l + 1) * cw * 2 + 15) & ~15)) + (size_t)wv * a.stage;
+  for (int q = threadIdx.x; q < (l + 1) * cw / 2; q += BLOCK) {
+    ((unsigned *)linv)[q] = ((const unsigned *)(a.tab + I[1]))[q];
+    ((unsigned *)lout)[q] = ((const unsigned *)(a.tab + I[2]))[q];
+  }
+  // lane c: first columns of colour c's run and of a row of colour c (-1: none)
+  const int in0 = lane < k ? hdr[1 + lane] : -1, out0 = lane < k ? hdr[1 + k + lane] : -1;
+  const uint32_t usable = (uint32_t)__ballot(in0 >= 0);
+  __syncthreads();
+  const uint8_t *col = a.colors + (int64_t)(a.j0 + jj) * a.n;
+  const int32_t *scol = a.scol + jj * a.nnz;
+  const float *sw = WEIGHTED ? a.sw + jj * a.nnz : nullptr;
+  const uint16_t *off = a.off + jj * a.n_items * 32;
+  const T *__restrict__ M = (const T *)a.M + jj * a.mplane;
+  T *__restrict__ B = (T *)a.B + jj * a.bplane;
+  T *__restrict__ Pt = (T *)a.partial + jj * a.pplane;
+  T *__restrict__ P8 = (T *)a.partial8 + jj * a.p8plane;
+  T f = T(1);
+  if constexpr (sizeof(T) == 4) {
+    f = rel_factor(a.mx_in[jj]);
+    if (blockIdx.x == 0 && chunk == 0 && threadIdx.x == 0) a.e_out[jj] = rel_frame(a.e_in[jj], a.mx_in[jj]);
+  }
+  // lanes of a run by class (low, high): vectors, lanes per run, streams
+  const int nv_l = (lin_low + N - 1) / N, nv_h = (lin_high + N - 1) / N;
+  const int lp_l = max(1, min(nv_l, WAVE)), lp_h = max(1, min(nv_h, WAVE));
+  const int st_l = WAVE / lp_l, st_h = WAVE / lp_h;
+  const int stream_l = lane / lp_l, vec_l = lane - stream_l * lp_l;
+  const int stream_h = lane / lp_h, vec_h = lane - stream_h * lp_h;
+  float cmax = 0.f;
+  bool ovf = false;
+
+  // one task (or one range of it): out[p] = sum over its entries
+  T out[NP];
+  int pabs[NP];
+  auto task = [&](int64_t beg, int r, int64_t item, int nout) {
+    const int rrow = r < l ? r : l;
+#pragma unroll
+    for (int v = 0; v < NP; ++v) {
+      out[v] = T(0);
+      pabs[v] = lane + v * WAVE < nout ? lout[rrow * cw + lane + v * WAVE] : 0;
+    }
+    const int o_c = lane <= k ? (int)off[item * 32 + lane] : 0;
+    uint32_t todo = usable & ~(1u << r);
+    const int o_n = shfl_i32(o_c, min(lane + 1, WAVE - 1));
+    todo &= (uint32_t)__ballot(lane < k && o_c != o_n);
+    if (todo == 0) return;
+    // pieces of up to 64 entries of one colour; the next piece's indices are
+    // loaded while this one's rows are gathered
+    int c = __builtin_ctz(todo), e = __builtin_amdgcn_readlane(o_c, c), end = __builtin_amdgcn_readlane(o_c, c + 1);
+    int nx_j = scol[beg + min(e + lane, end - 1)];
+    float nx_w = 1.f;
+    if constexpr (WEIGHTED) nx_w = sw[beg + min(e + lane, end - 1)];
+    V16<T> acc;
+#pragma unroll
+    for (int u = 0; u < N; ++u) acc.x[u] = T(0);
+    while (todo) {
+      const int cc = c, nb = min(WAVE, end - e);
+      const bool last = e + WAVE >= end;  // of this colour
+      const int my_j = nx_j;
+      const float my_w = nx_w;
+      e += WAVE;
+      if (last) {
+        todo &= todo - 1;
+        if (todo) {
+          c = __builtin_ctz(todo);
+          e = __builtin_amdgcn_readlane(o_c, c);
+          end = __builtin_amdgcn_readlane(o_c, c + 1);
+        }
+      }
+      if (todo) {
+        nx_j = scol[beg + min(e + lane, end - 1)];
+        if constexpr (WEIGHTED) nx_w = sw[beg + min(e + lane, end - 1)];
+      }
+      const bool low = cc < l;
+      const int lp = low ? lp_l : lp_h, st = low ? st_l : st_h, nv = low ? nv_l : nv_h;
+      const int stream = low ? stream_l : stream_h, vec0 = low ? vec_l : vec_h;
+      const T *Mc = M + __builtin_amdgcn_readlane(in0, cc);
+      const int passes = (nv + WAVE - 1) / WAVE;  // runs of more than 64 vectors (then one stream)
+      for (int ps = 0; ps < passes; ++ps) {
+        const int vec = min(vec0 + ps * WAVE, nv - 1);
+        if (passes > 1) {
+#pragma unroll
+          for (int u = 0; u < N; ++u) acc.x[u] = T(0);
+        }
+        auto rows = [&](int t0, auto un) {
+          constexpr int U = decltype(un)::value;
+          u32x4 v[U];
+          float wq[U];
+#pragma unroll
+          for (int q = 0; q < U; ++q) {
+            const int sq = min(t0 + q * st + stream, nb - 1);
+            const int jq = shfl_i32(my_j, sq);
+            wq[q] = 1.f;
+            if constexpr (WEIGHTED) wq[q] = shfl(my_w, sq);
+            v[q] = *(const u32x4 *)(Mc + (int64_t)jq * a.ldm + vec * N);
+          }
+#pragma unroll
+          for (int q = 0; q < U; ++q) {
+            const bool ok = t0 + q * st + stream < nb;
+            const V16<T> x = __builtin_bit_cast(V16<T>, v[q]);
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+              const T y = ok ? x.x[u] : T(0);
+              if constexpr (WEIGHTED) acc.x[u] = A::fma((T)wq[q], y, acc.x[u], ovf);
+              else acc.x[u] = A::add(acc.x[u], y, ovf);
+            }
+          }
+        };
+        int t0 = 0;
+        for (; nb - t0 > 2 * st; t0 += UNR * st) rows(t0, std::integral_constant<int, UNR>());
+        if (nb - t0 > st) rows(t0, std::integral_constant<int, 2>());
+        else if (nb > t0) rows(t0, std::integral_constant<int, 1>());
+        if (!last && passes == 1) break;
+        // the colour's sum (of each stream) to the stage, from there to the outputs
+        wave_lds_fence();
+        if (stream < st && vec0 + ps * WAVE < nv) *(V16<T> *)(stg + stream * nv * N + vec * N) = acc;
+        wave_lds_fence();
+        if (ps == passes - 1) {
+          const int row = low ? cc : l;
+#pragma unroll
+          for (int v = 0; v < NP; ++v) {
+            const int o = linv[row * cw + pabs[v]];
+            T x = T(0);
+            if (o != 0xFFFF) {
+              x = stg[o];
+              for (int s2 = 1; s2 < st; ++s2) x = A::add(x, stg[s2 * nv * N + o], ovf);
+            }
+            out[v] = A::add(out[v], x, ovf);
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < N; ++u) acc.x[u] = T(0);
+      }
+    }
+  };
+  auto write = [&](T *dst, int r, int nout, bool final) {
+    const int gap = r < l ? 0 : ogap;
+#pragma unroll
+    for (int v = 0; v < NP; ++v) {
+      const int p = lane + v * WAVE;
+      if (p < nout) {
+        T x = out[v];
+        if constexpr (sizeof(T) == 4) {
+          x *= f;
+          if (final) cmax = fmaxf(cmax, x);
+        }
+        dst[p + (p >= osplit ? gap : 0)] = x;
+      }
+    }
+  };
+
+  // the split tasks, range blockIdx.x % xsplit (workgroups go to the XCDs in turn)
+  if (a.x_tasks > 0) {
+    const int xr = blockIdx.x % a.xsplit;
+    const int64_t step = (int64_t)(gridDim.x / a.xsplit) * WAVES_PER_BLOCK;
+    for (int64_t t = (int64_t)(blockIdx.x / a.xsplit) * WAVES_PER_BLOCK + wv; t < a.x_tasks; t += step) {
+      const int r = __builtin_amdgcn_readfirstlane((int)col[a.task_row[t]]);
+      const int o0 = __builtin_amdgcn_readlane(out0, r);
+      if (o0 < 0) continue;
+      const int nout = r < l ? lout_low : lout_high;
+      task(a.task_beg[t] + a.tsplit[t * (a.xsplit + 1) + xr], r, t * a.xsplit + xr, nout);
+      write(P8 + ((int64_t)xr * a.x_tasks + t) * a.ldb + o0, r, nout, false);
+    }
+  }
+  for (int64_t t = a.x_tasks + (int64_t)blockIdx.x * WAVES_PER_BLOCK + wv; t < a.n_tasks;
+       t += (int64_t)gridDim.x * WAVES_PER_BLOCK) {
+    const int row = a.task_row[t], slot = a.task_slot[t];
+    const int r = __builtin_amdgcn_readfirstlane((int)col[row]);
+    const int o0 = __builtin_amdgcn_readlane(out0, r);
+    if (o0 < 0) continue;
+    const int nout = r < l ? lout_low : lout_high;
+    task(a.task_beg[t], r, a.x_tasks * a.xsplit + t - a.x_tasks, nout);
+    write((slot < 0 ? B + (int64_t)row * a.ldb : Pt + (int64_t)slot * a.ldb) + o0, r, nout, slot < 0);
+  }
+  if constexpr (is_u64<T>) {
+    if (ovf) atomicOr(a.ovf, 1);
+  }
+  if constexpr (sizeof(T) == 4) {
+    cmax = wave_max(cmax);
+    if (lane == 0 && cmax > 0.f) atomicMax(a.mx_out + jj, __float_as_uint(cmax));
+  }
+}
+
+// The eight range partials of every split task, in range order: to its row, or to
+// the slot of its segment.
+template <typename T>
+__global__ void __launch_bounds__(BLOCK) k_rel_xsum(RelXsumArgs a) {
+  constexpr int N = V16<T>::N;
+  const int jj = blockIdx.y;
+  const int64_t nvec = (a.w + N - 1) / N, total = nvec * a.n_tasks;
+  const T *P = (const T *)a.partial8 + jj * a.p8plane;
+  bool ovf = false;
+  float cmax = 0.f;
+  for (int64_t q = (int64_t)blockIdx.x * BLOCK + threadIdx.x; q < total; q += (int64_t)gridDim.x * BLOCK) {
+    const int64_t t = q / nvec, v = q - t * nvec;
+    V16<T> x[8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) x[r] = *(const V16<T> *)(P + ((int64_t)r * a.n_tasks + t) * a.ld + v * N);
+    const int slot = a.task_slot[t];
+    V16<T> s = x[0];
+#pragma unroll
+    for (int r = 1; r < 8; ++r)
+#pragma unroll
+      for (int u = 0; u < N; ++u) {
+        bool o = false;
+        s.x[u] = Arith<T>::add(s.x[u], x[r].x[u], o);
+        ovf |= o && v * N + u < a.w;
+      }
+    T *dst = slot < 0 ? (T *)a.B + jj * a.bplane + (int64_t)a.task_row[t] * a.ld
+                      : (T *)a.partial + jj * a.pplane + (int64_t)slot * a.ld;
+    *(V16<T> *)(dst + v * N) = s;
+    if (slot < 0)
+#pragma unroll
+      for (int u = 0; u < N; ++u)
+        if (v * N + u < a.w) cmax = fmaxf(cmax, (float)s.x[u]);
+  }
+  if constexpr (is_u64<T>) {
+    if (ovf) atomicOr(a.ovf, 1);
+  }
+  if (a.mx) {
+    cmax = wave_max(cmax);
+    if ((threadIdx.x & (WAVE - 1)) == 0 && cmax > 0.f) atomicMax(a.mx + jj, __float_as_uint(cmax));
   }
 }
 
@@ -706,6 +1021,7 @@ __global__ void __launch_bounds__(NT) k_rel_ema(RelEmaArgs a) {
     stage(Y, a.ldy, a.wb, i0, nrow, fy, lb);
     __syncthreads();
     for (int C = threadIdx.x; C < a.ws; C += NT) {
+      const int oc = a.opos ? a.opos[C] : C;
       T acc[R];
 #pragma unroll
       for (int r = 0; r < R; ++r) acc[r] = T(0);
@@ -739,7 +1055,7 @@ __global__ void __launch_bounds__(NT) k_rel_ema(RelEmaArgs a) {
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         if (r < nrow) {
-          Ms[(i0 + r) * a.ldm + C] = acc[r];
+          Ms[(i0 + r) * a.ldm + oc] = acc[r];
           if constexpr (SC) cmax = fmaxf(cmax, (float)acc[r]);
         }
       }
@@ -913,6 +1229,9 @@ static int rel_spmm_t(const RelSpmmArgs &a, dim3 grid, size_t lds, hipStream_t s
     case 1: rel_go(k_rel_spmm<T, WEIGHTED, 1, false>, a, grid, BLOCK, lds, s); return 0;
     case 2: rel_go(k_rel_spmm<T, WEIGHTED, 2, false>, a, grid, BLOCK, lds, s); return 0;
     case 3: rel_go(k_rel_spmm<T, WEIGHTED, 3, false>, a, grid, BLOCK, lds, s); return 0;
+    case 4: rel_go(k_rel_spmm<T, WEIGHTED, 4, false>, a, grid, BLOCK, lds, s); return 0;
+    case 5: rel_go(k_rel_spmm<T, WEIGHTED, 5, false>, a, grid, BLOCK, lds, s); return 0;
+    case 6: rel_go(k_rel_spmm<T, WEIGHTED, 6, false>, a, grid, BLOCK, lds, s); return 0;
     default: return -1;
   }
 }
@@ -921,6 +1240,42 @@ int launch_rel_spmm(int dtype, const RelSpmmArgs &a, dim3 grid, size_t lds, hipS
   if (dtype == DT_F32) return a.w ? rel_spmm_t<float, true>(a, grid, lds, s) : rel_spmm_t<float, false>(a, grid, lds, s);
   if (dtype == DT_F64) return a.w ? rel_spmm_t<double, true>(a, grid, lds, s) : rel_spmm_t<double, false>(a, grid, lds, s);
   return a.w ? -1 : rel_spmm_t<uint64_t, false>(a, grid, lds, s);
+}
+
+void launch_rel_sort(const RelSortArgs &a, int b, hipStream_t s) {
+  const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>((a.n_items + 3) / 4, 16384)), (unsigned)b);
+  if (a.w) k_rel_sort<true><<<grid, BLOCK, 0, s>>>(a);
+  else k_rel_sort<false><<<grid, BLOCK, 0, s>>>(a);
+}
+
+template <typename T, bool WEIGHTED>
+static void rel_wide_t(const RelWideArgs &a, dim3 grid, size_t lds, hipStream_t s) {
+  if (a.nout_max <= 128) rel_go(k_rel_wide<T, WEIGHTED, 2>, a, grid, BLOCK, lds, s);
+  else if (a.nout_max <= 256) rel_go(k_rel_wide<T, WEIGHTED, 4>, a, grid, BLOCK, lds, s);
+  else rel_go(k_rel_wide<T, WEIGHTED, 6>, a, grid, BLOCK, lds, s);
+}
+
+int launch_rel_wide(int dtype, const RelWideArgs &a, dim3 grid, size_t lds, hipStream_t s) {
+  if (a.nout_max > 384) return -1;
+  if (dtype == DT_F32) {
+    if (a.sw) rel_wide_t<float, true>(a, grid, lds, s);
+    else rel_wide_t<float, false>(a, grid, lds, s);
+  } else if (dtype == DT_F64) {
+    if (a.sw) rel_wide_t<double, true>(a, grid, lds, s);
+    else rel_wide_t<double, false>(a, grid, lds, s);
+  } else {
+    rel_wide_t<uint64_t, false>(a, grid, lds, s);
+  }
+  return 0;
+}
+
+void launch_rel_xsum(int dtype, const RelXsumArgs &a, int b, hipStream_t s) {
+  const int N = dtype == DT_F32 ? 4 : 2;
+  const int64_t blocks = (a.n_tasks * ((a.w + N - 1) / N) + BLOCK - 1) / BLOCK;
+  const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>(blocks, 16384)), (unsigned)b);
+  if (dtype == DT_F32) k_rel_xsum<float><<<grid, BLOCK, 0, s>>>(a);
+  else if (dtype == DT_F64) k_rel_xsum<double><<<grid, BLOCK, 0, s>>>(a);
+  else k_rel_xsum<uint64_t><<<grid, BLOCK, 0, s>>>(a);
 }
 
 void launch_rel_combine(int dtype, const RelCombineArgs &a, int b, hipStream_t s) {

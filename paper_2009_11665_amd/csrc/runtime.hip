@@ -799,6 +799,8 @@ struct DevPlan {
   std::vector<char *> cpr;  // colour-restricted tables per node
   std::vector<uint32_t *> rel_pairs, rel_root;  // vertex-relative: per node, per template
   std::vector<uint16_t *> rel_map;              // per node
+  std::vector<uint16_t *> rel_mpos, rel_bpos, rel_tab;
+  std::vector<int32_t *> rel_hdr, rel_info;
 };
 
 // pair-major copy ([q][col]) of a [col][np] x 2 table
@@ -839,6 +841,16 @@ void fill_devplan(const Plan::DeviceTables &d, DevPlan *out) {
   for (void *p : d.rel_pairs) out->rel_pairs.push_back((uint32_t *)p);
   for (void *p : d.rel_map) out->rel_map.push_back((uint16_t *)p);
   for (void *p : d.rel_root) out->rel_root.push_back((uint32_t *)p);
+  out->rel_mpos.clear();
+  out->rel_bpos.clear();
+  out->rel_tab.clear();
+  out->rel_hdr.clear();
+  out->rel_info.clear();
+  for (void *p : d.rel_mpos) out->rel_mpos.push_back((uint16_t *)p);
+  for (void *p : d.rel_bpos) out->rel_bpos.push_back((uint16_t *)p);
+  for (void *p : d.rel_tab) out->rel_tab.push_back((uint16_t *)p);
+  for (void *p : d.rel_hdr) out->rel_hdr.push_back((int32_t *)p);
+  for (void *p : d.rel_info) out->rel_info.push_back((int32_t *)p);
 }
 
 sg2v_status plan_device(const Plan &P, int device, hipStream_t s, DevPlan *out) {
@@ -902,18 +914,39 @@ sg2v_status plan_device(const Plan &P, int device, hipStream_t s, DevPlan *out) 
     if (fits) ST_TRY(upload(l16, &D.root_list16[r], s));
   }
   if (rel_ok(P, 4, kRelLds)) {
-    D.rel_pairs.assign(nn, nullptr);
-    D.rel_map.assign(nn, nullptr);
+    for (auto *v : {&D.rel_pairs, &D.rel_map, &D.rel_mpos, &D.rel_bpos, &D.rel_tab, &D.rel_hdr, &D.rel_info})
+      v->assign(nn, nullptr);
     D.rel_root.assign(P.roots.size(), nullptr);
+    std::vector<char> wm, wb;
+    rel_wide_nodes(P, wm, wb);
+    auto u16 = [](const std::vector<int32_t> &x) { return std::vector<uint16_t>(x.begin(), x.end()); };
+    auto lay_b = [&](int p) { return rel_layout(P.k, P.nodes[p].size, wb[p]); };
+    auto lay_m = [&](int q) {
+      const Node &A = P.nodes[q];
+      if (A.size > 1 && P.nodes[A.active].size == 1) return lay_b(A.passive);
+      return rel_layout(P.k, A.size - 1, wm[q]);
+    };
     for (size_t i = 0; i < nn; ++i) {
       const Node &nd = P.nodes[i];
+      if (wb[i]) ST_TRY(upload(u16(lay_b((int)i).pos), &D.rel_bpos[i], s));
+      if (wm[i]) ST_TRY(upload(u16(lay_m((int)i).pos), &D.rel_mpos[i], s));
       if (nd.size == 1) continue;
-      if (nd.n_passive_uses > 0) ST_TRY(upload(rel_map(P.k, nd.size).map, &D.rel_map[i], s));
+      if (nd.n_passive_uses > 0 && (rel_wide(P.k, nd.size) || !wb[i])) {
+        const RelWide w = rel_wide_tables(P.k, nd.size, wb[i]);
+        ST_TRY(upload(w.hdr, &D.rel_hdr[i], s));
+        ST_TRY(upload(w.info, &D.rel_info[i], s));
+        ST_TRY(upload(w.tab, &D.rel_tab[i], s));
+        HIP_TRY(hipStreamSynchronize(s));  // the copies read this scope's arrays
+      }
+      if (nd.n_passive_uses > 0 && !rel_wide(P.k, nd.size)) {
+        ST_TRY(upload(rel_map(P.k, nd.size).map, &D.rel_map[i], s));
+      }
       const int ma = P.nodes[nd.active].size;
       if (P.root_index[i] >= 0)
-        ST_TRY(upload(rel_root_list(P.k, nd.size, ma), &D.rel_root[P.root_index[i]], s));
+        ST_TRY(upload(rel_root_list(P.k, nd.size, ma, lay_m(nd.active), lay_b(nd.passive)),
+                      &D.rel_root[P.root_index[i]], s));
       else if (ma > 1)
-        ST_TRY(upload(rel_pairs(P.k, nd.size, ma), &D.rel_pairs[i], s));
+        ST_TRY(upload(rel_pairs(P.k, nd.size, ma, lay_m(nd.active), lay_b(nd.passive)), &D.rel_pairs[i], s));
     }
   }
   HIP_TRY(hipStreamSynchronize(s));
@@ -956,6 +989,7 @@ struct PassPlan {
 
 struct Workspace {
   DevBuf arena, small, partial, result, ovf, grad, bucket, nbrcol, xpart;
+  DevBuf relsort;  // entries by neighbour colour (wide vertex-relative aggregations)
 };
 
 Workspace &workspace() {
@@ -1111,6 +1145,9 @@ struct RelPass {
   int64_t arena = 0, partial_off = 0;
   int64_t small_bytes = 0;
   int ntab = 0;
+  bool wide = false;         // some aggregation goes in chunks
+  int64_t wide_ld = 0;       // widest output row of those
+  std::vector<char> wide_m, wide_b;
 };
 
 // Row stride of w columns: whole 16-byte vectors; rows below 64 bytes a power
@@ -1163,6 +1200,9 @@ void build_rel(const Plan &P, const sg2v_graph *g, int b, int dt, RelPass &rp) {
   }
   std::vector<Tab *> all;
   rp.ntab = 0;
+  rel_wide_nodes(P, rp.wide_m, rp.wide_b);
+  rp.wide = false;
+  rp.wide_ld = 0;
   int64_t widest = 1;
   for (int kind = 0; kind < 2; ++kind)  // the histogram's table is number 0 (single vertices come first)
     for (size_t s = 0; s < nn; ++s) {
@@ -1170,7 +1210,12 @@ void build_rel(const Plan &P, const sg2v_graph *g, int b, int dt, RelPass &rp) {
       if (r.t.last < 0) continue;
       const int q = P.nodes[s].size - (kind == 0 ? 0 : 1);
       r.t.cols = binom(P.k - 1, q);
-      r.t.ld = rel_ld(r.t.cols, es);
+      const bool padded = kind == 0 ? rp.wide_b[s] : rp.wide_m[s];
+      r.t.ld = rel_ld(padded ? rel_layout(P.k, q, true).width : r.t.cols, es);
+      if (kind == 0 && P.nodes[s].size > 1) {
+        rp.wide |= rel_wide(P.k, P.nodes[s].size);
+        rp.wide_ld = std::max(rp.wide_ld, r.t.ld);
+      }
       r.plane = g->n * r.t.ld;
       r.t.bytes = round_up(r.plane * b * es, 256);
       r.id = rp.ntab++;
@@ -1178,7 +1223,8 @@ void build_rel(const Plan &P, const sg2v_graph *g, int b, int dt, RelPass &rp) {
       all.push_back(&r.t);
     }
   rp.partial_off = place_tables(all);
-  rp.arena = rp.partial_off + round_up(std::max<int64_t>(g->n_rslots, 1) * widest * b * es, 256);
+  const int64_t slots = std::max<int64_t>(rp.wide ? std::max(g->n_rslots, g->n_slots) : g->n_rslots, 1);
+  rp.arena = rp.partial_off + round_up(slots * widest * b * es, 256);
   rp.small_bytes = (int64_t)rp.ntab * b * 8 + 256;
 }
 
@@ -1220,6 +1266,9 @@ struct Ctx {
   int64_t res_stride = 0;  // results per template (plans of several templates)
   bool rel = false;        // vertex-relative tables (rp) instead of absolute ones (pp)
   RelPass rp;
+  int64_t rel_x = 0;       // tasks taken per neighbour range in wide aggregations
+  int64_t rel_items = 0;
+  int sort_j0 = -1, sort_b = 0;  // pass whose sorted entries are in ws->relsort
   // sg2v_count_noalloc: colour-skip masks copied into the scratch area
   std::map<std::tuple<int, int, int>, void *> tmp_masks;
   std::vector<std::vector<uint32_t>> tmp_host;
@@ -1944,7 +1993,7 @@ int rel_rows(const Ctx &x, int64_t most, int64_t planes) {
   return R;
 }
 
-void rel_combine(Ctx &x, RelTab &t, bool track) {
+void rel_combine(Ctx &x, RelTab &t, int64_t cols, bool track) {
   if (x.g->n_rlong == 0) return;
   RelCombineArgs c{};
   c.partial = (char *)x.ws->arena.p + x.rp.partial_off;
@@ -1952,7 +2001,7 @@ void rel_combine(Ctx &x, RelTab &t, bool track) {
   c.B = t.t.p;
   c.ld = t.t.ld;
   c.bplane = t.plane;
-  c.w = (int32_t)t.t.cols;
+  c.w = (int32_t)cols;
   c.long_row = x.g->rlong_row;
   c.long_slot0 = x.g->rlong_slot0;
   c.long_nslot = x.g->rlong_nslot;
@@ -1997,7 +2046,147 @@ sg2v_status rel_hist(Ctx &x, int node) {
     const int64_t groups = std::max<int64_t>((x.g->n + a.R - 1) / a.R, 4 * (int64_t)a.n_seg);
     launch_rel_hist(x.dt, a, dim3(rel_blocks(x, groups, ny), (unsigned)ny), x.s);
   }
-  rel_combine(x, H, false);
+  rel_combine(x, H, H.t.cols, false);
+  return SG2V_OK;
+}
+
+sg2v_status rel_wide_spmm(Ctx &x, int node) {
+  const Plan &P = *x.P;
+  const int k = P.k, m = P.nodes[node].size;
+  sg2v_graph *g = x.g;
+  RelTab &Mt = x.rp.m_alias[node] >= 0 ? x.rp.B[x.rp.m_alias[node]] : x.rp.M[node];
+  RelTab &B = x.rp.B[node];
+  // entries by colour, once per pass
+  const int64_t nnz = std::max<int64_t>(g->nnz, 1);
+  int32_t *scol = (int32_t *)x.ws->relsort.p;
+  float *sw = g->w ? (float *)(scol + (size_t)x.b * nnz) : nullptr;
+  uint16_t *off = (uint16_t *)(scol + (size_t)x.b * nnz * (g->w ? 2 : 1));
+  if (x.sort_j0 != x.j0 || x.sort_b != x.b) {
+    RelSortArgs sa{};
+    sa.col_idx = g->col_idx;
+    sa.w = g->w;
+    sa.colors = x.c->d;
+    sa.n = g->n;
+    sa.nnz = nnz;
+    sa.k = k;
+    sa.j0 = x.j0;
+    sa.task_beg = g->task_beg;
+    sa.task_len = g->task_len;
+    sa.tsplit = g->tsplit;
+    sa.x_tasks = x.rel_x;
+    sa.xsplit = kXsplit;
+    sa.n_items = x.rel_items;
+    sa.out = scol;
+    sa.wout = sw;
+    sa.off = off;
+    launch_rel_sort(sa, x.b, x.s);
+    x.sort_j0 = x.j0;
+    x.sort_b = x.b;
+  }
+  const int64_t w = x.rp.wide_b[node] ? B.t.ld : B.t.cols;
+  if (x.rp.wide_b[node] || x.dt == DT_U64) {
+    // padding columns that a sum, a maximum or an overflow flag meets
+    launch_fill_u32((unsigned *)((char *)x.ws->arena.p + x.rp.partial_off), x.b * g->n_slots * B.t.ld * x.es / 4, 0u, x.s);
+    launch_fill_u32((unsigned *)x.ws->xpart.p, x.b * (int64_t)kXsplit * x.rel_x * B.t.ld * x.es / 4, 0u, x.s);
+  }
+  if (x.rp.wide_b[node] && x.dt == DT_U64) launch_fill_u32((unsigned *)B.t.p, x.b * B.plane * 2, 0u, x.s);
+  RelWideArgs a{};
+  a.scol = scol;
+  a.sw = sw;
+  a.off = off;
+  a.n_items = x.rel_items;
+  a.nnz = nnz;
+  a.colors = x.c->d;
+  a.n = g->n;
+  a.k = k;
+  a.j0 = x.j0;
+  a.l = rel_wide(k, m) ? rel_low(k) : k;
+  a.nchunk = 0;
+  for (int h = 0; h <= k - a.l; ++h)
+    if (m - h >= 0 && m - h <= a.l) a.nchunk += (int)binom(k - a.l, h);
+  a.hdr = x.dp.rel_hdr[node];
+  a.info = x.dp.rel_info[node];
+  a.tab = x.dp.rel_tab[node];
+  a.task_row = g->task_row;
+  a.task_slot = g->task_slot;
+  a.task_beg = g->task_beg;
+  a.tsplit = g->tsplit;
+  a.x_tasks = x.rel_x;
+  a.n_tasks = g->n_tasks;
+  a.xsplit = kXsplit;
+  a.nout_max = 0;
+  int cw = 4;
+  const int N = 16 / x.es;
+  a.stage = 64 * N;
+  for (int s = std::max(0, m - (k - a.l)); s <= std::min(a.l, m); ++s) {
+    const int C = (int)binom(a.l, s);
+    a.nout_max = std::max(a.nout_max, a.l == k ? (int)binom(k - 1, s) : C);
+    cw = std::max(cw, (int)round_up(C, 4));
+    a.stage = std::max(a.stage, (int)round_up(C + 32, 4));
+  }
+  a.M = Mt.t.p;
+  a.ldm = Mt.t.ld;
+  a.mplane = Mt.plane;
+  a.B = B.t.p;
+  a.ldb = B.t.ld;
+  a.bplane = B.plane;
+  a.partial = (char *)x.ws->arena.p + x.rp.partial_off;
+  a.pplane = g->n_slots * B.t.ld;
+  a.partial8 = x.ws->xpart.p;
+  a.p8plane = (int64_t)kXsplit * x.rel_x * B.t.ld;
+  a.e_in = Mt.t.e;
+  a.mx_in = Mt.t.mx;
+  a.e_out = B.t.e;
+  a.mx_out = B.t.mx;
+  a.ovf = x.ovf;
+  const size_t lds = (size_t)round_up(2 * (a.l + 1) * cw * 2, 16) + (size_t)4 * a.stage * x.es;
+  {
+    const double n = (double)g->n, ez = (double)g->nnz;
+    ProfScope ps(SG2V_K_SPMM,
+                 x.b * (n * (Mt.t.cols + B.t.cols) * x.es + a.nchunk * (ez * (4.0 + (g->w ? 4.0 : 0.0)) + 90.0 * g->n_tasks)),
+                 ez * (double)binom(k, m) * x.b, x.s);
+    // blocks along the tasks: whole rounds of the eight XCDs
+    const int64_t gx = round_up(std::max<int64_t>(1, std::min<int64_t>((x.rel_items + 3) / 4, 4096)), kXsplit);
+    if (launch_rel_wide(x.dt, a, dim3((unsigned)gx, (unsigned)(a.nchunk * x.b)), lds, x.s)) {
+      set_error("sg2v_count: no chunked aggregation of %d columns", a.nout_max);
+      return SG2V_EINVAL;
+    }
+  }
+  if (x.rel_x > 0) {
+    RelXsumArgs xs{};
+    xs.partial8 = a.partial8;
+    xs.p8plane = a.p8plane;
+    xs.task_row = g->task_row;
+    xs.task_slot = g->task_slot;
+    xs.n_tasks = x.rel_x;
+    xs.B = a.B;
+    xs.partial = a.partial;
+    xs.ld = a.ldb;
+    xs.bplane = a.bplane;
+    xs.pplane = a.pplane;
+    xs.w = (int32_t)w;
+    xs.mx = x.dt == DT_F32 ? B.t.mx : nullptr;
+    xs.ovf = x.ovf;
+    ProfScope ps(SG2V_K_SPMM_COMBINE, 9.0 * x.b * (double)x.rel_x * w * x.es, (double)x.rel_x * w * x.b, x.s);
+    launch_rel_xsum(x.dt, xs, x.b, x.s);
+  }
+  if (g->n_long > 0) {
+    RelCombineArgs c{};
+    c.partial = a.partial;
+    c.pplane = a.pplane;
+    c.B = a.B;
+    c.ld = a.ldb;
+    c.bplane = a.bplane;
+    c.w = (int32_t)w;
+    c.long_row = g->long_row;
+    c.long_slot0 = g->long_slot0;
+    c.long_nslot = g->long_nslot;
+    c.n_long = g->n_long;
+    c.mx = x.dt == DT_F32 ? B.t.mx : nullptr;
+    c.ovf = x.ovf;
+    ProfScope ps(SG2V_K_SPMM_COMBINE, (double)(g->n_slots + g->n_long) * w * x.b * x.es, (double)g->n_slots * w * x.b, x.s);
+    launch_rel_combine(x.dt, c, x.b, x.s);
+  }
   return SG2V_OK;
 }
 
@@ -2022,6 +2211,13 @@ sg2v_status rel_spmm(Ctx &x, int node) {
   a.bplane = B.plane;
   a.partial = (char *)x.ws->arena.p + x.rp.partial_off;
   a.pplane = x.g->n_rslots * B.t.ld;
+  // Sorted entries pay where a row has several of a colour: with them at hand for
+  // the wide aggregations, from a mean degree of 4 k on for the others too (455 sets
+  // of the 15-vertex tree: RMAT scale 20, FP32 16.2 -> 10.5 ms; scale 18, FP64 5.9 ->
+  // 6.1 ms, so FP32 only).
+  if (rel_wide(k, m) || (x.rp.wide && x.es == 4 && !x.rp.wide_b[node] && x.g->nnz >= 4 * k * x.g->n))
+    return rel_wide_spmm(x, node);
+  a.opos = x.dp.rel_bpos[node];
   a.cw = (int32_t)round_up(binom(k, m), 4);
   a.wout = (int32_t)B.t.cols;
   a.wout4 = (int32_t)round_up(B.t.cols, 4);
@@ -2031,7 +2227,7 @@ sg2v_status rel_spmm(Ctx &x, int node) {
   a.wmap = (int32_t)round_up(Mt.t.cols, 4);
   a.sr = (int32_t)round_up(Mt.t.cols, 4) + 4;
   a.lp = (int32_t)((Mt.t.cols + N - 1) / N);
-  if (a.lp > 64 || a.wout < 1 || a.wout > 192) {
+  if (a.lp > 64 || a.wout < 1 || a.wout > 384) {
     set_error("sg2v_count: aggregated rows of %d columns have no vertex-relative kernel", (int)Mt.t.cols);
     return SG2V_EINVAL;
   }
@@ -2072,12 +2268,15 @@ sg2v_status rel_spmm(Ctx &x, int node) {
                  x.b * (n * (Mt.t.cols + B.t.cols) * x.es + nnz * (5.0 + (x.g->w ? 4.0 : 0.0)) + 9.0 * n),
                  nnz * (double)binom(k, m) * x.b, x.s);
     const int64_t groups = std::max<int64_t>((x.g->n + a.R - 1) / a.R, 4 * (int64_t)a.n_seg);
+    if (a.opos && x.dt == DT_U64) launch_fill_u32((unsigned *)B.t.p, x.b * B.plane * 2, 0u, x.s);
+    if (a.opos)  // padding of partial rows, which the combine reads
+      launch_fill_u32((unsigned *)a.partial, x.b * a.pplane * x.es / 4, 0u, x.s);
     if (launch_rel_spmm(x.dt, a, dim3(rel_blocks(x, groups, x.b), (unsigned)x.b), lds, x.s)) {
       set_error("sg2v_count: no vertex-relative SpMM variant for %d columns", a.wout);
       return SG2V_EINVAL;
     }
   }
-  rel_combine(x, B, true);
+  rel_combine(x, B, a.opos ? B.t.ld : B.t.cols, true);
   return SG2V_OK;
 }
 
@@ -2095,9 +2294,14 @@ sg2v_status rel_ema(Ctx &x, int node) {
   a.M = O.t.p;
   a.ldm = O.t.ld;
   a.mplane = O.plane;
-  a.wa = (int32_t)X.t.cols;
-  a.wb = (int32_t)Y.t.cols;
+  // padded tables are staged with their padding
+  auto width = [&](bool padded, const RelTab &t, int q) { return padded ? rel_layout(x.P->k, q, true).width : t.t.cols; };
+  const int am = x.rp.m_alias[nd.active];
+  a.wa = (int32_t)width(am >= 0 ? x.rp.wide_b[am] : x.rp.wide_m[nd.active], X, x.P->nodes[nd.active].size - 1);
+  a.wb = (int32_t)width(x.rp.wide_b[nd.passive], Y, x.P->nodes[nd.passive].size);
   a.ws = (int32_t)O.t.cols;
+  a.opos = x.dp.rel_mpos[node];
+  if (a.opos && x.dt == DT_U64) launch_fill_u32((unsigned *)O.t.p, x.b * O.plane * 2, 0u, x.s);
   a.np = (int32_t)binom(nd.size - 1, x.P->nodes[nd.active].size - 1);
   a.pairs = x.dp.rel_pairs[node];
   a.n = x.g->n;
@@ -2281,6 +2485,38 @@ bool rel_wanted(const sg2v_tuning_t &t) {
   return (t.flags & ~(SG2V_TUNE_BATCH_SERIAL | SG2V_TUNE_GRAD_RECOMPUTE)) == 0;
 }
 
+// Buffers of the wide aggregations: sorted entries and their offsets, and the
+// range partials of split tasks.  Where a fixed area cannot hold them the pass
+// uses the absolute tables.
+sg2v_status rel_wide_buffers(Ctx &x) {
+  sg2v_graph *g = x.g;
+  const int64_t nnz = std::max<int64_t>(g->nnz, 1);
+  // the automatic rule of the neighbour-range split: large graphs whose long
+  // tasks hold at least half the entries
+  x.rel_x = 0;
+  if (large_graph(g->n) && g->long_share >= 0.5 && (g->tsplit || !t_noalloc)) {
+    while (x.rel_x < g->n_tasks && g->h_task_len[x.rel_x] >= kXsplitMin) ++x.rel_x;
+    if ((double)x.b * kXsplit * x.rel_x * x.rp.wide_ld * x.es > 4 * kXpartBytes) x.rel_x = 0;
+  }
+  x.rel_items = x.rel_x * kXsplit + g->n_tasks - x.rel_x;
+  const size_t sort_bytes = (size_t)x.b * (nnz * (g->w ? 8 : 4) + x.rel_items * 64) + 256;
+  const size_t part_bytes = (size_t)x.b * kXsplit * x.rel_x * x.rp.wide_ld * x.es + 256;
+  if (Carver *cv = x.ws->arena.cv) {
+    const size_t need = x.rp.arena + x.rp.small_bytes + (size_t)kRootBlocks * x.b * 8 + sort_bytes + part_bytes + 8192;
+    if (need > cv->cap) {
+      x.rel = false;
+      return SG2V_OK;
+    }
+  }
+  if (x.rel_x > 0 && !g->tsplit) {
+    HIP_TRY(hipMalloc((void **)&g->tsplit, (size_t)g->n_tasks * (kXsplit + 1) * sizeof(uint16_t)));
+    launch_task_split(g->col_idx, g->task_beg, g->task_len, g->n_tasks, g->n, kXsplit, g->xbounds, g->tsplit, x.s);
+    HIP_TRY(hipGetLastError());
+  }
+  ST_TRY(x.ws->relsort.ensure(sort_bytes));
+  return x.ws->xpart.ensure(part_bytes);
+}
+
 sg2v_status prepare(Ctx &x, const sg2v_plan *plan, sg2v_graph *g, const sg2v_colorings *c,
                     sg2v_mode mode, int b, hipStream_t s, const PassOpts &opt, Workspace *wsp = nullptr) {
   x.P = &plan->p;
@@ -2336,11 +2572,13 @@ sg2v_status prepare(Ctx &x, const sg2v_plan *plan, sg2v_graph *g, const sg2v_col
     build_rel(plan->p, g, b, x.dt, x.rp);
     x.rel = x.rp.arena <= std::max<int64_t>(x.pp.arena, (int64_t)1 << 20) && x.rp.small_bytes <= x.pp.small_bytes + 4096;
   }
+  if (x.rel && x.rp.wide) ST_TRY(rel_wide_buffers(x));
   ST_TRY(x.ws->arena.ensure(x.rel ? x.rp.arena : x.pp.arena));
   ST_TRY(x.ws->small.ensure(x.rel ? x.rp.small_bytes : x.pp.small_bytes));
   ST_TRY(x.ws->partial.ensure((size_t)kRootBlocks * b * 8));
   ST_TRY(x.ws->ovf.ensure(256));
   x.ovf = (int *)x.ws->ovf.p;
+  x.sort_j0 = -1;
   if (x.rel) return bind_tables(x);
   ST_TRY(x.ws->bucket.ensure((size_t)b * (64 + g->n) * 4 + 256));
   if (!(tuning().flags & SG2V_TUNE_NO_COLOR_SKIP))
@@ -2617,7 +2855,7 @@ extern "C" sg2v_status sg2v_count_noalloc(const sg2v_plan *plan, const sg2v_grap
     cv.cap = SG2V_NOALLOC_SCRATCH_BYTES;
     Workspace ws;
     DevBuf *bufs[] = {&ws.arena, &ws.small, &ws.partial, &ws.result, &ws.ovf,
-                      &ws.grad,  &ws.bucket, &ws.nbrcol, &ws.xpart};
+                      &ws.grad,  &ws.bucket, &ws.nbrcol, &ws.xpart, &ws.relsort};
     // colourings per pass: as sg2v_count would take them, halved until the pass fits
     int b = choose_batch(P, ncol, dt, g->n, g->n_slots);
     std::unique_ptr<Ctx> x;
@@ -2735,7 +2973,7 @@ struct BatchGraph {
   uint64_t seed = 0;
   int ncol = 0, mode = 0;
   sg2v_tuning_t tune{};
-  uint64_t gens[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+  uint64_t gens[10] = {0};
   std::vector<std::unique_ptr<sg2v_colorings>> cols;
   // per-template workspaces when the templates run as parallel graph branches
   std::vector<std::unique_ptr<Workspace>> wss;
@@ -2872,6 +3110,7 @@ void ws_gens(Workspace &ws, uint64_t *out) {
   out[6] = ws.bucket.gen;
   out[7] = ws.nbrcol.gen;
   out[8] = ws.xpart.gen;
+  out[9] = ws.relsort.gen;
 }
 
 }  // namespace
@@ -2946,7 +3185,7 @@ extern "C" sg2v_status sg2v_count_batch(const sg2v_plan *const *plans, int32_t n
     return e.g == g && e.seed == seed && e.ncol == ncol && e.mode == mode && e.device == dev && e.plans == pv &&
            same_tuning(e.tune, tune) && e.conc == conc;
   };
-  uint64_t gens[9];
+  uint64_t gens[10];
   ws_gens(ws, gens);
   BatchGraph *hit = nullptr;
   if (conc) {
@@ -2993,7 +3232,7 @@ extern "C" sg2v_status sg2v_count_batch(const sg2v_plan *const *plans, int32_t n
       // reuse a cached executable graph if every input and buffer is unchanged
       ws_gens(ws, gens);
       for (auto &e : g_batch_cache)
-        if (same_key(*e) && std::equal(gens, gens + 9, e->gens)) hit = e.get();
+        if (same_key(*e) && std::equal(gens, gens + 10, e->gens)) hit = e.get();
     }
   }
   char *res = (char *)ws.result.p;
@@ -3741,6 +3980,8 @@ extern "C" void sg2v_plan_destroy(sg2v_plan *plan) {
     for (void *q : d.rel_pairs) (void)hipFree(q);
     for (void *q : d.rel_map) (void)hipFree(q);
     for (void *q : d.rel_root) (void)hipFree(q);
+    for (auto *v : {&d.rel_mpos, &d.rel_bpos, &d.rel_tab, &d.rel_hdr, &d.rel_info})
+      for (void *q : *v) (void)hipFree(q);
     (void)hipSetDevice(cur);
   }
   delete plan;

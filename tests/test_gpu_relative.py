@@ -24,7 +24,9 @@ TEMPLATES = [
     ([-1, 0, 1, 2], 4), ([-1, 0, 1, 2], 12),           # widths 1..3; 220 sets
     ([-1, 0, 0, 0, 0], 6), (gg.PATH5, 9), (gg.BINTREE7, 7), (gg.BINTREE7, 9),
     (gg.PATH8, 8), (gg.CATERPILLAR10, 10),
-    ([-1, 0, 1, 2, 3, 4], 12),                         # 495 sets: absolute tables
+    ([-1, 0, 1, 2, 3, 4, 5], 11), (gg.PATH8, 12),      # chunks by high colours
+    (gg.BINTREE15, 15),                                # 6435 sets
+    ([-1, 0, 1, 2, 3], 16),                            # 560 sets: absolute tables
 ]
 
 
@@ -70,6 +72,26 @@ def test_relative_tables_against_oracle_and_absolute(par, k, n):
                     else:
                         assert r["colorful"][j] == pytest.approx(f, rel=TOL[mode])
                         assert r["colorful"][j] == pytest.approx(full["colorful"][j], rel=2 * TOL[mode])
+
+
+def test_relative_chunks_with_neighbour_ranges():
+    """RMAT scale 18 (50M entries): long tasks are taken once per neighbour range;
+    exact counts equal those in absolute tables, with and without renumbering."""
+    G = gg.rmat(18, 25_000_000, seed=5)
+    plan = sg.Plan(gg.BINTREE15, 15)
+    got = []
+    for relabel in (False, True):
+        g = sg.Graph.from_csr(G, relabel=relabel)
+        c = sg.Colorings(g, 15, 2, 1)
+        print("ranges: relative", relabel, flush=True)
+        got.append(int(sg.count(plan, g, c, "u64")["colorful_u64"][0]))
+        f64 = sg.count(plan, g, c, "fp64")["colorful"][0]
+        f32 = sg.count(plan, g, c, "fp32s")["colorful"][0]
+        assert abs(f32 - f64) <= TOL["fp32s"] * f64
+    with sg.tuned(flags=sg.TUNE_NO_COLOR_SKIP):
+        print("ranges: absolute", flush=True)
+        got.append(int(sg.count(plan, g, c, "u64")["colorful_u64"][0]))
+    assert got[0] == got[1] == got[2] and got[0] % 128 == 0
 
 
 def test_relative_tables_partial_pass_and_several_templates():
