@@ -118,6 +118,9 @@ struct Plan {
     // output columns where they are not the ranks (per node: multiply-adds,
     // aggregations); chunk tables of wide aggregations
     std::vector<void *> rel_mpos, rel_bpos, rel_hdr, rel_info, rel_tab;
+    // adjoint in vertex-relative tables, uploaded on first use: maps, pairs of the
+    // active and of the passive columns
+    std::vector<void *> back_map, back_px, back_py;
     // SpMM colour-skip masks per (node, colourings per pass, chunk width)
     std::map<std::tuple<int, int, int>, void *> chunks;
   };
@@ -177,6 +180,14 @@ RelMap rel_map(int k, int m);
 std::vector<uint32_t> rel_pairs(int k, int m, int ma, const RelLayout &X, const RelLayout &Y);
 // root list (x | y << 16) of a template of t vertices, ma in the active child
 std::vector<uint32_t> rel_root_list(int k, int t, int ma, const RelLayout &X, const RelLayout &Y);
+
+// Adjoint: maps of the aggregation (as rel_map's, but a gathered row is an
+// aggregation's, an output row a passive table's), and the pairs (output set,
+// other operand) of a split's active and passive columns
+RelMap rel_map_back(int k, int m);
+std::vector<uint32_t> rel_pairs_back(int k, int m, int ma, bool active);
+// whether the adjoint of the plan runs in vertex-relative tables
+bool rel_grad_ok(const Plan &P, int es, size_t lds);
 
 sg2v_status plan_build(const int32_t *parent, int t, int k, Plan &out);
 // Several templates over the same k, sharing isomorphic rooted sub-templates.

@@ -430,6 +430,9 @@ struct RelEmaArgs {
   int *e_out;
   unsigned *mx_out;
   int *ovf;
+  int32_t accumulate;      // 1: added to M, whose exponent and largest mantissa are e_old, mx_old
+  const int *e_old;
+  const unsigned *mx_old;
 };
 
 struct RelRootArgs {
@@ -454,6 +457,85 @@ struct RelFinalArgs {
   int *ovf;
 };
 
+// Adjoint of one colouring (relgrad.hip).  Exponents and largest mantissas as
+// above (one value each, FP32S only).
+
+struct RelRevArgs {
+  const int64_t *row_ptr;
+  const int32_t *col_idx;
+  int64_t n, nnz;
+  uint32_t *rev;           // entry (j, i) of entry (i, j)
+  int *bad;                // set if an entry has none, or not a unique one
+};
+
+struct RelBackArgs {
+  const int64_t *row_ptr;
+  const int32_t *col_idx;
+  const float *w;          // nullable
+  const uint8_t *col;      // colours of the colouring
+  int64_t n;
+  int32_t k;
+  const void *X;           // adjoint of the aggregation
+  int64_t ldx;
+  const void *M;           // the passive table
+  int64_t ldm;
+  void *O;                 // adjoint of the passive table
+  int64_t ldo;
+  void *partial;           // [slots][ldo]
+  const uint16_t *map;     // [k][cw]: column of an absolute set in a row without that colour, or sr - 4
+  const uint16_t *olist;   // [k][wout4]: absolute set (own colour added) of each column
+  int32_t cw, wout, wout4, sr, lp, streams, R, tlong;
+  const int32_t *seg_row, *seg_len, *seg_slot;
+  const int64_t *seg_beg;
+  int32_t n_seg;
+  const uint32_t *rev;
+  double *grad;            // += scale * derivative, at the reverse entry
+  double scale;
+  const int *ex, *em;
+  const unsigned *mxx, *mxm;
+  int32_t accumulate;
+  const int *e_old;
+  const unsigned *mx_old;
+  int *e_out;
+  unsigned *mx_out;
+};
+
+struct RelBackCombineArgs {
+  const void *partial;
+  void *O;
+  int64_t ldo;
+  int32_t w;
+  const int32_t *long_row, *long_slot0, *long_nslot;
+  int32_t n_long;
+  int32_t accumulate;
+  const int *ex;
+  const unsigned *mxx;
+  const int *e_old;
+  const unsigned *mx_old;
+  unsigned *mx_out;
+};
+
+struct RelHistBackArgs {
+  const int64_t *row_ptr;
+  const int32_t *col_idx;
+  const uint8_t *col;
+  int64_t n;
+  const void *Hb;
+  int64_t ldh;
+  double *grad;
+  double scale;
+  const int *e;
+  const unsigned *mx;
+  int32_t R, tlong;
+  const int32_t *seg_row, *seg_len;
+  const int64_t *seg_beg;
+  int32_t n_seg;
+};
+
+void launch_rel_rev(const RelRevArgs &a, hipStream_t s);
+int launch_rel_back(int dtype, const RelBackArgs &a, dim3 grid, size_t lds, hipStream_t s);
+void launch_rel_back_combine(int dtype, const RelBackCombineArgs &a, hipStream_t s);
+void launch_rel_hist_back(int dtype, const RelHistBackArgs &a, dim3 grid, hipStream_t s);
 void launch_rel_init(int *e, unsigned *mx, int ntab, int b, unsigned hist_bits, hipStream_t s);
 void launch_rel_hist(int dtype, const RelHistArgs &a, dim3 grid, hipStream_t s);
 int launch_rel_spmm(int dtype, const RelSpmmArgs &a, dim3 grid, size_t lds, hipStream_t s);

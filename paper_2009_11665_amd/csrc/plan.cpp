@@ -727,6 +727,66 @@ std::vector<uint32_t> rel_root_list(int k, int t, int ma, const RelLayout &X, co
 }
 
 
+RelMap rel_map_back(int k, int m) {
+  RelMap r;
+  const int64_t C = binom(k, m);
+  r.w_in = (int)binom(k - 1, m);
+  r.w_out = (int)binom(k - 1, m - 1);
+  r.cw = (int)((C + 3) / 4 * 4);
+  r.wout4 = (r.w_out + 3) / 4 * 4;
+  r.zero = (r.w_in + 3) / 4 * 4;
+  r.map.assign((size_t)k * r.cw, (uint16_t)r.zero);
+  r.map.resize((size_t)k * (r.cw + r.wout4), 0);
+  for (int c = 0; c < k; ++c) {
+    for (int p = 0; p < r.w_in; ++p)
+      r.map[(size_t)c * r.cw + colex_rank(abs_of(colex_unrank(p, m, k - 1), c))] = (uint16_t)p;
+    for (int p = 0; p < r.w_out; ++p)
+      r.map[(size_t)k * r.cw + (size_t)c * r.wout4 + p] =
+          (uint16_t)colex_rank(abs_of(colex_unrank(p, m - 1, k - 1), c) | (1u << c));
+  }
+  return r;
+}
+
+std::vector<uint32_t> rel_pairs_back(int k, int m, int ma, bool active) {
+  const int q = active ? ma - 1 : m - ma, other = m - 1 - q;  // sizes of the sets
+  const int64_t w = binom(k - 1, q);
+  const int np = (int)binom(k - 1 - q, other);
+  std::vector<uint32_t> out((size_t)w * np);
+  const uint32_t all = (1u << (k - 1)) - 1;
+  for (int64_t x = 0; x < w; ++x) {
+    const uint32_t Q = colex_unrank(x, q, k - 1);
+    int n = 0;
+    for (uint32_t rest = all & ~Q, s = rest;; s = (s - 1) & rest) {  // subsets of the rest
+      if (__builtin_popcount(s) == other)
+        out[(size_t)n++ * w + x] = (uint32_t)colex_rank(Q | s) | ((uint32_t)colex_rank(s) << 16);
+      if (s == 0) break;
+    }
+  }
+  return out;
+}
+
+bool rel_grad_ok(const Plan &P, int es, size_t lds) {
+  if (P.roots.size() != 1 || P.root_kind == ROOT_VERTEX || !rel_ok(P, es, lds)) return false;
+  const int pad = 16 / es;
+  for (size_t q = 0; q < P.nodes.size(); ++q) {
+    const Node &nd = P.nodes[q];
+    if (nd.size == 1) continue;
+    if (nd.n_passive_uses > 0 &&
+        (rel_wide(P.k, nd.size) || binom(P.k - 1, nd.size) * es > 64 * 16 || binom(P.k - 1, nd.size - 1) > 128))
+      return false;
+    const int ma = P.nodes[nd.active].size, mp = nd.size - ma;
+    if (ma == 1) continue;
+    const int64_t wa = binom(P.k - 1, ma - 1), wb = binom(P.k - 1, mp), ws = binom(P.k - 1, nd.size - 1);
+    if (P.root_index[q] >= 0) {
+      if ((size_t)(std::max(wa, wb) * (16 + pad) * es) > lds) return false;
+    } else if ((size_t)((ws + std::max(wa, wb)) * (4 + pad) * es) > lds) {
+      return false;
+    }
+  }
+  return true;
+}
+
+
 // ---------------------------------------------------------------------------
 // Choice of root and cut order (Sec. 2.3.2).  The colourful count sums the
 // rooted counts over every image of the root, so it is the number of

@@ -1,0 +1,68 @@
+// Device helpers of the vertex-relative kernels (rel.hip, relgrad.hip).
+#pragma once
+
+#include "kernels.h"
+
+namespace sg2v {
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+// LDS add whose order is fixed for a given address: the adds of one wave are
+// issued in program order and those of one instruction in lane order.
+template <typename T>
+__device__ __forceinline__ void rel_add(T *p, T v, bool valid, bool &ovf) {
+  if constexpr (is_u64<T>) {
+    const T old = atomicAdd((unsigned long long *)p, (unsigned long long)v);
+    ovf |= valid && old + v < old;
+  } else {
+    __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+  }
+}
+
+// FP32S frame of a table of one colouring: exponent E and factor 2^(e - E)
+// from its exponent and the bits of its largest mantissa (0: a zero table)
+__device__ __forceinline__ int rel_frame(int e, unsigned mx) { return mx ? e + ilog2_bits(mx) + 1 : 0; }
+__device__ __forceinline__ float rel_factor(unsigned mx) { return mx ? exp2_int(-(ilog2_bits(mx) + 1)) : 0.f; }
+
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+__device__ __forceinline__ float wave_max(float m) {
+  for (int off = 1; off < WAVE; off <<= 1) m = fmaxf(m, shfl_xor(m, off));
+  return m;
+}
+
+// FP32S: a contribution of exponent ec (cz: it is zero) added to a table of
+// exponent eo and largest mantissa bits mo: the exponent of the sum and the
+// factors of the old values and of the contribution
+struct RelAdd {
+  int e;
+  float so, sn;
+};
+__device__ __forceinline__ RelAdd rel_accumulate(int eo, unsigned mo, int ec, bool cz) {
+  RelAdd r;
+  if (cz) {
+    r.e = eo;
+    r.so = 1.f;
+    r.sn = 0.f;
+  } else if (mo == 0u) {
+    r.e = ec;
+    r.so = 0.f;
+    r.sn = 1.f;
+  } else {
+    r.e = max(eo, ec);
+    r.so = exp2_int(eo - r.e);
+    r.sn = exp2_int(ec - r.e);
+  }
+  return r;
+}
+
+template <typename K, typename A>
+inline void rel_go(K kern, const A &a, dim3 grid, int nt, size_t lds, hipStream_t s) {
+  if (lds > 65536) (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  kern<<<grid, nt, lds, s>>>(a);
+}
+
+}  // namespace sg2v

@@ -21,37 +21,9 @@
 
 #include "kernels.h"
 #include "launch.h"
+#include "rel.h"
 
 namespace sg2v {
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-// LDS add whose order is fixed for a given address: the adds of one wave are
-// issued in program order and those of one instruction in lane order.
-template <typename T>
-__device__ __forceinline__ void rel_add(T *p, T v, bool valid, bool &ovf) {
-  if constexpr (is_u64<T>) {
-    const T old = atomicAdd((unsigned long long *)p, (unsigned long long)v);
-    ovf |= valid && old + v < old;
-  } else {
-    __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-  }
-}
-
-// FP32S frame of a table of one colouring: exponent E and factor 2^(e - E)
-// from its exponent and the bits of its largest mantissa (0: a zero table)
-__device__ __forceinline__ int rel_frame(int e, unsigned mx) { return mx ? e + ilog2_bits(mx) + 1 : 0; }
-__device__ __forceinline__ float rel_factor(unsigned mx) { return mx ? exp2_int(-(ilog2_bits(mx) + 1)) : 0.f; }
-
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
-__device__ __forceinline__ float wave_max(float m) {
-  for (int off = 1; off < WAVE; off <<= 1) m = fmaxf(m, shfl_xor(m, off));
-  return m;
-}
 
 // Start of a pass: exponents and largest mantissas of every table (the
 // histogram's, table 0, is bounded by the largest weighted degree).
@@ -968,7 +940,10 @@ __global__ void __launch_bounds__(BLOCK) k_rel_combine(RelCombineArgs a) {
 // average over the splits of the nine-vertex trees (4M rows of about 60 columns
 // three times, 2.9 GB: 3.7 TB/s).
 
-template <typename T, int R, int NT>
+// Without X (HASX false) it counts as one: the adjoint of a root reduction.  The
+// adjoint also adds to a table that holds values already (a.accumulate).
+
+template <typename T, int R, int NT, bool HASX>
 __global__ void __launch_bounds__(NT) k_rel_ema(RelEmaArgs a) {
   constexpr int N = V16<T>::N;
   constexpr int RP = R + N;
@@ -976,16 +951,18 @@ __global__ void __launch_bounds__(NT) k_rel_ema(RelEmaArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int jj = blockIdx.y;
   T *la = (T *)smem;
-  T *lb = la + (size_t)RP * a.wa;
+  T *lb = la + (size_t)RP * (HASX ? a.wa : 0);
   const T *X = (const T *)a.X + jj * a.xplane;
   const T *Y = (const T *)a.Y + jj * a.yplane;
   T *Ms = (T *)a.M + jj * a.mplane;
   T fx = T(1), fy = T(1);
+  RelAdd add{0, 1.f, 1.f};
   if constexpr (SC) {
-    fx = rel_factor(a.mxx[jj]);
+    if constexpr (HASX) fx = rel_factor(a.mxx[jj]);
     fy = rel_factor(a.mxy[jj]);
-    if (blockIdx.x == 0 && threadIdx.x == 0)
-      a.e_out[jj] = rel_frame(a.ex[jj], a.mxx[jj]) + rel_frame(a.ey[jj], a.mxy[jj]);
+    add.e = (HASX ? rel_frame(a.ex[jj], a.mxx[jj]) : 0) + rel_frame(a.ey[jj], a.mxy[jj]);
+    if (a.accumulate) add = rel_accumulate(a.e_old[jj], a.mx_old[jj], add.e, (HASX && a.mxx[jj] == 0u) || a.mxy[jj] == 0u);
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.e_out[jj] = add.e;
   }
   bool ovf = false;
   float cmax = 0.f;
@@ -1017,7 +994,7 @@ __global__ void __launch_bounds__(NT) k_rel_ema(RelEmaArgs a) {
     const int64_t i0 = t * R;
     const int nrow = (int)min<int64_t>(R, a.n - i0);
     __syncthreads();
-    stage(X, a.ldx, a.wa, i0, nrow, fx, la);
+    if constexpr (HASX) stage(X, a.ldx, a.wa, i0, nrow, fx, la);
     stage(Y, a.ldy, a.wb, i0, nrow, fy, lb);
     __syncthreads();
     for (int C = threadIdx.x; C < a.ws; C += NT) {
@@ -1036,6 +1013,12 @@ __global__ void __launch_bounds__(NT) k_rel_ema(RelEmaArgs a) {
           const V16<T> *yb = (const V16<T> *)(lb + (int)(p[qq] >> 16) * RP);
 #pragma unroll
           for (int v = 0; v < R / N; ++v) {
+            if constexpr (!HASX) {
+              const V16<T> yv = yb[v];
+#pragma unroll
+              for (int e = 0; e < N; ++e) acc[v * N + e] = Arith<T>::add(acc[v * N + e], yv.x[e], ovf);
+              continue;
+            }
             const V16<T> xv = xa[v], yv = yb[v];
             if constexpr (is_u64<T>) {
               // rows past the end hold stale values: they may not raise the flag
@@ -1055,8 +1038,14 @@ __global__ void __launch_bounds__(NT) k_rel_ema(RelEmaArgs a) {
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         if (r < nrow) {
-          Ms[(i0 + r) * a.ldm + oc] = acc[r];
-          if constexpr (SC) cmax = fmaxf(cmax, (float)acc[r]);
+          T *dst = Ms + (i0 + r) * a.ldm + oc;
+          T y = acc[r];
+          if (a.accumulate) {
+            if constexpr (SC) y = *dst * add.so + y * add.sn;
+            else y += *dst;
+          }
+          *dst = y;
+          if constexpr (SC) cmax = fmaxf(cmax, (float)y);
         }
       }
     }
@@ -1186,12 +1175,6 @@ __global__ void __launch_bounds__(WAVE) k_rel_final(RelFinalArgs a) {
 // ===========================================================================
 // launchers
 
-template <typename K, typename A>
-static void rel_go(K kern, const A &a, dim3 grid, int nt, size_t lds, hipStream_t s) {
-  if (lds > 65536) (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  kern<<<grid, nt, lds, s>>>(a);
-}
-
 void launch_rel_init(int *e, unsigned *mx, int ntab, int b, unsigned hist_bits, hipStream_t s) {
   k_rel_init<<<1, BLOCK, 0, s>>>(e, mx, ntab, b, hist_bits);
 }
@@ -1290,15 +1273,19 @@ void launch_rel_combine(int dtype, const RelCombineArgs &a, int b, hipStream_t s
 template <typename T, int NT>
 static int rel_ema_nt(const RelEmaArgs &a, int R, dim3 grid, size_t lds, hipStream_t s) {
   switch (R) {
-    case 4: rel_go(k_rel_ema<T, 4, NT>, a, grid, NT, lds, s); return 0;
-    case 8: rel_go(k_rel_ema<T, 8, NT>, a, grid, NT, lds, s); return 0;
-    case 16: rel_go(k_rel_ema<T, 16, NT>, a, grid, NT, lds, s); return 0;
+    case 4: rel_go(k_rel_ema<T, 4, NT, true>, a, grid, NT, lds, s); return 0;
+    case 8: rel_go(k_rel_ema<T, 8, NT, true>, a, grid, NT, lds, s); return 0;
+    case 16:
+      if (a.X) rel_go(k_rel_ema<T, 16, NT, true>, a, grid, NT, lds, s);
+      else rel_go(k_rel_ema<T, 16, NT, false>, a, grid, NT, lds, s);
+      return 0;
     default: return -1;
   }
 }
 
 template <typename T>
 static int rel_ema_t(const RelEmaArgs &a, int R, int nt, dim3 grid, size_t lds, hipStream_t s) {
+  if (!a.X && R != 16) return -1;
   if (nt == 512) return rel_ema_nt<T, 512>(a, R, grid, lds, s);
   if (nt == 256) return rel_ema_nt<T, 256>(a, R, grid, lds, s);
   if (nt == 128) return rel_ema_nt<T, 128>(a, R, grid, lds, s);

@@ -280,6 +280,8 @@ struct sg2v_graph {
   int32_t n_seg = 0, n_rlong = 0;
   int64_t n_rslots = 0;
   int32_t *rlong_row = nullptr, *rlong_slot0 = nullptr, *rlong_nslot = nullptr;
+  uint32_t *rev = nullptr;  // reverse entry of each entry (adjoint), built on first use
+  int rev_state = 0;        // 0: not built, 1: built, -1: entries without a unique reverse
   std::map<int, UnitTable> units;  // by G (lanes per neighbour row segment)
   uint16_t *tsplit = nullptr;      // [n_tasks][kXsplit + 1] neighbour-range split offsets
   int64_t *xbounds = nullptr;      // device, kXsplit + 1 range starts (renumbered graphs), or null
@@ -1161,7 +1163,9 @@ int64_t rel_ld(int64_t w, int es) {
   return p / es;
 }
 
-void build_rel(const Plan &P, const sg2v_graph *g, int b, int dt, RelPass &rp) {
+// keep: tables (node, 0: M / 1: B) kept to the end of the pass.
+void build_rel(const Plan &P, const sg2v_graph *g, int b, int dt, RelPass &rp,
+               const std::vector<std::pair<int, int>> &keep = {}) {
   const int es = esize_of(dt);
   const size_t nn = P.nodes.size();
   rp.steps.clear();
@@ -1197,6 +1201,10 @@ void build_rel(const Plan &P, const sg2v_graph *g, int b, int dt, RelPass &rp) {
       touch(rp.B[nd.passive], x);
       if (st.kind == S_EMA_GENERAL) touch(rp.M[st.node], x);
     }
+  }
+  for (auto &kp : keep) {
+    Tab &t = (kp.second == 0 ? Mtab(kp.first) : rp.B[kp.first]).t;
+    if (t.last >= 0) t.last = (int)rp.steps.size();
   }
   std::vector<Tab *> all;
   rp.ntab = 0;
@@ -2280,6 +2288,24 @@ sg2v_status rel_spmm(Ctx &x, int node) {
   return SG2V_OK;
 }
 
+sg2v_status rel_ema_launch(Ctx &x, const RelEmaArgs &a) {
+  const int Nv = 16 / x.es;
+  auto lds_for = [&](int R) { return (size_t)(a.wa + a.wb) * (R + Nv) * x.es; };
+  int R = 16;
+  while (R > 4 && lds_for(R) > kRelLds) R /= 2;
+  const size_t lds = lds_for(R);
+  // wide outputs: 512 threads share each staged tile; narrow ones 128
+  const int nt = a.ws >= 4 * 512 ? 512 : a.ws <= 256 ? 128 : 256;
+  const int64_t ntiles = (x.g->n + R - 1) / R;
+  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>((int64_t)(160 * 1024 / lds), 8 * 256 / nt));
+  const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(ntiles, (int64_t)x.cu_count * per_cu));
+  if (launch_rel_ema(x.dt, a, R, nt, dim3((unsigned)blocks, (unsigned)x.b), lds, x.s)) {
+    set_error("sg2v_count: no vertex-relative eMA variant for R=%d", R);
+    return SG2V_EINVAL;
+  }
+  return SG2V_OK;
+}
+
 sg2v_status rel_ema(Ctx &x, int node) {
   const Node &nd = x.P->nodes[node];
   auto Mtab = [&](int s) -> RelTab & { return x.rp.m_alias[s] >= 0 ? x.rp.B[x.rp.m_alias[s]] : x.rp.M[s]; };
@@ -2312,23 +2338,9 @@ sg2v_status rel_ema(Ctx &x, int node) {
   a.e_out = O.t.e;
   a.mx_out = O.t.mx;
   a.ovf = x.ovf;
-  const int Nv = 16 / x.es;
-  auto lds_for = [&](int R) { return (size_t)(a.wa + a.wb) * (R + Nv) * x.es; };
-  int R = 16;
-  while (R > 4 && lds_for(R) > kRelLds) R /= 2;
-  const size_t lds = lds_for(R);
-  // wide outputs: 512 threads share each staged tile; narrow ones 128
-  const int nt = a.ws >= 4 * 512 ? 512 : a.ws <= 256 ? 128 : 256;
-  const int64_t ntiles = (x.g->n + R - 1) / R;
-  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>((int64_t)(160 * 1024 / lds), 8 * 256 / nt));
-  const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(ntiles, (int64_t)x.cu_count * per_cu));
   ProfScope ps(SG2V_K_EMA_GENERAL, (double)x.g->n * x.b * (double)(a.wa + a.wb + a.ws) * x.es,
                (double)x.g->n * x.b * (double)a.ws * a.np, x.s);
-  if (launch_rel_ema(x.dt, a, R, nt, dim3((unsigned)blocks, (unsigned)x.b), lds, x.s)) {
-    set_error("sg2v_count: no vertex-relative eMA variant for R=%d", R);
-    return SG2V_EINVAL;
-  }
-  return SG2V_OK;
+  return rel_ema_launch(x, a);
 }
 
 sg2v_status rel_root(Ctx &x, int node, void *result, int *Eout) {
@@ -2386,7 +2398,8 @@ sg2v_status rel_root(Ctx &x, int node, void *result, int *Eout) {
   return SG2V_OK;
 }
 
-sg2v_status run_rel(Ctx &x, void *result, int *Eout) {
+// the steps of the pass, or those before step `stop`
+sg2v_status run_rel(Ctx &x, void *result, int *Eout, int stop = INT_MAX) {
   if (x.dt == DT_F32) {
     const float mw = (float)std::max(1.0, x.g->max_wdeg);
     unsigned bits;
@@ -2394,7 +2407,8 @@ sg2v_status run_rel(Ctx &x, void *result, int *Eout) {
     launch_rel_init((int *)x.ws->small.p, (unsigned *)x.ws->small.p + (int64_t)x.rp.ntab * x.b, x.rp.ntab, x.b,
                     bits, x.s);
   }
-  for (const Step &st : x.rp.steps) {
+  for (int q = 0; q < std::min((int)x.rp.steps.size(), stop); ++q) {
+    const Step &st = x.rp.steps[q];
     switch (st.kind) {
       case S_HIST: ST_TRY(rel_hist(x, st.node)); break;
       case S_SPMM: ST_TRY(rel_spmm(x, st.node)); break;
@@ -3398,6 +3412,325 @@ bool keep_all_fits(const Plan &P, const sg2v_graph *g, int dt, int G, const Pass
   return (double)pp.arena <= budget;
 }
 
+// Reverse entries of the graph, built on first use; false where an entry has no
+// unique one.
+sg2v_status graph_rev(sg2v_graph *g, int *flag, hipStream_t s, bool *ok) {
+  if (g->rev_state == 0) {
+    g->rev_state = -1;
+    void *p = nullptr;
+    if (g->nnz >= ((int64_t)1 << 31) || hipMalloc(&p, std::max<int64_t>(g->nnz, 1) * 4) != hipSuccess) {
+      (void)hipGetLastError();
+    } else {
+      g->allocs.push_back(p);
+      g->rev = (uint32_t *)p;
+      RelRevArgs a{};
+      a.row_ptr = g->row_ptr;
+      a.col_idx = g->col_idx;
+      a.n = g->n;
+      a.nnz = g->nnz;
+      a.rev = g->rev;
+      a.bad = flag;
+      int bad = 0;
+      launch_fill_u32((unsigned *)flag, 1, 0u, s);
+      launch_rel_rev(a, s);
+      HIP_TRY(hipMemcpyAsync(&bad, flag, 4, hipMemcpyDeviceToHost, s));
+      HIP_TRY(hipStreamSynchronize(s));
+      if (!bad) g->rev_state = 1;
+    }
+  }
+  *ok = g->rev_state == 1;
+  return SG2V_OK;
+}
+
+sg2v_status plan_back(const Plan &P, int device, hipStream_t s, Plan::DeviceTables **out) {
+  std::lock_guard<std::mutex> lk(P.mu);
+  *out = nullptr;
+  for (auto &d : P.dev)
+    if (d.device == device) *out = &d;
+  if (!*out) return SG2V_EINVAL;
+  Plan::DeviceTables &D = **out;
+  if (!D.back_map.empty()) return SG2V_OK;
+  const size_t nn = P.nodes.size();
+  for (auto *v : {&D.back_map, &D.back_px, &D.back_py}) v->assign(nn, nullptr);
+  for (size_t q = 0; q < nn; ++q) {
+    const Node &nd = P.nodes[q];
+    if (nd.size == 1) continue;
+    if (nd.n_passive_uses > 0) ST_TRY(upload(rel_map_back(P.k, nd.size).map, &D.back_map[q], s));
+    const int ma = P.nodes[nd.active].size;
+    if (ma == 1) continue;
+    ST_TRY(upload(rel_pairs_back(P.k, nd.size, ma, true), &D.back_px[q], s));
+    ST_TRY(upload(rel_pairs_back(P.k, nd.size, ma, false), &D.back_py[q], s));
+  }
+  HIP_TRY(hipStreamSynchronize(s));
+  return SG2V_OK;
+}
+
+// Adjoint in vertex-relative tables.  One adjoint table per aggregation and per
+// multiply-add (a split with a one-vertex active child shares its aggregation's,
+// as in the forward pass), so an aggregation's uses are summed before its
+// neighbours are visited once.  The steps of the forward pass are taken in
+// reverse with the root's derivative 1; the weight of a colouring and, in FP32S,
+// the tables' exponents meet in the scale of the per-entry sums.  FP32S adjoint
+// tables keep one exponent and largest mantissa each on the device, a new pair
+// for every contribution.  done: false when the absolute tables have to do it.
+sg2v_status rel_grad(const sg2v_plan *plan, sg2v_graph *g, const sg2v_colorings *c, sg2v_mode mode,
+                     const double *grad_colorful, double *grad_w, hipStream_t s, bool *done) {
+  const Plan &P = plan->p;
+  const int dt = dtype_of(mode), es = esize_of(dt), k = P.k;
+  const sg2v_tuning_t tu = tuning();
+  *done = false;
+  Ctx x;
+  // device properties, plan tables and the shared small buffers
+  PassOpts none;
+  if (!rel_wanted(tu) || !rel_grad_ok(P, es, kRelLds)) return SG2V_OK;
+  ST_TRY(prepare(x, plan, g, c, mode, 1, s, none));
+  if (!x.rel || x.lds_max < kRelLds) return SG2V_OK;
+  bool ok = false;
+  ST_TRY(graph_rev(g, x.ovf, s, &ok));
+  if (!ok) return SG2V_OK;
+  Workspace &ws = *x.ws;
+  const size_t nn = P.nodes.size();
+  std::vector<std::pair<int, int>> every;
+  for (size_t q = 0; q < nn; ++q) {
+    if (P.nodes[q].size > 1 && P.root_index[q] < 0) every.push_back({(int)q, 0});
+    if (P.nodes[q].n_passive_uses > 0) every.push_back({(int)q, 1});
+  }
+  build_rel(P, g, 1, dt, x.rp, every);
+  // adjoint tables
+  struct Adj {
+    char *p = nullptr;
+    int64_t off = -1, ld = 0;
+    int ver = -1;  // exponent and maximum of its contents, -1: nothing yet
+  };
+  std::vector<Adj> Mb(nn), Bb(nn);
+  int64_t top = 0, maxld = 1;
+  for (size_t q = 0; q < nn; ++q)
+    for (int kind = 0; kind < 2; ++kind) {
+      RelTab &t = kind == 0 ? x.rp.M[q] : x.rp.B[q];
+      if (t.t.last < 0) continue;
+      Adj &a = kind == 0 ? Mb[q] : Bb[q];
+      a.ld = t.t.ld;
+      a.off = top;
+      maxld = std::max(maxld, a.ld);
+      top += round_up(g->n * a.ld * es, 256);
+    }
+  const int64_t part_off = top;
+  top += round_up(std::max<int64_t>(g->n_rslots, 1) * maxld * es, 256);
+  const int nslots = 2 * (int)x.rp.steps.size() + 8;
+  const int64_t small_off = top;
+  top += round_up((int64_t)nslots * 8, 256);
+  bool keep_all = !(tu.flags & SG2V_TUNE_GRAD_RECOMPUTE);
+  if (keep_all) {
+    size_t fr = 0, tot = 0;
+    (void)hipMemGetInfo(&fr, &tot);
+    const double budget = tu.budget_bytes > 0 ? (double)tu.budget_bytes : 0.5 * (double)fr;
+    keep_all = (double)x.rp.arena <= budget;
+  }
+  Plan::DeviceTables *D = nullptr;
+  ST_TRY(plan_back(P, g->device, s, &D));
+  ST_TRY(ws.grad.ensure(top));
+  ST_TRY(ws.result.ensure((size_t)c->count * 12 + 64));
+  char *gb = (char *)ws.grad.p;
+  for (size_t q = 0; q < nn; ++q) {
+    Mb[q].p = gb + Mb[q].off;
+    Bb[q].p = gb + Bb[q].off;
+  }
+  int *ev = (int *)(gb + small_off);
+  unsigned *mv = (unsigned *)ev + nslots;
+  void *res = ws.result.p;
+  int *Eres = (int *)((char *)res + (size_t)c->count * 8);
+  const std::vector<Step> steps = x.rp.steps;
+  const int ns = (int)steps.size();
+  const bool sc = dt == DT_F32;
+  auto forward = [&](const std::vector<std::pair<int, int>> &keep, int stop) -> sg2v_status {
+    build_rel(P, g, 1, dt, x.rp, keep);
+    ST_TRY(ws.arena.ensure(x.rp.arena));
+    ST_TRY(ws.small.ensure(x.rp.small_bytes));
+    ST_TRY(bind_tables(x));
+    return run_rel(x, res, Eres, stop);
+  };
+  auto Mtab = [&](int q) -> RelTab & { return x.rp.m_alias[q] >= 0 ? x.rp.B[x.rp.m_alias[q]] : x.rp.M[q]; };
+  auto Madj = [&](int q) -> Adj & { return x.rp.m_alias[q] >= 0 ? Bb[x.rp.m_alias[q]] : Mb[q]; };
+
+  for (int j = 0; j < c->count; ++j) {
+    if (grad_colorful[j] == 0.0) continue;
+    x.j0 = j;
+    launch_fill_u32((unsigned *)ev, 2 * nslots, 0u, s);
+    for (size_t q = 0; q < nn; ++q) Mb[q].ver = Bb[q].ver = -1;
+    int slot = 0;
+    if (keep_all) ST_TRY(forward(every, ns - 1));
+    // adds to `to` the products of `from` (null: ones) and `with` over the pairs
+    auto product = [&](Adj &to, int64_t wout, const Adj *from, int64_t wfrom, RelTab &with, void *pairs, int64_t np) -> sg2v_status {
+      RelEmaArgs a{};
+      if (from) {
+        a.X = from->p;
+        a.ldx = from->ld;
+        a.wa = (int32_t)wfrom;
+        a.ex = ev + from->ver;
+        a.mxx = mv + from->ver;
+      }
+      a.Y = with.t.p;
+      a.ldy = with.t.ld;
+      a.wb = (int32_t)with.t.cols;
+      a.ey = with.t.e;
+      a.mxy = with.t.mx;
+      a.M = to.p;
+      a.ldm = to.ld;
+      a.ws = (int32_t)wout;
+      a.np = (int32_t)np;
+      a.pairs = (const uint32_t *)pairs;
+      a.n = g->n;
+      a.ovf = x.ovf;
+      a.accumulate = to.ver >= 0;
+      a.e_old = ev + std::max(to.ver, 0);
+      a.mx_old = mv + std::max(to.ver, 0);
+      a.e_out = ev + slot;
+      a.mx_out = mv + slot;
+      to.ver = slot++;
+      ProfScope ps(SG2V_K_EMA_GENERAL, (double)g->n * (a.wa + a.wb + a.ws) * es, (double)g->n * wout * np, s);
+      return rel_ema_launch(x, a);
+    };
+    for (int q = ns - 1; q >= 0; --q) {
+      const Step st = steps[q];
+      const Node &nd = P.nodes[st.node];
+      if (!keep_all) {
+        std::vector<std::pair<int, int>> keep;
+        if (st.kind == S_SPMM) keep.push_back({st.node, 0});
+        if (st.kind == S_EMA_GENERAL || st.kind == S_ROOT) {
+          if (P.nodes[nd.active].size > 1) keep.push_back({nd.active, 0});
+          keep.push_back({nd.passive, 1});
+        }
+        if (!keep.empty()) ST_TRY(forward(keep, q));
+      }
+      if (st.kind == S_ROOT || st.kind == S_EMA_GENERAL) {
+        const int ma = P.nodes[nd.active].size, mp = P.nodes[nd.passive].size;
+        const int64_t wa = binom(k - 1, ma - 1), wb = binom(k - 1, mp), wsz = binom(k - 1, nd.size - 1);
+        Adj *from = st.kind == S_ROOT ? nullptr : &Mb[st.node];
+        if (ma == 1) {  // root over one vertex: the sum of its aggregation
+          launch_fill_value(dt, Bb[nd.passive].p, g->n * Bb[nd.passive].ld, 1.0, s);
+          launch_fill_u32(mv + slot, 1, 0x3F800000u, s);
+          Bb[nd.passive].ver = slot++;
+        } else {
+          if (from && from->ver < 0) continue;
+          ST_TRY(product(Madj(nd.active), wa, from, wsz, x.rp.B[nd.passive], D->back_px[st.node],
+                         binom(k - 1 - (ma - 1), mp)));
+          ST_TRY(product(Bb[nd.passive], wb, from, wsz, Mtab(nd.active), D->back_py[st.node],
+                         binom(k - 1 - mp, ma - 1)));
+        }
+      } else if (st.kind == S_HIST) {
+        Adj &H = Bb[st.node];
+        if (H.ver < 0) continue;
+        RelHistBackArgs a{};
+        a.row_ptr = g->row_ptr;
+        a.col_idx = g->col_idx;
+        a.col = c->d + (int64_t)j * g->n;
+        a.n = g->n;
+        a.Hb = H.p;
+        a.ldh = H.ld;
+        a.grad = grad_w;
+        a.scale = grad_colorful[j];
+        a.e = ev + H.ver;
+        a.mx = mv + H.ver;
+        a.R = rel_rows(x, 32, 1);
+        a.tlong = (int32_t)kRelLong;
+        a.seg_row = g->seg_row;
+        a.seg_len = g->seg_len;
+        a.seg_beg = g->seg_beg;
+        a.n_seg = g->n_seg;
+        const int64_t groups = std::max<int64_t>((g->n + a.R - 1) / a.R, 4 * (int64_t)a.n_seg);
+        ProfScope ps(SG2V_K_HIST, (double)g->nnz * 21.0, (double)g->nnz, s);
+        launch_rel_hist_back(dt, a, dim3(rel_blocks(x, groups, 1)), s);
+      } else if (st.kind == S_SPMM) {
+        Adj &X = Bb[st.node], &O = Madj(st.node);
+        if (X.ver < 0) continue;
+        RelTab &M = Mtab(st.node);
+        const int m = nd.size, N = 16 / es;
+        RelBackArgs a{};
+        a.row_ptr = g->row_ptr;
+        a.col_idx = g->col_idx;
+        a.w = g->w;
+        a.col = c->d + (int64_t)j * g->n;
+        a.n = g->n;
+        a.k = k;
+        a.X = X.p;
+        a.ldx = X.ld;
+        a.M = M.t.p;
+        a.ldm = M.t.ld;
+        a.O = O.p;
+        a.ldo = O.ld;
+        a.partial = gb + part_off;
+        a.cw = (int32_t)round_up(binom(k, m), 4);
+        a.wout = (int32_t)binom(k - 1, m - 1);
+        a.wout4 = (int32_t)round_up(a.wout, 4);
+        const int64_t win = binom(k - 1, m);
+        a.sr = (int32_t)round_up(win, 4) + 4;
+        a.map = (const uint16_t *)D->back_map[st.node];
+        a.olist = a.map + (size_t)k * a.cw;
+        a.lp = (int32_t)((win + N - 1) / N);
+        if (a.lp > 64) {
+          set_error("sg2v_count_grad: rows of %d columns have no vertex-relative adjoint", (int)win);
+          return SG2V_EINVAL;
+        }
+        a.streams = 64 / a.lp;
+        a.R = rel_rows(x, 32, 1);
+        a.tlong = (int32_t)kRelLong;
+        a.seg_row = g->seg_row;
+        a.seg_len = g->seg_len;
+        a.seg_slot = g->seg_slot;
+        a.seg_beg = g->seg_beg;
+        a.n_seg = g->n_seg;
+        a.rev = g->rev;
+        a.grad = grad_w;
+        a.scale = grad_colorful[j];
+        a.ex = ev + X.ver;
+        a.mxx = mv + X.ver;
+        a.em = M.t.e;
+        a.mxm = M.t.mx;
+        a.accumulate = O.ver >= 0;
+        a.e_old = ev + std::max(O.ver, 0);
+        a.mx_old = mv + std::max(O.ver, 0);
+        a.e_out = ev + slot;
+        a.mx_out = mv + slot;
+        const size_t lds = (size_t)round_up((int64_t)k * (a.cw + a.wout4) * 2, 16) +
+                           (size_t)4 * std::max(4 * a.streams * a.sr, (int)a.wout) * es;
+        {
+          const double n = (double)g->n, nz = (double)g->nnz;
+          ProfScope ps(SG2V_K_SPMM, n * (win + 2.0 * a.wout) * es + nz * (25.0 + (g->w ? 4.0 : 0.0)), 2.0 * nz * a.wout, s);
+          const int64_t groups = std::max<int64_t>((g->n + a.R - 1) / a.R, 4 * (int64_t)a.n_seg);
+          if (launch_rel_back(dt, a, dim3(rel_blocks(x, groups, 1)), lds, s)) {
+            set_error("sg2v_count_grad: no vertex-relative adjoint of %d columns", a.wout);
+            return SG2V_EINVAL;
+          }
+        }
+        if (g->n_rlong > 0) {
+          RelBackCombineArgs cb{};
+          cb.partial = a.partial;
+          cb.O = O.p;
+          cb.ldo = O.ld;
+          cb.w = a.wout;
+          cb.long_row = g->rlong_row;
+          cb.long_slot0 = g->rlong_slot0;
+          cb.long_nslot = g->rlong_nslot;
+          cb.n_long = g->n_rlong;
+          cb.accumulate = a.accumulate;
+          cb.ex = a.ex;
+          cb.mxx = a.mxx;
+          cb.e_old = a.e_old;
+          cb.mx_old = a.mx_old;
+          cb.mx_out = a.mx_out;
+          launch_rel_back_combine(dt, cb, s);
+        }
+        O.ver = slot++;
+      }
+      HIP_TRY(hipGetLastError());
+    }
+  }
+  (void)sc;
+  HIP_TRY(hipStreamSynchronize(s));
+  *done = true;
+  return SG2V_OK;
+}
+
 sg2v_status count_grad_fp32s(const sg2v_plan *plan, sg2v_graph *gg, const sg2v_colorings *c,
                              const double *grad_colorful, double *grad_w, hipStream_t s) {
   const Plan &P = plan->p;
@@ -3713,6 +4046,11 @@ sg2v_status count_grad_stored(const sg2v_plan *plan, const sg2v_graph *g, const 
     HIP_TRY(hipStreamSynchronize(s));
     return SG2V_OK;
   }
+  {
+    bool done = false;
+    ST_TRY(rel_grad(plan, gg, c, mode, grad_colorful, (double *)grad_w, s, &done));
+    if (done) return SG2V_OK;
+  }
   if (mode == SG2V_FP32S) return count_grad_fp32s(plan, gg, c, grad_colorful, (double *)grad_w, s);
   const size_t nn = P.nodes.size();
   int64_t widest = 1;
@@ -3980,7 +4318,7 @@ extern "C" void sg2v_plan_destroy(sg2v_plan *plan) {
     for (void *q : d.rel_pairs) (void)hipFree(q);
     for (void *q : d.rel_map) (void)hipFree(q);
     for (void *q : d.rel_root) (void)hipFree(q);
-    for (auto *v : {&d.rel_mpos, &d.rel_bpos, &d.rel_tab, &d.rel_hdr, &d.rel_info})
+    for (auto *v : {&d.rel_mpos, &d.rel_bpos, &d.rel_tab, &d.rel_hdr, &d.rel_info, &d.back_map, &d.back_px, &d.back_py})
       for (void *q : *v) (void)hipFree(q);
     (void)hipSetDevice(cur);
   }

@@ -118,3 +118,44 @@ def test_relative_overflow_flag():
         ref = [O.count(G, par, k, O.colors(n, k, 1, j), mode=O.U64) for j in range(2)]
         assert [int(x) for x in r["colorful_u64"]] == [x[1] for x in ref]
         assert r["overflow"] == any(x[2] for x in ref)
+
+
+@pytest.mark.parametrize("n", [5, 33, 1500])
+@pytest.mark.parametrize("par,k", [([-1, 0], 3), ([-1, 0, 1], 3), ([-1, 0, 0, 0], 5), (gg.PATH5, 7),
+                                   (gg.BINTREE7, 7), (gg.CATERPILLAR10, 10), (gg.PATH8, 9)])
+def test_relative_adjoint_against_oracle_and_absolute(par, k, n):
+    """Per-entry derivatives: rows of no entries, long and segmented rows, one and
+    two columns per lane, several colourings of either sign and of weight zero."""
+    G = hubs(n, 7 * n + k, True)
+    g = sg.Graph.from_csr(G)
+    plan = sg.Plan(par, k)
+    gcol = [1.0, 0.0, -0.75]
+    c = sg.Colorings(g, k, 4, 3)
+    ref = np.zeros(G.nnz)
+    for j, a in enumerate(gcol):
+        if a:
+            ref += a * O.grad(G, par, k, O.colors(n, k, 4, j))[1]
+    top = np.abs(ref).max()
+    for mode, tol in (("fp64", 1e-10), ("fp32s", 2e-5)):
+        print("adjoint", n, par, k, mode, flush=True)
+        got = sg.count_grad(plan, g, c, gcol, mode).cpu().numpy()
+        with sg.tuned(flags=sg.TUNE_NO_COLOR_SKIP):
+            full = sg.count_grad(plan, g, c, gcol, mode).cpu().numpy()
+        np.testing.assert_allclose(got, ref, rtol=tol, atol=tol * top)
+        np.testing.assert_allclose(got, full, rtol=2 * tol, atol=2 * tol * top)
+
+
+def test_adjoint_of_entries_without_reverse():
+    """A row that repeats or lacks a reverse entry has the absolute adjoint: the
+    derivative by every entry as it stands."""
+    G = gg.from_edge_list(6, [(0, 1), (1, 2), (2, 3), (3, 4), (4, 5), (0, 5)], np.linspace(0.5, 1.5, 6))
+    drop = int(G.row_ptr[3])  # first entry of vertex 3
+    rp = G.row_ptr.copy()
+    rp[4:] -= 1
+    g = sg.Graph(6, rp, np.delete(G.col_idx, drop), np.delete(G.w, drop))
+    plan = sg.Plan(gg.PATH5, 5)
+    c = sg.Colorings(g, 5, 3, 2)
+    a = sg.count_grad(plan, g, c, [1.0, 1.0], "fp64").cpu().numpy()
+    with sg.tuned(flags=sg.TUNE_NO_COLOR_SKIP):
+        b = sg.count_grad(plan, g, c, [1.0, 1.0], "fp64").cpu().numpy()
+    np.testing.assert_array_equal(a, b)
