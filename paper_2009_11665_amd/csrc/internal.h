@@ -107,6 +107,7 @@ struct Plan {
   // device copies of the tables, uploaded on first use per device
   struct DeviceTables {
     int device = -1;
+    std::vector<void *> owned;        // the allocations that hold the tables below
     std::vector<void *> pairs, drop;  // per node
     std::vector<void *> tr_a, tr_p, add;
     std::vector<void *> cpr;  // colour-restricted tables, one block per node

@@ -532,6 +532,8 @@ struct RelHistBackArgs {
   int32_t n_seg;
 };
 
+// largest sum of |w| over a row (NaN sums left out)
+void launch_max_wdeg(const int64_t *row_ptr, const float *w, int64_t n, double *out, hipStream_t s);
 void launch_rel_rev(const RelRevArgs &a, hipStream_t s);
 int launch_rel_back(int dtype, const RelBackArgs &a, dim3 grid, size_t lds, hipStream_t s);
 void launch_rel_back_combine(int dtype, const RelBackCombineArgs &a, hipStream_t s);

@@ -354,6 +354,29 @@ __global__ void __launch_bounds__(BLOCK) k_rel_hist_back(RelHistBackArgs a) {
   }
 }
 
+// Largest weighted degree: a wave per row, lanes over its entries.  Sums of
+// absolute values order as their bits do.
+__global__ void k_zero_f64(double *out) { *out = 0.0; }
+__global__ void __launch_bounds__(BLOCK) k_max_wdeg(const int64_t *row_ptr, const float *w, int64_t n, double *out) {
+  const int lane = threadIdx.x & (WAVE - 1);
+  const int64_t nwaves = (int64_t)gridDim.x * WAVES_PER_BLOCK;
+  double best = 0.0;
+  for (int64_t i = ((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE; i < n; i += nwaves) {
+    const int64_t b = row_ptr[i], e = row_ptr[i + 1];
+    double s = 0.0;
+    for (int64_t q = b + lane; q < e; q += WAVE) s += fabs((double)w[q]);
+    for (int off = 1; off < WAVE; off <<= 1) s += shfl_xor(s, off);
+    if (s > best) best = s;
+  }
+  if (lane == 0 && best > 0.0)
+    atomicMax((unsigned long long *)out, __builtin_bit_cast(unsigned long long, best));
+}
+
+void launch_max_wdeg(const int64_t *row_ptr, const float *w, int64_t n, double *out, hipStream_t s) {
+  k_zero_f64<<<1, 1, 0, s>>>(out);
+  k_max_wdeg<<<(unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 3) / 4, 4096)), BLOCK, 0, s>>>(row_ptr, w, n, out);
+}
+
 void launch_rel_rev(const RelRevArgs &a, hipStream_t s) {
   const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>((a.nnz + BLOCK - 1) / BLOCK, 16384));
   k_rel_rev<<<g, BLOCK, 0, s>>>(a);
