@@ -223,30 +223,37 @@ __global__ void __launch_bounds__(BLOCK) k_rel_spmm(RelSpmmArgs a) {
       pabs[u] = pok[u] ? lout[r * a.wout4 + p0 + u * WAVE] : 0;
     }
   };
-  // entries [pos, stop) of the stage, whose first entry is t0
-  auto add_staged = [&](int t0, int pos, int stop, int inf, float wt) {
-    for (int i = pos; i < stop; i += UA * SW) {
+  T *const ls = (T *)smem;  // the stage through the start of the LDS: one address add per element
+  const int stg_off = __builtin_amdgcn_readfirstlane((int)(stg - ls));
+  // Entries [pos, stop) of the stage, whose first entry is t0; c8: map offset of
+  // each entry's colour, by lane.  UA * SW entries at a time, their map reads and
+  // then their stage reads in flight together; only the last group has bounds
+  // (with bounds in every group: weighted fp64 k = 10 1.95 ms, now 1.87).
+  auto add_staged = [&](int t0, int pos, int stop, int c8, float wt) {
+    auto some = [&](int i, auto full) {
+      constexpr bool FULL = decltype(full)::value;
       T x[UA][NP];
       int o[UA][NP];
 #pragma unroll
       for (int u = 0; u < UA; ++u) {
-        const int idx = min(SPLIT ? i + u * SW + grp : i + u, stop - 1);
-        const int c = CW * (SPLIT ? shfl_i32(inf, idx) : __builtin_amdgcn_readlane(inf, idx));
+        const int at = SPLIT ? i + u * SW + grp : i + u, idx = FULL ? at : min(at, stop - 1);
+        const int c = SPLIT ? shfl_i32(c8, idx) : __builtin_amdgcn_readlane(c8, idx);
 #pragma unroll
         for (int v = 0; v < NP; ++v) o[u][v] = lmap[c + pabs[v]];
       }
 #pragma unroll
       for (int u = 0; u < UA; ++u) {
-        const int idx = min(SPLIT ? i + u * SW + grp : i + u, stop - 1);
+        const int at = SPLIT ? i + u * SW + grp : i + u, idx = FULL ? at : min(at, stop - 1);
+        const int so = stg_off + (idx - t0) * SR;
 #pragma unroll
-        for (int v = 0; v < NP; ++v) x[u][v] = stg[(idx - t0) * SR + o[u][v]];
+        for (int v = 0; v < NP; ++v) x[u][v] = ls[so + o[u][v]];
       }
 #pragma unroll
       for (int u = 0; u < UA; ++u) {
         const int idx = SPLIT ? i + u * SW + grp : i + u;
         float w = 1.f;  // every lane is active here
         if constexpr (WEIGHTED) w = SPLIT ? shfl(wt, idx) : __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wt), idx & (WAVE - 1)));
-        if (idx < stop) {
+        if (FULL || idx < stop) {
           if constexpr (WEIGHTED) {
 #pragma unroll
             for (int v = 0; v < NP; ++v) acc[v] = A::fma((T)w, x[u][v], acc[v], ovf);
@@ -263,7 +270,10 @@ __global__ void __launch_bounds__(BLOCK) k_rel_spmm(RelSpmmArgs a) {
           }
         }
       }
-    }
+    };
+    int i = pos;
+    for (; i + UA * SW <= stop; i += UA * SW) some(i, std::true_type());
+    if (i < stop) some(i, std::false_type());
   };
   auto sum_groups = [&]() {
     if constexpr (SPLIT) {
@@ -321,7 +331,7 @@ __global__ void __launch_bounds__(BLOCK) k_rel_spmm(RelSpmmArgs a) {
         }
       };
       issue(0);
-      const int inf = col[my_j];
+      const int my_c = col[my_j];
       fetch(base + stride);
       for (int t0 = 0; t0 < nb; t0 += E) {
         wave_lds_fence();  // the previous batch has been read
@@ -332,6 +342,7 @@ __global__ void __launch_bounds__(BLOCK) k_rel_spmm(RelSpmmArgs a) {
         }
         issue(t0 + E);
         wave_lds_fence();
+        const int c8 = my_c * CW;
         int pos = t0;
         const int lim = min(t0 + E, nb);
         while (pos < lim) {
@@ -342,7 +353,7 @@ __global__ void __launch_bounds__(BLOCK) k_rel_spmm(RelSpmmArgs a) {
               open_row(__builtin_amdgcn_readlane(rcol, cur));
             }
           const int stop = seg || cur == r1 - 1 ? lim : min(lim, __builtin_amdgcn_readlane(ro, cur + 1) - base);
-          add_staged(t0, pos, stop, inf, my_w);
+          add_staged(t0, pos, stop, c8, my_w);
           pos = stop;
         }
       }

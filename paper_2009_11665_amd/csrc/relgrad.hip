@@ -112,28 +112,35 @@ __global__ void __launch_bounds__(BLOCK) k_rel_back(RelBackArgs a) {
       pabs[u] = pok[u] ? lout[r * a.wout4 + lane + u * WAVE] : 0;
     }
   };
-  // entries [pos, stop) of the stage; dot: their products, lane = entry of the block
-  auto add_staged = [&](int t0, int pos, int stop, int inf, float wt, T &dot) {
-    for (int i = pos; i < stop; i += UA) {
+  T *const ls = (T *)smem;
+  const int stg_off = __builtin_amdgcn_readfirstlane((int)(stg - ls));
+  // Entries [pos, stop) of the stage, whose first entry is t0; c8: map offset of
+  // each entry's colour; dot: their products, lane = entry of the block.  Only
+  // the last group of UA has bounds.
+  auto add_staged = [&](int t0, int pos, int stop, int c8, float wt, T &dot) {
+    auto some = [&](int i, auto full) {
+      constexpr bool FULL = decltype(full)::value;
       T x[UA][NP], d[UA];
       int o[UA][NP];
 #pragma unroll
       for (int u = 0; u < UA; ++u) {
-        const int c = CW * __builtin_amdgcn_readlane(inf, min(i + u, stop - 1));
+        const int c = __builtin_amdgcn_readlane(c8, FULL ? i + u : min(i + u, stop - 1));
 #pragma unroll
         for (int v = 0; v < NP; ++v) o[u][v] = lmap[c + pabs[v]];
       }
 #pragma unroll
-      for (int u = 0; u < UA; ++u)
+      for (int u = 0; u < UA; ++u) {
+        const int so = stg_off + ((FULL ? i + u : min(i + u, stop - 1)) - t0) * SR;
 #pragma unroll
-        for (int v = 0; v < NP; ++v) x[u][v] = stg[(min(i + u, stop - 1) - t0) * SR + o[u][v]];
+        for (int v = 0; v < NP; ++v) x[u][v] = ls[so + o[u][v]];
+      }
 #pragma unroll
       for (int u = 0; u < UA; ++u) {
         d[u] = T(0);
         float w = 1.f;
         if constexpr (WEIGHTED)
           w = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wt), (i + u) & (WAVE - 1)));
-        const bool ok = i + u < stop;
+        const bool ok = FULL || i + u < stop;
 #pragma unroll
         for (int v = 0; v < NP; ++v) {
           d[u] += own[v] * x[u][v];
@@ -149,7 +156,10 @@ __global__ void __launch_bounds__(BLOCK) k_rel_back(RelBackArgs a) {
       const int k4 = lane - i;  // this lane's entry among the four
       const T mine = shfl(r, ((k4 & 1) << 5) | ((k4 & 2) << 3));
       if (k4 >= 0 && k4 < UA && lane < stop) dot = mine;
-    }
+    };
+    int i = pos;
+    for (; i + UA <= stop; i += UA) some(i, std::true_type());
+    if (i < stop) some(i, std::false_type());
   };
   auto walk = [&](int64_t beg, int first, int stride, int cnt, int ro, int r0, int r1, int rcol, int64_t row0, bool seg) {
     int cur = r0;
@@ -199,7 +209,7 @@ __global__ void __launch_bounds__(BLOCK) k_rel_back(RelBackArgs a) {
         }
       };
       issue(0);
-      const int inf = col[my_j];
+      const int my_c = col[my_j];
       const double old = a.grad[my_r];
       T dot = T(0);
       fetch(base + stride);
@@ -212,13 +222,14 @@ __global__ void __launch_bounds__(BLOCK) k_rel_back(RelBackArgs a) {
         }
         issue(t0 + E);
         wave_lds_fence();
+        const int c8 = my_c * CW;
         int pos = t0;
         const int lim = min(t0 + E, nb);
         while (pos < lim) {
           if (!seg)
             while (cur < r1 - 1 && __builtin_amdgcn_readlane(ro, cur + 1) <= base + pos) next();
           const int stop = seg || cur == r1 - 1 ? lim : min(lim, __builtin_amdgcn_readlane(ro, cur + 1) - base);
-          add_staged(t0, pos, stop, inf, my_w, dot);
+          add_staged(t0, pos, stop, c8, my_w, dot);
           pos = stop;
         }
       }
