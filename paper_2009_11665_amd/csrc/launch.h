@@ -422,6 +422,7 @@ struct RelEmaArgs {
   void *M;
   int64_t ldm, mplane;
   int32_t wa, wb, ws, np;
+  int32_t groups;          // thread groups of ws threads, each with its own rows of a tile (1: any ws)
   const uint32_t *pairs;   // [np][ws]: x | y << 16
   const uint16_t *opos;    // column of each output (null: its rank)
   int64_t n;

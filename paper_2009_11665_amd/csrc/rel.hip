@@ -944,9 +944,12 @@ __global__ void __launch_bounds__(BLOCK) k_rel_combine(RelCombineArgs a) {
 // ---------------------------------------------------------------------------
 // Multiply-add of a split whose active child has several vertices:
 //   M_s(i, Q) = sum over the pairs (x, y) of Q of M_a(i, x) B(i, y).
-// A block stages R consecutive rows of both tables in LDS, transposed (R rows
-// plus one 16-byte vector per column, so that lanes on different columns
-// spread over the banks); a thread owns output columns and keeps R sums.  Half
+// A block stages R * groups consecutive rows of both tables in LDS, transposed
+// (the rows plus one 16-byte vector per column, so that lanes on different
+// columns spread over the banks); a thread owns output columns and keeps R sums.
+// Narrow outputs have a thread group for each R rows of the tile: balanced tree
+// of 7 vertices, 16 colourings of 65536 vertices (6 to 20 columns), whole count
+// 0.99 -> 0.72 ms; all trees of 9 vertices 124.7 -> 119.7 ms.  Half
 // the columns of the absolute tables and rows in order: 1.42 -> 0.78 ms on
 // average over the splits of the nine-vertex trees (4M rows of about 60 columns
 // three times, 2.9 GB: 3.7 TB/s).
@@ -957,10 +960,10 @@ __global__ void __launch_bounds__(BLOCK) k_rel_combine(RelCombineArgs a) {
 template <typename T, int R, int NT, bool HASX>
 __global__ void __launch_bounds__(NT) k_rel_ema(RelEmaArgs a) {
   constexpr int N = V16<T>::N;
-  constexpr int RP = R + N;
   constexpr bool SC = sizeof(T) == 4;
   extern __shared__ __align__(16) unsigned char smem[];
   const int jj = blockIdx.y;
+  const int RT = R * a.groups, RP = RT + N;
   T *la = (T *)smem;
   T *lb = la + (size_t)RP * (HASX ? a.wa : 0);
   const T *X = (const T *)a.X + jj * a.xplane;
@@ -977,7 +980,7 @@ __global__ void __launch_bounds__(NT) k_rel_ema(RelEmaArgs a) {
   }
   bool ovf = false;
   float cmax = 0.f;
-  // eight 16-byte loads in flight per thread
+  // four 16-byte loads in flight per thread
   auto stage = [&](const T *src, int64_t ld, int w, int64_t i0, int nrow, T f, T *dst) {
     const int nv = (w + N - 1) / N, total = nrow * nv;
     for (int x0 = threadIdx.x; x0 < total; x0 += 4 * NT) {
@@ -1000,28 +1003,36 @@ __global__ void __launch_bounds__(NT) k_rel_ema(RelEmaArgs a) {
       }
     }
   };
-  const int64_t ntiles = (a.n + R - 1) / R;
+  // this thread's rows of a tile, its first column, and its pairs where they fit
+  const int g = a.groups > 1 ? (int)threadIdx.x / a.ws : 0, rg = g * R;
+  const int C0 = g < a.groups ? (int)threadIdx.x - g * a.ws : a.ws;
+  const bool once = a.np <= 8 && a.ws <= NT;
+  uint32_t p[8];
+  auto fetch_pairs = [&](int q0, int C) {
+#pragma unroll
+    for (int qq = 0; qq < 8; ++qq) p[qq] = a.pairs[(int64_t)min(q0 + qq, a.np - 1) * a.ws + C];
+  };
+  if (once) fetch_pairs(0, min(C0, a.ws - 1));
+  const int64_t ntiles = (a.n + RT - 1) / RT;
   for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-    const int64_t i0 = t * R;
-    const int nrow = (int)min<int64_t>(R, a.n - i0);
+    const int64_t i0 = t * RT;
+    const int nrow = (int)min<int64_t>(RT, a.n - i0);
     __syncthreads();
     if constexpr (HASX) stage(X, a.ldx, a.wa, i0, nrow, fx, la);
     stage(Y, a.ldy, a.wb, i0, nrow, fy, lb);
     __syncthreads();
-    for (int C = threadIdx.x; C < a.ws; C += NT) {
+    for (int C = C0; C < a.ws; C += NT) {
       const int oc = a.opos ? a.opos[C] : C;
       T acc[R];
 #pragma unroll
       for (int r = 0; r < R; ++r) acc[r] = T(0);
       for (int q0 = 0; q0 < a.np; q0 += 8) {
-        uint32_t p[8];
-#pragma unroll
-        for (int qq = 0; qq < 8; ++qq) p[qq] = a.pairs[(int64_t)min(q0 + qq, a.np - 1) * a.ws + C];
+        if (!once) fetch_pairs(q0, C);
 #pragma unroll
         for (int qq = 0; qq < 8; ++qq) {
           if (q0 + qq >= a.np) break;  // uniform
-          const V16<T> *xa = (const V16<T> *)(la + (int)(p[qq] & 0xFFFFu) * RP);
-          const V16<T> *yb = (const V16<T> *)(lb + (int)(p[qq] >> 16) * RP);
+          const V16<T> *xa = (const V16<T> *)(la + (int)(p[qq] & 0xFFFFu) * RP + rg);
+          const V16<T> *yb = (const V16<T> *)(lb + (int)(p[qq] >> 16) * RP + rg);
 #pragma unroll
           for (int v = 0; v < R / N; ++v) {
             if constexpr (!HASX) {
@@ -1037,7 +1048,7 @@ __global__ void __launch_bounds__(NT) k_rel_ema(RelEmaArgs a) {
               for (int e = 0; e < N; ++e) {
                 bool o = false;
                 acc[v * N + e] = Arith<T>::fma(xv.x[e], yv.x[e], acc[v * N + e], o);
-                ovf |= o && v * N + e < nrow;
+                ovf |= o && rg + v * N + e < nrow;
               }
             } else {
 #pragma unroll
@@ -1048,8 +1059,8 @@ __global__ void __launch_bounds__(NT) k_rel_ema(RelEmaArgs a) {
       }
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        if (r < nrow) {
-          T *dst = Ms + (i0 + r) * a.ldm + oc;
+        if (rg + r < nrow) {
+          T *dst = Ms + (i0 + rg + r) * a.ldm + oc;
           T y = acc[r];
           if (a.accumulate) {
             if constexpr (SC) y = *dst * add.so + y * add.sn;

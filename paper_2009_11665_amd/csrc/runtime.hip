@@ -2352,18 +2352,24 @@ sg2v_status rel_spmm(Ctx &x, int node) {
   return SG2V_OK;
 }
 
-sg2v_status rel_ema_launch(Ctx &x, const RelEmaArgs &a) {
+sg2v_status rel_ema_launch(Ctx &x, RelEmaArgs a) {
   const int Nv = 16 / x.es;
-  auto lds_for = [&](int R) { return (size_t)(a.wa + a.wb) * (R + Nv) * x.es; };
   int R = 16;
-  while (R > 4 && lds_for(R) > kRelLds) R /= 2;
-  const size_t lds = lds_for(R);
-  // wide outputs: 512 threads share each staged tile; narrow ones 128
-  const int nt = a.ws >= 4 * 512 ? 512 : a.ws <= 256 ? 128 : 256;
-  const int64_t ntiles = (x.g->n + R - 1) / R;
-  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>((int64_t)(160 * 1024 / lds), 8 * 256 / nt));
+  auto lds = [&]() { return (size_t)(a.wa + a.wb) * (R * a.groups + Nv) * x.es; };
+  // Wide outputs: 512 threads share each staged tile.  Narrow ones: 128 or 256
+  // threads, whichever has the larger share in whole groups of ws threads, and a
+  // group for each R rows of the tile (20 columns: 120 of 128 threads work, not 20).
+  auto used = [&](int nt) { return (double)(nt / a.ws * a.ws) / nt; };
+  const int nt = a.ws >= 4 * 512 ? 512 : a.ws > 256 || used(256) > 1.1 * used(128) ? 256 : 128;
+  a.groups = std::max(1, nt / a.ws);
+  // fewer groups where there would not be four tiles per CU (a call of 2000
+  // vertices is bound by the length of one tile's work), or the tile is too large
+  while (a.groups > 1 && ((x.g->n + R * a.groups - 1) / (R * a.groups) * x.b < 4 * x.cu_count || lds() > kRelLds)) --a.groups;
+  while (R > 4 && lds() > kRelLds) R /= 2;
+  const int64_t ntiles = (x.g->n + R * a.groups - 1) / (R * a.groups);
+  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>((int64_t)(160 * 1024 / lds()), 8 * 256 / nt));
   const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(ntiles, (int64_t)x.cu_count * per_cu));
-  if (launch_rel_ema(x.dt, a, R, nt, dim3((unsigned)blocks, (unsigned)x.b), lds, x.s)) {
+  if (launch_rel_ema(x.dt, a, R, nt, dim3((unsigned)blocks, (unsigned)x.b), lds(), x.s)) {
     set_error("sg2v_count: no vertex-relative eMA variant for R=%d", R);
     return SG2V_EINVAL;
   }

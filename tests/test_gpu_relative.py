@@ -159,3 +159,22 @@ def test_adjoint_of_entries_without_reverse():
     with sg.tuned(flags=sg.TUNE_NO_COLOR_SKIP):
         b = sg.count_grad(plan, g, c, [1.0, 1.0], "fp64").cpu().numpy()
     np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("par,k", [(gg.BINTREE7, 7), (gg.BINTREE7, 8), ([-1, 0, 0, 1, 1], 5), ([-1, 0, 1, 0, 3], 6)])
+@pytest.mark.parametrize("n", [20011, 24576])
+def test_relative_multiply_add_in_row_groups(par, k, n):
+    """Enough rows that threads of narrow outputs (6 to 35 columns) take several
+    groups of rows each; a last tile of 11, 43, ... rows and whole tiles."""
+    g = sg.Graph.from_csr(hubs(n, k, False))
+    plan = sg.Plan(par, k)
+    c = sg.Colorings(g, k, 5, 7)
+    print("row groups", n, par, k, flush=True)
+    got = {m: sg.count(plan, g, c, m) for m in ("u64", "fp64", "fp32s")}
+    with sg.tuned(flags=sg.TUNE_NO_COLOR_SKIP):
+        full = sg.count(plan, g, c, "u64")["colorful_u64"]
+    for j in range(7):
+        u = int(got["u64"]["colorful_u64"][j])
+        assert u == int(full[j])
+        for m in ("fp64", "fp32s"):
+            assert got[m]["colorful"][j] == pytest.approx(float(u), rel=TOL[m])
