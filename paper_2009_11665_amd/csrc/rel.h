@@ -34,6 +34,29 @@ __device__ __forceinline__ float wave_max(float m) {
   return m;
 }
 
+// Raises *mx, a table's largest mantissa, to this wave's.  The waves of a launch
+// share the address, and device-wide atomics to one address run one after the other
+// (about 10 ns each): a wave that would not raise it, as all but a few, only reads.
+__device__ __forceinline__ void rel_raise_wave(unsigned *mx, unsigned x) {
+  if (x > __hip_atomic_load(mx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(mx, x);
+}
+
+// The same for a block, of which every thread calls; one thread asks.  Path of 7
+// vertices, k = 9, 100,003 vertices, three colourings, with an atomic of every wave
+// 1.43 ms, with a read before it 0.93, once a block 0.92; multiply-add of 20
+// columns, 8 x 65536 rows, 100, 58 and 48 us.
+__device__ __forceinline__ void rel_raise(unsigned *mx, float m) {
+  __shared__ unsigned wave_mx[8];
+  m = wave_max(m);
+  if ((threadIdx.x & (WAVE - 1)) == 0) wave_mx[threadIdx.x / WAVE] = __float_as_uint(m);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    unsigned x = wave_mx[0];
+    for (int w = 1; w < (int)(blockDim.x / WAVE); ++w) x = max(x, wave_mx[w]);
+    rel_raise_wave(mx, x);
+  }
+}
+
 // FP32S: a contribution of exponent ec (cz: it is zero) added to a table of
 // exponent eo and largest mantissa bits mo: the exponent of the sum and the
 // factors of the old values and of the contribution

@@ -420,10 +420,7 @@ __global__ void __launch_bounds__(BLOCK) k_rel_spmm(RelSpmmArgs a) {
   if constexpr (is_u64<T>) {
     if (ovf) atomicOr(a.ovf, 1);
   }
-  if constexpr (sizeof(T) == 4) {
-    cmax = wave_max(cmax);
-    if (lane == 0 && cmax > 0.f) atomicMax(a.mx_out + jj, __float_as_uint(cmax));
-  }
+  if constexpr (sizeof(T) == 4) rel_raise(a.mx_out + jj, cmax);
 }
 
 // The same aggregation for narrow outputs: a lane adds the elements it has read
@@ -587,10 +584,7 @@ __global__ void __launch_bounds__(BLOCK) k_rel_spmm_add(RelSpmmArgs a) {
   if constexpr (is_u64<T>) {
     if (ovf) atomicOr(a.ovf, 1);
   }
-  if constexpr (sizeof(T) == 4) {
-    cmax = wave_max(cmax);
-    if (lane == 0 && cmax > 0.f) atomicMax(a.mx_out + jj, __float_as_uint(cmax));
-  }
+  if constexpr (sizeof(T) == 4) rel_raise(a.mx_out + jj, cmax);
 }
 
 // ---------------------------------------------------------------------------
@@ -855,9 +849,9 @@ __global__ void __launch_bounds__(BLOCK, 6) k_rel_wide(RelWideArgs a) {
   if constexpr (is_u64<T>) {
     if (ovf) atomicOr(a.ovf, 1);
   }
-  if constexpr (sizeof(T) == 4) {
+  if constexpr (sizeof(T) == 4) {  // the waves of a block end at different times
     cmax = wave_max(cmax);
-    if (lane == 0 && cmax > 0.f) atomicMax(a.mx_out + jj, __float_as_uint(cmax));
+    if (lane == 0) rel_raise_wave(a.mx_out + jj, __float_as_uint(cmax));
   }
 }
 
@@ -897,10 +891,7 @@ __global__ void __launch_bounds__(BLOCK) k_rel_xsum(RelXsumArgs a) {
   if constexpr (is_u64<T>) {
     if (ovf) atomicOr(a.ovf, 1);
   }
-  if (a.mx) {
-    cmax = wave_max(cmax);
-    if ((threadIdx.x & (WAVE - 1)) == 0 && cmax > 0.f) atomicMax(a.mx + jj, __float_as_uint(cmax));
-  }
+  if (a.mx) rel_raise(a.mx + jj, cmax);
 }
 
 // Partial rows of a long row summed in slot order.
@@ -935,10 +926,7 @@ __global__ void __launch_bounds__(BLOCK) k_rel_combine(RelCombineArgs a) {
   if constexpr (is_u64<T>) {
     if (ovf) atomicOr(a.ovf, 1);
   }
-  if (a.mx) {
-    cmax = wave_max(cmax);
-    if ((threadIdx.x & (WAVE - 1)) == 0 && cmax > 0.f) atomicMax(a.mx + jj, __float_as_uint(cmax));
-  }
+  if (a.mx) rel_raise(a.mx + jj, cmax);
 }
 
 // ---------------------------------------------------------------------------
@@ -1075,10 +1063,7 @@ __global__ void __launch_bounds__(NT) k_rel_ema(RelEmaArgs a) {
   if constexpr (is_u64<T>) {
     if (ovf) atomicOr(a.ovf, 1);
   }
-  if constexpr (SC) {
-    cmax = wave_max(cmax);
-    if ((threadIdx.x & (WAVE - 1)) == 0 && cmax > 0.f) atomicMax(a.mx_out + jj, __float_as_uint(cmax));
-  }
+  if constexpr (SC) rel_raise(a.mx_out + jj, cmax);
 }
 
 // ---------------------------------------------------------------------------

@@ -290,10 +290,7 @@ __global__ void __launch_bounds__(BLOCK) k_rel_back(RelBackArgs a) {
       r0 = r1;
     }
   }
-  if constexpr (SC) {
-    cmax = wave_max(cmax);
-    if (lane == 0 && cmax > 0.f) atomicMax(a.mx_out, __float_as_uint(cmax));
-  }
+  if constexpr (SC) rel_raise(a.mx_out, cmax);
 }
 
 // Partial rows of long rows, in slot order, to the adjoint table.
@@ -321,10 +318,7 @@ __global__ void __launch_bounds__(BLOCK) k_rel_back_combine(RelBackCombineArgs a
     *dst = y;
     if constexpr (SC) cmax = fmaxf(cmax, y);
   }
-  if constexpr (SC) {
-    cmax = wave_max(cmax);
-    if ((threadIdx.x & (WAVE - 1)) == 0 && cmax > 0.f) atomicMax(a.mx_out, __float_as_uint(cmax));
-  }
+  if constexpr (SC) rel_raise(a.mx_out, cmax);
 }
 
 // Derivative by the entries of the histogram: Hbar(i, c_j).
@@ -379,8 +373,10 @@ __global__ void __launch_bounds__(BLOCK) k_max_wdeg(const int64_t *row_ptr, cons
     for (int off = 1; off < WAVE; off <<= 1) s += shfl_xor(s, off);
     if (s > best) best = s;
   }
-  if (lane == 0 && best > 0.0)
-    atomicMax((unsigned long long *)out, __builtin_bit_cast(unsigned long long, best));
+  // most waves only read: as in rel_raise
+  const unsigned long long mine = __builtin_bit_cast(unsigned long long, best);
+  if (lane == 0 && best > 0.0 && mine > __hip_atomic_load((unsigned long long *)out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    atomicMax((unsigned long long *)out, mine);
 }
 
 void launch_max_wdeg(const int64_t *row_ptr, const float *w, int64_t n, double *out, hipStream_t s) {
