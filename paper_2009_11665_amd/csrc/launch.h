@@ -329,6 +329,7 @@ struct RelSpmmArgs {
   int32_t cw, wout, wout4; // absolute sets and output columns, padded
   int32_t sr;              // stride of a staged row; its element sr - 4 is zero
   int32_t lp, streams;     // lanes per gathered row, rows gathered at a time
+  int32_t padded;          // the last lane of a gathered row holds padding
   int32_t gw;              // lanes of an output group (64: the whole wave)
   int32_t R;               // rows per wave, at most 63
   int32_t tlong;

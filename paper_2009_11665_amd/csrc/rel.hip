@@ -502,11 +502,22 @@ __global__ void __launch_bounds__(BLOCK) k_rel_spmm_add(RelSpmmArgs a) {
           if (act && sq < nb) {
             const M16 mp = *(const M16 *)(lmap + (iq & 0xFFFF) + vec * N);
             C *row = acc + ((unsigned)iq >> 16);
-#pragma unroll
-            for (int u = 0; u < N; ++u) {
+            auto add = [&](int u) {
               C y = (C)x.x[u];
               if constexpr (WEIGHTED) y *= (C)wq;
               rel_add<C>(row + mp.x[u], y, mp.x[u] != a.cw, ovf);
+            };
+            // The padding of one row's entries goes to one address, adds to which are
+            // serial: up to three of four elements in FP32, left out (15 columns, 8 x
+            // 2.1M entries, 396 -> 354 us).  In 8-byte elements it is one of two at
+            // most, and the branches cost more (path of 8, U64: 1.44 -> 1.57 ms).
+            if (sizeof(T) == 4 && a.padded) {
+#pragma unroll
+              for (int u = 0; u < N; ++u)
+                if (mp.x[u] != a.cw) add(u);
+            } else {
+#pragma unroll
+              for (int u = 0; u < N; ++u) add(u);
             }
           }
         }
@@ -1156,17 +1167,26 @@ __global__ void __launch_bounds__(BLOCK) k_rel_root(RelRootArgs a) {
   }
 }
 
-// Block partials of each colouring in a fixed order (one wave per colouring),
-// and in FP32S the exponent of the result.
+// Block partials of each colouring in a fixed order (one wave per colouring, eight
+// loads in flight per lane: 2048 partials one after the other took 10 us), and in
+// FP32S the exponent of the result.
 template <typename Acc>
 __global__ void __launch_bounds__(WAVE) k_rel_final(RelFinalArgs a) {
   const int j = blockIdx.x, lane = threadIdx.x;
   const Acc *pj = (const Acc *)a.partial + (int64_t)j * a.nblk;
   Acc s = Acc(0);
   bool o = false;
-  for (int q = lane; q < a.nblk; q += WAVE) {
-    if constexpr (is_u64<Acc>) s = Arith<Acc>::add(s, pj[q], o);
-    else s += pj[q];
+  constexpr int U = 8;
+  for (int q = lane; q < a.nblk; q += U * WAVE) {
+    Acc v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = pj[min(q + u * WAVE, a.nblk - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const Acc x = q + u * WAVE < a.nblk ? v[u] : Acc(0);
+      if constexpr (is_u64<Acc>) s = Arith<Acc>::add(s, x, o);
+      else s += x;
+    }
   }
   for (int off = 1; off < WAVE; off <<= 1) {
     if constexpr (is_u64<Acc>) s = Arith<Acc>::add(s, shfl_xor(s, off), o);

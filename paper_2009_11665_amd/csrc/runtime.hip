@@ -2299,6 +2299,7 @@ sg2v_status rel_spmm(Ctx &x, int node) {
   a.wmap = (int32_t)round_up(Mt.t.cols, 4);
   a.sr = (int32_t)round_up(Mt.t.cols, 4) + 4;
   a.lp = (int32_t)((Mt.t.cols + N - 1) / N);
+  a.padded = Mt.t.cols % N != 0;
   if (a.lp > 64 || a.wout < 1 || a.wout > 384) {
     set_error("sg2v_count: aggregated rows of %d columns have no vertex-relative kernel", (int)Mt.t.cols);
     return SG2V_EINVAL;
