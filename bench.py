@@ -28,7 +28,7 @@ if ROOT not in sys.path:
 
 METRIC = "colorings/s batched FP32 vs plain FP64, RMAT-1M 15-vertex tree; HBM GB/s"
 HBM_PEAK_GBPS = 8000.0
-KERNEL_SOURCE = os.path.join(ROOT, "paper_2009_11665_amd", "csrc", "kernels.hip")
+KERNEL_SOURCE = os.path.join(ROOT, "paper_2009_11665_amd", "csrc", "rel.hip")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "spmm_traffic_bintree15_rmat20.json")
 
 
@@ -68,10 +68,11 @@ def oracle_work(parent, k, n, nnz):
 
 
 def kernel_sha():
-    """Hash of the SpMM kernel source (the text between its BEGIN/END marks)."""
+    """Hash of the source of the large workload's SpMM (the text between its
+    BEGIN/END marks)."""
     with open(KERNEL_SOURCE) as f:
         src = f.read()
-    body = src[src.index("// BEGIN k_spmm"):src.index("// END k_spmm")]
+    body = src[src.index("// BEGIN k_rel_wide"):src.index("// END k_rel_wide")]
     return hashlib.sha256(body.encode()).hexdigest()[:16]
 
 
@@ -119,7 +120,7 @@ def write_traffic(spmm_fetch, spmm_write, copy_fetch, copy_write, gather_fetch, 
             raise SystemExit(f"no matching dispatches of {counter} in {db}")
         return sum(v) / len(v), len(v)
 
-    is_spmm = lambda name: "k_spmm<float" in name  # noqa: E731
+    is_spmm = lambda name: "k_rel_wide<float" in name  # noqa: E731
     is_copy = lambda name: "copyBuffer" in name  # noqa: E731
     is_gather = lambda name: "gather" in name.lower()  # noqa: E731
     nbytes = mib * (1 << 20)
@@ -135,7 +136,7 @@ def write_traffic(spmm_fetch, spmm_write, copy_fetch, copy_write, gather_fetch, 
     sf, nf = mean_of(spmm_fetch, "FETCH_SIZE", is_spmm)
     sw, nw = mean_of(spmm_write, "WRITE_SIZE", is_spmm)
     rd, wr = sf * 1024.0 * f_fetch, sw * 1024.0 * f_write
-    out = {"kernel": "k_spmm<float,...>", "kernel_source_sha": kernel_sha(),
+    out = {"kernel": "k_rel_wide<float,...>", "kernel_source_sha": kernel_sha(),
            "graph_relabel": relabel,
            "spmm_launches_per_colouring": nf,
            "hbm_bytes_per_launch": rd + wr, "read_bytes_per_launch": rd, "write_bytes_per_launch": wr,
@@ -561,8 +562,8 @@ def main():
     passes = prof["hist"]["launches"] // args.steps if args.steps else 0
     achieved = sp["bytes"] / (sp["ms"] * 1e-3) / 1e9 if sp["ms"] > 0 else 0.0
     # measured HBM bytes per SpMM launch (rocprofv3 counters)
-    traffic = load_traffic(sp["launches"] // (args.steps * ncol) if sp["launches"] % (args.steps * ncol) == 0
-                           else None, args.relabel)
+    whole = sp["launches"] % (args.steps * ncol) == 0 and not args.tune_flags
+    traffic = load_traffic(sp["launches"] // (args.steps * ncol) if whole else None, args.relabel)
     total_bytes = sum(v["bytes"] for v in prof.values())
     kernels = {kk: {"launches": v["launches"], "ms_per_step": v["ms"] / args.steps,
                     "model_GBps": (v["bytes"] / (v["ms"] * 1e-3) / 1e9) if v["ms"] else 0.0}
@@ -591,12 +592,11 @@ def main():
             "xsplit_min": args.xsplit_min,
             "passes_per_step": passes,
             "colorings_per_pass": ncol / passes if passes else None,
-            "mode": ("fp32 mantissa + per-column exponent; one colouring per pass (a single "
-                     "colouring's 6435-column table already fills 101 SpMM column chunks, so "
-                     "colourings are not concatenated as columns here)"
+            "mode": ("fp32 mantissa + power-of-two exponents; one colouring per pass (one "
+                     "colouring's tables of thousands of columns fill the chip)"
                      if passes == ncol else
-                     f"fp32 mantissa + per-column exponent; {ncol // max(passes, 1)} colourings "
-                     "concatenated as table columns per pass"),
+                     f"fp32 mantissa + power-of-two exponents; {ncol // max(passes, 1)} colourings "
+                     "per pass"),
         },
         "fp64_plain": fp64,
         "speedup_vs_fp64_plain": (value / fp64["value"]) if fp64 else None,
@@ -609,7 +609,7 @@ def main():
         "kernels": kernels,
         "roofline": {
             "bound": "hbm",
-            "kernel": "k_spmm",
+            "kernel": "k_spmm" if args.tune_flags else "k_rel_wide",
             "achieved": achieved,
             "peak": HBM_PEAK_GBPS,
             "unit": "GB/s",

@@ -663,6 +663,7 @@ __global__ void __launch_bounds__(BLOCK) k_rel_sort(RelSortArgs a) {
   }
 }
 
+// BEGIN k_rel_wide
 // Bound by the lines in flight per CU: 82 lines per entry and table of 3003
 // columns, half of them from beyond the L2 (6.3 TB/s), about 71 in flight per CU
 // at 452 cycles.  Six waves per SIMD (five without the launch bound): 214 -> 199
@@ -866,6 +867,8 @@ __global__ void __launch_bounds__(BLOCK, 6) k_rel_wide(RelWideArgs a) {
   }
 }
 
+// END k_rel_wide
+
 // The eight range partials of every split task, in range order: to its row, or to
 // the slot of its segment.
 template <typename T>
@@ -946,13 +949,12 @@ __global__ void __launch_bounds__(BLOCK) k_rel_combine(RelCombineArgs a) {
 // A block stages R * groups consecutive rows of both tables in LDS, transposed
 // (the rows plus one 16-byte vector per column, so that lanes on different
 // columns spread over the banks); a thread owns output columns and keeps R sums.
-// Narrow outputs have a thread group for each R rows of the tile: balanced tree
-// of 7 vertices, 16 colourings of 65536 vertices (6 to 20 columns), whole count
-// 0.99 -> 0.72 ms; all trees of 9 vertices 124.7 -> 119.7 ms.  Half
-// the columns of the absolute tables and rows in order: 1.42 -> 0.78 ms on
+// Half the columns of the absolute tables and rows in order: 1.42 -> 0.78 ms on
 // average over the splits of the nine-vertex trees (4M rows of about 60 columns
-// three times, 2.9 GB: 3.7 TB/s).
-
+// three times, 2.9 GB: 3.7 TB/s).  Narrow outputs have a thread group for each R
+// rows of the tile: binary tree of 7 vertices, 8 colourings of 65536 vertices (6 to
+// 20 columns), whole count 0.99 -> 0.72 ms; all trees of 9, 124.7 -> 119.7 ms.
+//
 // Without X (HASX false) it counts as one: the adjoint of a root reduction.  The
 // adjoint also adds to a table that holds values already (a.accumulate).
 
