@@ -74,6 +74,16 @@ constexpr int kSpmmBlocks = 2048;  // blocks of an SpMM launch without the split
 // early pick up the remaining units (2048: 284 ms, 4096: 278 ms, 8192: 283 ms
 // for the 15-vertex tree on RMAT scale 20)
 constexpr int kXsplitBlocks = 4096;
+// Vertex-relative count: rows (vertices times colourings) of a pass.  Each step has
+// a plane of its own, so a pass gains nothing from colourings beyond a full chip, and
+// tables that fit the Infinity Cache are read from it by the next step: 16 colourings
+// of three templates on 500,000 vertices in passes of 1, 2, 4, 8 and 16 take 41.7,
+// 41.0, 41.9, 45.5 and 50.3 ms, path of 5 on as many 4.3, 3.9, 3.9, 4.3 and 5.2 ms;
+// all trees of 7 on 200,000 vertices 6.7, 5.4, 4.8 and 4.5 ms.  Few rows leave the
+// chip idle: caterpillar of 10 on 16,384 vertices in passes of 4, 8, 16 takes 1.29,
+// 1.11, 0.96 ms.
+constexpr int64_t kRelRowsMost = 1600000;
+constexpr int64_t kRelRowsLeast = 262144;
 constexpr int kRootBlocks = 2048;    // most root blocks (per-block partial sums)
 constexpr int kXsplit = 8;          // neighbour ranges (one per XCD)
 constexpr int64_t kXsplitMin = 512; // tasks at least this long are split by range
@@ -2544,12 +2554,23 @@ sg2v_status check_inputs(const sg2v_plan *plan, const sg2v_graph *g, const sg2v_
   return SG2V_OK;
 }
 
+// Flags that ask for kernels or layouts of the absolute tables keep them; the
+// widths, tile rows and split sizes of the tuning apply to those only.
+bool rel_wanted(const sg2v_tuning_t &t) {
+  return (t.flags & ~(SG2V_TUNE_BATCH_SERIAL | SG2V_TUNE_GRAD_RECOMPUTE)) == 0;
+}
+
 int choose_batch(const Plan &P, int ncol, int dt, int64_t n, int64_t n_slots) {
   sg2v_tuning_t tu = tuning();
   int64_t widest_passive = 1;
   for (auto &nd : P.nodes)
     if (nd.n_passive_uses > 0) widest_passive = std::max(widest_passive, nd.size == 1 ? P.k : nd.cols);
-  int b = tu.batch > 0 ? tu.batch : (int)std::max<int64_t>(1, 1024 / widest_passive);
+  int64_t most = std::max<int64_t>(1, 1024 / widest_passive);
+  if (rel_wanted(tu) && rel_ok(P, dt == DT_F32 ? 4 : 8, kRelLds)) {
+    most = std::min(most, std::max<int64_t>(1, kRelRowsMost / n));
+    if (widest_passive <= 1024) most = std::max(most, kRelRowsLeast / n);
+  }
+  int b = tu.batch > 0 ? tu.batch : (int)std::min<int64_t>(most, 65535);
   b = std::max(1, std::min({b, ncol, 65535}));  // colourings of a pass index grid.y
   // memory budget
   size_t fr = 0, tot = 0;
@@ -2562,12 +2583,6 @@ int choose_batch(const Plan &P, int ncol, int dt, int64_t n, int64_t n_slots) {
     b = (b + 1) / 2;
   }
   return b;
-}
-
-// Flags that ask for kernels or layouts of the absolute tables keep them; the
-// widths, tile rows and split sizes of the tuning apply to those only.
-bool rel_wanted(const sg2v_tuning_t &t) {
-  return (t.flags & ~(SG2V_TUNE_BATCH_SERIAL | SG2V_TUNE_GRAD_RECOMPUTE)) == 0;
 }
 
 // Buffers of the wide aggregations: sorted entries and their offsets, and the

@@ -178,3 +178,22 @@ def test_relative_multiply_add_in_row_groups(par, k, n):
         assert u == int(full[j])
         for m in ("fp64", "fp32s"):
             assert got[m]["colorful"][j] == pytest.approx(float(u), rel=TOL[m])
+
+
+@pytest.mark.parametrize("n,ncol", [(1000, 270), (120011, 20)])
+def test_relative_passes_by_rows(n, ncol):
+    """Colourings of a pass by its rows: more than the columns of the absolute
+    tables would give (262 of path5 on 1000 vertices), fewer on a large graph (13
+    of 120,011); a last pass of the rest.  Exact counts do not depend on it."""
+    edges = [(v, (v * 7 + 3) % n) for v in range(n)] + [(v, (v + 1) % n) for v in range(n - 1)]
+    g = sg.Graph.from_csr(gg.from_edge_list(n, sorted({(min(e), max(e)) for e in edges if e[0] != e[1]}), None))
+    plan = sg.Plan(gg.PATH5, 5)
+    c = sg.Colorings(g, 5, 8, ncol)
+    print("passes", n, ncol, flush=True)
+    r = sg.count(plan, g, c, "u64")["colorful_u64"]
+    f = sg.count(plan, g, c, "fp32s")["colorful"]
+    with sg.tuned(batch=7):
+        s = sg.count(plan, g, c, "u64")["colorful_u64"]
+    assert [int(x) for x in r] == [int(x) for x in s] and all(int(x) > 0 for x in r)
+    for x, y in zip(r, f):
+        assert y == pytest.approx(float(x), rel=TOL["fp32s"])
