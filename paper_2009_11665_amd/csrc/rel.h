@@ -24,6 +24,24 @@ __device__ __forceinline__ void rel_add(T *p, T v, bool valid, bool &ovf) {
 __device__ __forceinline__ int rel_frame(int e, unsigned mx) { return mx ? e + ilog2_bits(mx) + 1 : 0; }
 __device__ __forceinline__ float rel_factor(unsigned mx) { return mx ? exp2_int(-(ilog2_bits(mx) + 1)) : 0.f; }
 
+// A gathered vector in its table's frame.  Weighted FP32 sums take the factor
+// before the weight: the values are then at most 1 and the sum is of the size of
+// the weights, whatever the size of the values before it (sums of w x scaled
+// afterwards leave the range of a float where w * max|x| does, from three edges of
+// 2^-50 in a row on).  Without weights a sum is below 2^62 (degree times degree),
+// and one multiplication of it costs less than one of every element.
+template <typename T, bool WEIGHTED>
+__device__ __forceinline__ u32x4 rel_scaled(u32x4 v, T f) {
+  if constexpr (WEIGHTED && sizeof(T) == 4) {
+    V16<T> x = __builtin_bit_cast(V16<T>, v);
+#pragma unroll
+    for (int u = 0; u < V16<T>::N; ++u) x.x[u] *= f;
+    return __builtin_bit_cast(u32x4, x);
+  } else {
+    return v;
+  }
+}
+
 __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();

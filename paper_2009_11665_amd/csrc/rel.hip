@@ -192,9 +192,9 @@ __global__ void __launch_bounds__(BLOCK) k_rel_spmm(RelSpmmArgs a) {
   const T *__restrict__ M = (const T *)a.M + jj * a.mplane;
   T *__restrict__ B = (T *)a.B + jj * a.bplane;
   T *__restrict__ Pt = (T *)a.partial + jj * a.pplane;
-  T f = T(1);
+  T fs = T(1), f = T(1);  // factors of the staged rows and of the sums
   if constexpr (sizeof(T) == 4) {
-    f = rel_factor(a.mx_in[jj]);
+    (WEIGHTED ? fs : f) = rel_factor(a.mx_in[jj]);
     if (blockIdx.x == 0 && threadIdx.x == 0) a.e_out[jj] = rel_frame(a.e_in[jj], a.mx_in[jj]);
   }
   const int stream = lane / a.lp, vec = lane - stream * a.lp;
@@ -338,7 +338,7 @@ __global__ void __launch_bounds__(BLOCK) k_rel_spmm(RelSpmmArgs a) {
 #pragma unroll
         for (int q = 0; q < UNR; ++q) {
           const int sl = q * streams + stream;
-          if (act) *(u32x4 *)(stg + sl * SR + vec * N) = v[q];
+          if (act) *(u32x4 *)(stg + sl * SR + vec * N) = rel_scaled<T, WEIGHTED>(v[q], fs);
         }
         issue(t0 + E);
         wave_lds_fence();
@@ -535,10 +535,12 @@ __global__ void __launch_bounds__(BLOCK) k_rel_spmm_add(RelSpmmArgs a) {
       const C *q = acc0 + lout[r * a.wout4 + p];
       C x = q[0];
       for (int w2 = 1; w2 < WAVES_PER_BLOCK; ++w2) x = Arith<C>::add(x, q[(size_t)w2 * R * S], ovf);
-      T y = (T)x;
+      T y;
       if constexpr (sizeof(T) == 4) {
-        y *= f;
+        y = (T)(x * (C)f);  // in double: weighted sums may leave the range of a float
         if (slot < 0) cmax = fmaxf(cmax, y);
+      } else {
+        y = (T)x;
       }
       dst[a.opos ? a.opos[p] : p] = y;
     }
@@ -574,10 +576,13 @@ __global__ void __launch_bounds__(BLOCK) k_rel_spmm_add(RelSpmmArgs a) {
     while (__ballot(loc < nr)) {
       const int r = shfl_i32(rcol, loc & (WAVE - 1));
       if (loc < nr && !(lm >> loc & 1)) {
-        T y = (T)acc[loc * S + lout[r * a.wout4 + p]];
+        const C x = acc[loc * S + lout[r * a.wout4 + p]];
+        T y;
         if constexpr (sizeof(T) == 4) {
-          y *= f;
+          y = (T)(x * (C)f);
           cmax = fmaxf(cmax, y);
+        } else {
+          y = (T)x;
         }
         B[(row0 + loc) * a.ldb + (a.opos ? a.opos[p] : p)] = y;
       }
@@ -701,9 +706,9 @@ __global__ void __launch_bounds__(BLOCK, 6) k_rel_wide(RelWideArgs a) {
   T *__restrict__ B = (T *)a.B + jj * a.bplane;
   T *__restrict__ Pt = (T *)a.partial + jj * a.pplane;
   T *__restrict__ P8 = (T *)a.partial8 + jj * a.p8plane;
-  T f = T(1);
+  T fs = T(1), f = T(1);  // factors of the gathered rows and of the sums
   if constexpr (sizeof(T) == 4) {
-    f = rel_factor(a.mx_in[jj]);
+    (WEIGHTED ? fs : f) = rel_factor(a.mx_in[jj]);
     if (blockIdx.x == 0 && chunk == 0 && threadIdx.x == 0) a.e_out[jj] = rel_frame(a.e_in[jj], a.mx_in[jj]);
   }
   // lanes of a run by class (low, high): vectors, lanes per run, streams
@@ -783,7 +788,7 @@ __global__ void __launch_bounds__(BLOCK, 6) k_rel_wide(RelWideArgs a) {
 #pragma unroll
           for (int q = 0; q < U; ++q) {
             const bool ok = t0 + q * st + stream < nb;
-            const V16<T> x = __builtin_bit_cast(V16<T>, v[q]);
+            const V16<T> x = __builtin_bit_cast(V16<T>, rel_scaled<T, WEIGHTED>(v[q], fs));
 #pragma unroll
             for (int u = 0; u < N; ++u) {
               const T y = ok ? x.x[u] : T(0);

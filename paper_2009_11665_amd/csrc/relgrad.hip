@@ -76,11 +76,11 @@ __global__ void __launch_bounds__(BLOCK) k_rel_back(RelBackArgs a) {
   const T *__restrict__ M = (const T *)a.M;
   T *O = (T *)a.O;
   T *Pt = (T *)a.partial;
-  T f = T(1), fm = T(1);
+  T fs = T(1), f = T(1), fm = T(1);  // factors of the staged rows, of their sums and of M
   RelAdd add{0, 1.f, 1.f};
   double scale = a.scale;
   if constexpr (SC) {
-    f = rel_factor(a.mxx[0]);
+    (WEIGHTED ? fs : f) = rel_factor(a.mxx[0]);
     fm = rel_factor(a.mxm[0]);
     const int ec = rel_frame(a.ex[0], a.mxx[0]);
     scale = ldexp(scale, ec + rel_frame(a.em[0], a.mxm[0]));
@@ -218,7 +218,7 @@ __global__ void __launch_bounds__(BLOCK) k_rel_back(RelBackArgs a) {
 #pragma unroll
         for (int q = 0; q < UNR; ++q) {
           const int sl = q * streams + stream;
-          if (act) *(u32x4 *)(stg + sl * SR + vec * N) = v[q];
+          if (act) *(u32x4 *)(stg + sl * SR + vec * N) = rel_scaled<T, WEIGHTED>(v[q], fs);
         }
         issue(t0 + E);
         wave_lds_fence();

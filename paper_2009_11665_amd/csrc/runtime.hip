@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cfloat>
 #include <chrono>
 #include <climits>
 #include <fstream>
@@ -2482,7 +2483,9 @@ sg2v_status rel_root(Ctx &x, int node, void *result, int *Eout) {
 // the steps of the pass, or those before step `stop`
 sg2v_status run_rel(Ctx &x, void *result, int *Eout, int stop = INT_MAX) {
   if (x.dt == DT_F32) {
-    const float mw = (float)std::max(1.0, x.g->max_wdeg);
+    // the histogram's bound, of the size of its largest sums whatever the weights are
+    // (0: every table is zero)
+    const float mw = x.g->max_wdeg > 0.0 ? std::max((float)x.g->max_wdeg, FLT_MIN) : 0.f;
     unsigned bits;
     std::memcpy(&bits, &mw, 4);
     launch_rel_init((int *)x.ws->small.p, (unsigned *)x.ws->small.p + (int64_t)x.rp.ntab * x.b, x.rp.ntab, x.b,
