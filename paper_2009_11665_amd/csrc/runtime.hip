@@ -2230,9 +2230,26 @@ sg2v_status rel_wide_spmm(Ctx &x, int node) {
                  ez * (double)binom(k, m) * x.b, x.s);
     // blocks along the tasks: whole rounds of the eight XCDs
     const int64_t gx = round_up(std::max<int64_t>(1, std::min<int64_t>((x.rel_items + 3) / 4, 4096)), kXsplit);
-    if (launch_rel_wide(x.dt, a, dim3((unsigned)gx, (unsigned)(a.nchunk * x.b)), lds, x.s)) {
-      set_error("sg2v_count: no chunked aggregation of %d columns", a.nout_max);
-      return SG2V_EINVAL;
+    // grid.y holds the chunks of a colouring and the colourings: at most 65,535 in all
+    const int per = 65535 / a.nchunk;
+    for (int j = 0; j < x.b; j += per) {
+      RelWideArgs c = a;
+      c.j0 += j;
+      c.scol += (int64_t)j * nnz;
+      if (c.sw) c.sw += (int64_t)j * nnz;
+      c.off += (int64_t)j * a.n_items * 32;
+      c.M = (const char *)a.M + (int64_t)j * a.mplane * x.es;
+      c.B = (char *)a.B + (int64_t)j * a.bplane * x.es;
+      c.partial = (char *)a.partial + (int64_t)j * a.pplane * x.es;
+      c.partial8 = (char *)a.partial8 + (int64_t)j * a.p8plane * x.es;
+      c.e_in += j;
+      c.mx_in += j;
+      c.e_out += j;
+      c.mx_out += j;
+      if (launch_rel_wide(x.dt, c, dim3((unsigned)gx, (unsigned)(a.nchunk * std::min(per, x.b - j))), lds, x.s)) {
+        set_error("sg2v_count: no chunked aggregation of %d columns", a.nout_max);
+        return SG2V_EINVAL;
+      }
     }
   }
   if (x.rel_x > 0) {

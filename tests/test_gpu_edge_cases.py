@@ -64,3 +64,26 @@ def test_noalloc_on_renumbered_graph():
     np.testing.assert_array_equal(na["colorful_u64"], ref["colorful_u64"])
     _, u, _ = O.count(G, par, k, O.colors(G.n, k, seed, 2), mode=O.U64)
     assert int(na["colorful_u64"][2]) == u
+
+
+@pytest.mark.parametrize("tuned", [{}, {"batch": 30000}])
+def test_many_colourings_of_a_chunked_aggregation(tuned):
+    """Chunks times colourings past the 65,535 blocks that a grid dimension holds
+    (path of 8 with 12 colours: 4 chunks, 30,000 colourings of 8 vertices a pass)."""
+    n, ncol = 8, 30000
+    e = [(i, j) for i in range(n) for j in range(i + 1, n) if (i, j) != (2, 5)]
+    g = sg.Graph.from_csr(gg.from_edge_list(n, e, None))
+    plan = sg.Plan(gg.PATH8, 12)
+    c = sg.Colorings(g, 12, 3, ncol)
+    print("chunks x colourings", tuned, flush=True)
+    got = {}
+    with sg.tuned(**tuned):
+        for m in ("u64", "fp64", "fp32s"):
+            got[m] = sg.count(plan, g, c, m)
+    with sg.tuned(batch=1000):
+        ref = sg.count(plan, g, c, "u64")["colorful_u64"]
+    assert [int(x) for x in got["u64"]["colorful_u64"]] == [int(x) for x in ref]
+    assert sum(int(x) > 0 for x in ref[16384:]) > 100
+    f = [float(x) for x in ref]
+    np.testing.assert_allclose(got["fp64"]["colorful"], f, rtol=1e-12)
+    np.testing.assert_allclose(got["fp32s"]["colorful"], f, rtol=1e-5)
