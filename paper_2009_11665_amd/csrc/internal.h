@@ -146,6 +146,8 @@ struct RelMap {
 // ones.  In a gathered row of a vertex of colour c these are one run: the sets
 // without c, of PH if c is low and of PH - {c} if it is high.
 bool rel_wide(int k, int m);
+// aggregations below those that may use their sorted entries (chunk tables are made)
+bool rel_sorted(int k, int m);
 int rel_low(int k);
 // Columns of the q-sets: their ranks, or (tables gathered in chunks) each choice
 // of high relative colours at a multiple of 32 columns.

@@ -511,6 +511,8 @@ bool rel_wide(int k, int m) {
   return m >= 2 && (binom(k, m) > 512 || binom(k - 1, m) > 384 || binom(k - 1, m - 1) > 128);
 }
 
+bool rel_sorted(int k, int m) { return m >= 2 && !rel_wide(k, m) && binom(k, m) > 100; }
+
 // Ten low colours: a run is up to 126 columns of a low colour's row, 252 of a
 // high one's (15-vertex tree, RMAT scale 20, FP32: the aggregation of 6435 sets
 // takes 178 ms; nine: 228, shorter runs leave more of a line and of a wave unused;

@@ -992,6 +992,8 @@ sg2v_status plan_device(const Plan &P, int device, hipStream_t s, DevPlan *out) 
     D.rel_root.assign(P.roots.size(), nullptr);
     std::vector<char> wm, wb;
     rel_wide_nodes(P, wm, wb);
+    bool any_wide = false;
+    for (auto &nd : P.nodes) any_wide |= nd.n_passive_uses > 0 && rel_wide(P.k, nd.size);
     auto u16 = [](const std::vector<int32_t> &x) { return std::vector<uint16_t>(x.begin(), x.end()); };
     auto lay_b = [&](int p) { return rel_layout(P.k, P.nodes[p].size, wb[p]); };
     auto lay_m = [&](int q) {
@@ -1004,7 +1006,7 @@ sg2v_status plan_device(const Plan &P, int device, hipStream_t s, DevPlan *out) 
       if (wb[i]) pk.add(u16(lay_b((int)i).pos), &D.rel_bpos[i]);
       if (wm[i]) pk.add(u16(lay_m((int)i).pos), &D.rel_mpos[i]);
       if (nd.size == 1) continue;
-      if (nd.n_passive_uses > 0 && (rel_wide(P.k, nd.size) || !wb[i])) {
+      if (nd.n_passive_uses > 0 && (rel_wide(P.k, nd.size) || (any_wide && !wb[i] && rel_sorted(P.k, nd.size)))) {
         const RelWide w = rel_wide_tables(P.k, nd.size, wb[i]);
         pk.add(w.hdr, &D.rel_hdr[i]);
         pk.add(w.info, &D.rel_info[i]);
@@ -2311,11 +2313,16 @@ sg2v_status rel_spmm(Ctx &x, int node) {
   a.bplane = B.plane;
   a.partial = (char *)x.ws->arena.p + x.rp.partial_off;
   a.pplane = x.g->n_rslots * B.t.ld;
-  // Sorted entries pay where a row has several of a colour: with them at hand for
-  // the wide aggregations, from a mean degree of 4 k on for the others too (455 sets
-  // of the 15-vertex tree: RMAT scale 20, FP32 16.2 -> 10.5 ms; scale 18, FP64 5.9 ->
-  // 6.1 ms, so FP32 only).
-  if (rel_wide(k, m) || (x.rp.wide && x.es == 4 && !x.rp.wide_b[node] && x.g->nnz >= 4 * k * x.g->n))
+  // Sorted entries at hand for the wide aggregations serve the others too where a row
+  // has several of a colour and the output is wide enough for a wave per colour run:
+  // FP32, more than 100 sets, mean degree of 8 k.  Whole count of the 15-vertex tree
+  // (its 455 sets), staged over sorted: RMAT scale 20 of degree 190 (12.7 k) the
+  // aggregation 16.2 to 10.5 ms; 65,536 vertices at 13 k 1.02, 17 k 1.03, 6.7 k 1.00;
+  // 200,000 vertices at 4 k 0.98.  Caterpillar of 10, k = 12 (220 sets): 5 k 0.97,
+  // 8 k 1.00, 16 k 1.03.  With the 55 sets of path of 7, k = 11 as well, 0.88 at 5.5 k
+  // and 0.94 at 9 k, which are 0.97 and 1.00 without them: those run as LDS sums.
+  // FP64, RMAT scale 18, 5.9 over 6.1 ms: never.
+  if (rel_wide(k, m) || (x.rp.wide && x.es == 4 && !x.rp.wide_b[node] && rel_sorted(k, m) && x.g->nnz >= 8 * k * x.g->n))
     return rel_wide_spmm(x, node);
   a.opos = x.dp.rel_bpos[node];
   a.cw = (int32_t)round_up(binom(k, m), 4);
