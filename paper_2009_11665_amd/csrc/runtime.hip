@@ -2685,19 +2685,22 @@ sg2v_status prepare(Ctx &x, const sg2v_plan *plan, sg2v_graph *g, const sg2v_col
   // above; where the partial rows of long rows make them larger, they are not
   // used.
   x.rel = false;
-  if (Carver *cv = x.ws->arena.cv) {
-    // sg2v_count_noalloc takes what the absolute tables would fit
-    const size_t need = round_up(x.pp.arena, 256) + round_up(x.pp.small_bytes, 256) + round_up((size_t)kRootBlocks * b * 8, 256) +
-                        round_up((size_t)b * (64 + g->n) * 4 + 256, 256) + round_up((size_t)b * std::max<int64_t>(g->nnz, 1) + 256, 256) + 512;
+  if (opt.keep.empty() && !opt.no_fuse && rel_wanted(tu) && rel_ok(plan->p, x.es, std::min(kRelLds, x.lds_max))) {
+    build_rel(plan->p, g, b, x.dt, x.rp);
+    x.rel = x.rp.arena <= std::max<int64_t>(x.pp.arena, (int64_t)1 << 20) && x.rp.small_bytes <= x.pp.small_bytes + 4096;
+  }
+  Carver *cv = x.ws->arena.cv;
+  if (x.rel && cv) {
+    // sg2v_count_noalloc takes what the absolute tables' buffers (below) would fit
+    auto area = [](int64_t bytes) { return (size_t)round_up(bytes, 256); };
+    const size_t need = area(x.pp.arena) + area(x.pp.small_bytes) + area((int64_t)kRootBlocks * b * 8) + 256 +
+                        area((int64_t)b * (64 + g->n) * 4 + 256) + area((int64_t)b * std::max<int64_t>(g->nnz, 1) + 256) +
+                        area((int64_t)c->count * 12 + 64);
     if (need > cv->cap) {
       cv->exhausted = true;
       set_error("sg2v_count_noalloc: the count needs more than the %zu-byte scratch area (%zu bytes)", cv->cap, need);
       return SG2V_ENOMEM;
     }
-  }
-  if (opt.keep.empty() && !opt.no_fuse && rel_wanted(tu) && rel_ok(plan->p, x.es, std::min(kRelLds, x.lds_max))) {
-    build_rel(plan->p, g, b, x.dt, x.rp);
-    x.rel = x.rp.arena <= std::max<int64_t>(x.pp.arena, (int64_t)1 << 20) && x.rp.small_bytes <= x.pp.small_bytes + 4096;
   }
   if (x.rel && x.rp.wide) ST_TRY(rel_wide_buffers(x));
   ST_TRY(x.ws->arena.ensure(x.rel ? x.rp.arena : x.pp.arena));

@@ -81,3 +81,27 @@ def test_noalloc_rejects_what_does_not_fit():
     # the area is still usable afterwards
     cs = sg.Colorings(gs, k, 4, 2)
     check_same(sg.count_noalloc(plan, gs, cs, "fp32s"), sg.count(plan, gs, cs, "fp32s"), "fp32s")
+
+
+def test_noalloc_without_colour_skip_needs_no_neighbour_colours():
+    """A graph whose entries alone approach the area (a byte each for neighbour
+    colours): without the colour skip, which reads those, its tables fit."""
+    import torch
+
+    n, half = 16400, 2048  # 67.2M entries
+    off = torch.cat([torch.arange(-half, 0), torch.arange(1, half + 1)]).cuda()
+    ci = torch.sort((torch.arange(n, device="cuda")[:, None] + off) % n, dim=1)[0].to(torch.int32).reshape(-1)
+    assert ci.numel() > 64 << 20
+    g = sg.Graph(n, torch.arange(n + 1, device="cuda") * (2 * half), ci)
+    plan = sg.Plan([-1, 0, 1], 3)
+    c = sg.Colorings(g, 3, 1, 2)
+    say("noalloc: 67.2M entries, no colour skip")
+    with sg.tuned(flags=sg.TUNE_NO_COLOR_SKIP):
+        ref = sg.count(plan, g, c, "u64")
+        check_same(sg.count_noalloc(plan, g, c, "u64"), ref, "u64")
+    # every ordered pair of neighbours with all three colours
+    assert all(int(x) > 0 for x in ref["colorful_u64"])
+    say("noalloc: 67.2M entries, default")
+    with pytest.raises(sg.Sg2vError) as e:
+        sg.count_noalloc(plan, g, c, "u64")
+    assert e.value.status == -4 and "scratch area" in str(e.value)
