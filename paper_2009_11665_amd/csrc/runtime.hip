@@ -2587,13 +2587,41 @@ bool rel_wanted(const sg2v_tuning_t &t) {
   return (t.flags & ~(SG2V_TUNE_BATCH_SERIAL | SG2V_TUNE_GRAD_RECOMPUTE)) == 0;
 }
 
-int choose_batch(const Plan &P, int ncol, int dt, int64_t n, int64_t n_slots) {
+// What the wide aggregations take beside the tables: entries sorted by colour with
+// their offsets, and the range partials of tasks split by neighbour range (the
+// automatic rule: large graphs whose long tasks hold at least half the entries).
+struct WideNeed {
+  int64_t x_tasks = 0, items = 0;  // tasks taken per range; tasks and ranges of them
+  size_t sort = 0, part = 0;       // bytes
+};
+WideNeed rel_wide_need(const sg2v_graph *g, const RelPass &rp, int b, int es, bool split) {
+  WideNeed w;
+  if (split && large_graph(g->n) && g->long_share >= 0.5) {
+    while (w.x_tasks < g->n_tasks && g->h_task_len[w.x_tasks] >= kXsplitMin) ++w.x_tasks;
+    if ((double)b * kXsplit * w.x_tasks * rp.wide_ld * es > 4 * kXpartBytes) w.x_tasks = 0;
+  }
+  w.items = w.x_tasks * kXsplit + g->n_tasks - w.x_tasks;
+  w.sort = (size_t)b * (std::max<int64_t>(g->nnz, 1) * (g->w ? 8 : 4) + w.items * 64) + 256;
+  w.part = (size_t)b * kXsplit * w.x_tasks * rp.wide_ld * es + 256;
+  return w;
+}
+
+bool has_wide(const Plan &P) {
+  for (auto &nd : P.nodes)
+    if (nd.n_passive_uses > 0 && rel_wide(P.k, nd.size)) return true;
+  return false;
+}
+
+int choose_batch(const Plan &P, int ncol, int dt, const sg2v_graph *g) {
   sg2v_tuning_t tu = tuning();
+  const int64_t n = g->n;
+  const int es = esize_of(dt);
   int64_t widest_passive = 1;
   for (auto &nd : P.nodes)
     if (nd.n_passive_uses > 0) widest_passive = std::max(widest_passive, nd.size == 1 ? P.k : nd.cols);
   int64_t most = std::max<int64_t>(1, 1024 / widest_passive);
-  if (rel_wanted(tu) && rel_ok(P, dt == DT_F32 ? 4 : 8, kRelLds)) {
+  const bool rel = rel_wanted(tu) && rel_ok(P, es, kRelLds);
+  if (rel) {
     most = std::min(most, std::max<int64_t>(1, kRelRowsMost / n));
     if (widest_passive <= 1024) most = std::max(most, kRelRowsLeast / n);
   }
@@ -2605,43 +2633,73 @@ int choose_batch(const Plan &P, int ncol, int dt, int64_t n, int64_t n_slots) {
   int64_t budget = tu.budget_bytes > 0 ? tu.budget_bytes : (int64_t)(fr * 0.85);
   while (b > 1) {
     PassPlan pp;
-    build_pass(P, n, b, dt, pick_G(dt, widest_passive * b, n), n_slots, pp, PassOpts());
-    if (pp.arena <= budget) break;
+    build_pass(P, n, b, dt, pick_G(dt, widest_passive * b, n), g->n_slots, pp, PassOpts());
+    bool fits = pp.arena <= budget;
+    if (fits && rel && has_wide(P)) {
+      RelPass rp;
+      build_rel(P, g, b, dt, rp);
+      fits = rp.arena + (int64_t)rel_wide_need(g, rp, b, es, false).sort <= budget;
+    }
+    if (fits) break;
     b = (b + 1) / 2;
   }
   return b;
 }
 
-// Buffers of the wide aggregations: sorted entries and their offsets, and the
-// range partials of split tasks.  Where a fixed area cannot hold them the pass
-// uses the absolute tables.
+// Buffers of a pass with wide aggregations: its tables, sorted entries and range
+// partials.  What does not fit the fixed area, the tuning's budget or the free memory
+// goes: first the range partials (long tasks are then taken whole, with the same
+// results up to the order of their sums), then the relative tables (x.rel false).
 sg2v_status rel_wide_buffers(Ctx &x) {
   sg2v_graph *g = x.g;
-  const int64_t nnz = std::max<int64_t>(g->nnz, 1);
-  // the automatic rule of the neighbour-range split: large graphs whose long
-  // tasks hold at least half the entries
-  x.rel_x = 0;
-  if (large_graph(g->n) && g->long_share >= 0.5 && (g->tsplit || !t_noalloc)) {
-    while (x.rel_x < g->n_tasks && g->h_task_len[x.rel_x] >= kXsplitMin) ++x.rel_x;
-    if ((double)x.b * kXsplit * x.rel_x * x.rp.wide_ld * x.es > 4 * kXpartBytes) x.rel_x = 0;
-  }
-  x.rel_items = x.rel_x * kXsplit + g->n_tasks - x.rel_x;
-  const size_t sort_bytes = (size_t)x.b * (nnz * (g->w ? 8 : 4) + x.rel_items * 64) + 256;
-  const size_t part_bytes = (size_t)x.b * kXsplit * x.rel_x * x.rp.wide_ld * x.es + 256;
-  if (Carver *cv = x.ws->arena.cv) {
-    const size_t need = x.rp.arena + x.rp.small_bytes + (size_t)kRootBlocks * x.b * 8 + sort_bytes + part_bytes + 8192;
+  Workspace &ws = *x.ws;
+  WideNeed w = rel_wide_need(g, x.rp, x.b, x.es, g->tsplit || !t_noalloc);
+  if (Carver *cv = ws.arena.cv) {
+    const size_t need = x.rp.arena + x.rp.small_bytes + (size_t)kRootBlocks * x.b * 8 + w.sort + w.part + 8192;
     if (need > cv->cap) {
       x.rel = false;
       return SG2V_OK;
     }
+  } else {
+    size_t fr = 0, tot = 0;
+    (void)hipMemGetInfo(&fr, &tot);
+    const int64_t budget = tuning().budget_bytes;
+    const double most = budget > 0 ? (double)budget : 0.85 * (double)(fr + ws.arena.bytes + ws.relsort.bytes + ws.xpart.bytes);
+    auto fits = [&]() { return (double)x.rp.arena + (double)w.sort + (double)w.part <= most; };
+    // a buffer that cannot grow keeps its size: other templates of a batch may be set
+    // up for it
+    auto grow = [](DevBuf &d, size_t want, bool *ok) -> sg2v_status {
+      const size_t held = d.bytes;
+      if (!*ok) return SG2V_OK;
+      *ok = d.ensure(want) == SG2V_OK;
+      return *ok || held == 0 ? SG2V_OK : d.ensure(held);
+    };
+    if (!fits()) w = rel_wide_need(g, x.rp, x.b, x.es, false);
+    x.rel = fits();
+    ST_TRY(grow(ws.arena, x.rp.arena, &x.rel));
+    if (x.rel && w.x_tasks > 0) {
+      bool ok = true;
+      if (!g->tsplit) {
+        void *q = nullptr;
+        ok = hipMalloc(&q, (size_t)g->n_tasks * (kXsplit + 1) * sizeof(uint16_t)) == hipSuccess;
+        if (ok) {
+          g->tsplit = (uint16_t *)q;
+          launch_task_split(g->col_idx, g->task_beg, g->task_len, g->n_tasks, g->n, kXsplit, g->xbounds, g->tsplit, x.s);
+        }
+        const hipError_t e = hipGetLastError();
+        if (ok) HIP_TRY(e);
+      }
+      ST_TRY(grow(ws.relsort, w.sort, &ok));
+      ST_TRY(grow(ws.xpart, w.part, &ok));
+      if (!ok) w = rel_wide_need(g, x.rp, x.b, x.es, false);
+    }
+    ST_TRY(grow(ws.relsort, w.sort, &x.rel));
+    if (!x.rel) return SG2V_OK;
   }
-  if (x.rel_x > 0 && !g->tsplit) {
-    HIP_TRY(hipMalloc((void **)&g->tsplit, (size_t)g->n_tasks * (kXsplit + 1) * sizeof(uint16_t)));
-    launch_task_split(g->col_idx, g->task_beg, g->task_len, g->n_tasks, g->n, kXsplit, g->xbounds, g->tsplit, x.s);
-    HIP_TRY(hipGetLastError());
-  }
-  ST_TRY(x.ws->relsort.ensure(sort_bytes));
-  return x.ws->xpart.ensure(part_bytes);
+  x.rel_x = w.x_tasks;
+  x.rel_items = w.items;
+  ST_TRY(ws.relsort.ensure(w.sort));
+  return ws.xpart.ensure(w.part);
 }
 
 sg2v_status prepare(Ctx &x, const sg2v_plan *plan, sg2v_graph *g, const sg2v_colorings *c,
@@ -2808,7 +2866,7 @@ sg2v_status count_raw(const sg2v_plan *plan, const sg2v_graph *g, const sg2v_col
   bool device = false;
   for (auto &R : P.roots) device |= R.kind != ROOT_VERTEX;
   if (device) {
-    const int b = choose_batch(P, ncol, dt, g->n, g->n_slots);
+    const int b = choose_batch(P, ncol, dt, g);
     Ctx x;
     ST_TRY(prepare(x, plan, (sg2v_graph *)g, c, mode, b, s, PassOpts()));
     x.res_stride = ncol;
@@ -2987,7 +3045,7 @@ extern "C" sg2v_status sg2v_count_noalloc(const sg2v_plan *plan, const sg2v_grap
     DevBuf *bufs[] = {&ws.arena, &ws.small, &ws.partial, &ws.result, &ws.ovf,
                       &ws.grad,  &ws.bucket, &ws.nbrcol, &ws.xpart, &ws.relsort};
     // colourings per pass: as sg2v_count would take them, halved until the pass fits
-    int b = choose_batch(P, ncol, dt, g->n, g->n_slots);
+    int b = choose_batch(P, ncol, dt, g);
     std::unique_ptr<Ctx> x;
     for (;;) {
       cv.top = 0;
@@ -3284,7 +3342,7 @@ extern "C" sg2v_status sg2v_count_batch(const sg2v_plan *const *plans, int32_t n
   HIP_TRY(hipGetDevice(&dev));
 
   std::vector<int> bs(n_plans);
-  for (int p = 0; p < n_plans; ++p) bs[p] = choose_batch(plans[p]->p, ncol, dt, g->n, g->n_slots);
+  for (int p = 0; p < n_plans; ++p) bs[p] = choose_batch(plans[p]->p, ncol, dt, g);
   // Templates run as parallel branches of the graph, each with a workspace of
   // its own, when those fit in half of the free device memory (estimated from
   // the pass plan of each); otherwise one after another in the shared one.
@@ -3305,6 +3363,12 @@ extern "C" sg2v_status sg2v_count_batch(const sg2v_plan *const *plans, int32_t n
         if (nd.n_passive_uses > 0) widest = std::max(widest, nd.size == 1 ? plans[p]->p.k : nd.cols);
       build_pass(plans[p]->p, g->n, bs[p], dt, pick_G(dt, widest * bs[p], g->n), g->n_slots, pp, PassOpts());
       need += (double)pp.arena + pp.small_bytes + (double)bs[p] * (g->nnz + 4.0 * g->n + 64.0);
+      if (rel_wanted(tune) && has_wide(plans[p]->p) && rel_ok(plans[p]->p, esize_of(dt), kRelLds)) {
+        RelPass rp;
+        build_rel(plans[p]->p, g, bs[p], dt, rp);
+        const WideNeed w = rel_wide_need(g, rp, bs[p], esize_of(dt), true);
+        need += (double)w.sort + (double)w.part;
+      }
     }
     conc = need <= 0.5 * (double)fr;
   }

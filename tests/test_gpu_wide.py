@@ -44,3 +44,50 @@ def test_sorted_entries_by_mean_degree(par, k, side):
             assert f > 0
             assert got[j] == pytest.approx(f, rel=TOL[mode])
             assert full[j] == pytest.approx(f, rel=TOL["fp64"])
+
+
+def ring(n, deg, weighted):
+    """Every vertex and its deg nearest on a ring; weights of 0.5 to 1.5."""
+    d = np.arange(1, deg // 2 + 1)
+    ci = (np.arange(n)[:, None] + np.concatenate([-d, d])) % n
+    w = 0.5 + (ci * np.arange(n)[:, None] % 97) / 96.0 if weighted else None
+    order = np.argsort(ci, axis=1)
+    ci = np.take_along_axis(ci, order, axis=1).astype(np.int32).reshape(-1)
+    if weighted:
+        w = np.take_along_axis(w, order, axis=1).astype(np.float32).reshape(-1)
+    return sg.Graph(n, np.arange(n + 1, dtype=np.int64) * deg, ci, w)
+
+
+def test_budget_counts_the_sorted_entries():
+    """A budget that holds the tables but not the 24 MB of sorted entries beside them:
+    the count runs in absolute tables (whose one-vertex multiply-adds the relative
+    ones do not have), with the same results."""
+    n, deg = 3000, 1000
+    g = ring(n, deg, True)
+    plan = sg.Plan(gg.PATH8, 12)
+    tables = plan.info().bytes_per_vertex_fp32 * n
+    assert tables < 8 * deg * n
+    c = sg.Colorings(g, 12, 4, 3)
+    ref = sg.count(plan, g, c, "fp64")["colorful"]
+    for budget, absolute in ((tables + (2 << 20), True), (0, False)):
+        print("budget", budget, flush=True)
+        with sg.tuned(budget_bytes=budget):
+            sg.profile_start()
+            got = sg.count(plan, g, c, "fp32s")["colorful"]
+            prof = sg.profile_stop()
+        assert (prof["ema_single"]["launches"] > 0) == absolute
+        np.testing.assert_allclose(got, ref, rtol=TOL["fp32s"])
+
+
+@pytest.mark.parametrize("n,deg", [(3700, 8), (7000, 1000)])
+def test_chunks_inside_the_fixed_area(n, deg):
+    """sg2v_count_noalloc: sorted entries beside the tables in the area, and a graph
+    whose 56 MB of sorted entries do not fit there with them (absolute tables)."""
+    g = ring(n, deg, True)
+    plan = sg.Plan(gg.PATH8, 12)
+    c = sg.Colorings(g, 12, 4, 2)
+    print("noalloc, chunks", n, deg, flush=True)
+    ref = sg.count(plan, g, c, "fp64")["colorful"]
+    got = sg.count_noalloc(plan, g, c, "fp32s")["colorful"]
+    assert (np.asarray(ref) > 0).all()
+    np.testing.assert_allclose(got, ref, rtol=TOL["fp32s"])
