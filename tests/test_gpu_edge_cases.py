@@ -87,3 +87,30 @@ def test_many_colourings_of_a_chunked_aggregation(tuned):
     f = [float(x) for x in ref]
     np.testing.assert_allclose(got["fp64"]["colorful"], f, rtol=1e-12)
     np.testing.assert_allclose(got["fp32s"]["colorful"], f, rtol=1e-5)
+
+
+@pytest.mark.parametrize("deg", [254, 256, 1030])
+def test_rows_long_like_the_others_and_longer(deg):
+    """Graphs whose rows all have about as many entries as a long row (one wave each),
+    with a hub of twice their mean and more (whole blocks, two segments at 1030)."""
+    n = 2 * deg + 100
+    d = np.arange(1, deg // 2 + 1)
+    e = {(i, int(j)) for i in range(n) for j in (i + d) % n}
+    e |= {(0, j) for j in range(1, n)}
+    G = gg.from_edge_list(n, sorted({(min(x), max(x)) for x in e}), None)
+    g = sg.Graph.from_csr(G)
+    Gw = gg.Graph(n, G.row_ptr, G.col_idx, (1.0 + (G.col_idx + np.repeat(np.arange(n), np.diff(G.row_ptr))) % 7).astype(np.float32))
+    gw = sg.Graph.from_csr(Gw)
+    for par, k in (([-1, 0, 1], 3), (gg.PATH5, 5), (gg.PATH8, 9)):
+        plan = sg.Plan(par, k)
+        c = sg.Colorings(g, k, 2, 2)
+        say("rows of", deg, par, k)
+        u = sg.count(plan, g, c, "u64")["colorful_u64"]
+        f = sg.count(plan, gw, sg.Colorings(gw, k, 2, 2), "fp32s")["colorful"]
+        h = sg.count_grad(plan, gw, sg.Colorings(gw, k, 2, 1), [1.0], "fp64").cpu().numpy()
+        for j in range(2):
+            col = O.colors(n, k, 2, j)
+            assert int(u[j]) == O.count(G, par, k, col, mode=O.U64)[1] > 0
+            assert f[j] == pytest.approx(O.count(Gw, par, k, col)[0], rel=1e-5)
+        ref = O.grad(Gw, par, k, O.colors(n, k, 2, 0))[1]
+        np.testing.assert_allclose(h, ref, rtol=1e-10, atol=1e-10 * np.abs(ref).max())
