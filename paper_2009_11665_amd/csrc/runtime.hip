@@ -1113,6 +1113,7 @@ int pick_G(int dt, int64_t widest_cols_b, int64_t n) {
 struct PassOpts {
   std::vector<std::pair<int, int>> keep;  // (node, 0: M / 1: B) kept to the end of the pass
   bool no_fuse = false;                   // materialise every non-root table
+  bool adjoint = false;                   // relative tables wherever the plan has them
 };
 
 // greedy placement: largest first, lowest offset free over the lifetime;
@@ -2626,6 +2627,79 @@ bool has_wide(const Plan &P) {
   return false;
 }
 
+// Colourings of a pass in absolute tables, where they are columns side by side.
+int64_t abs_batch(const Plan &P) {
+  int64_t widest = 1;
+  for (auto &nd : P.nodes)
+    if (nd.n_passive_uses > 0) widest = std::max(widest, nd.size == 1 ? P.k : nd.cols);
+  return std::max<int64_t>(1, 1024 / widest);
+}
+
+// Which tables count ncol colourings in less time.  A gathered row of a relative table
+// is one colouring's: a 128-byte line and an LDS pass per entry, colouring and
+// aggregation, however few columns it has.  In absolute tables the colourings of a pass
+// share the lines, but every row of every 128-byte column chunk has a fixed cost.  So
+// few columns, many colourings and a high degree favour the absolute ones: path of 5
+// with 5 colours, 24 colourings of 65,536 vertices, FP32: degree 4 2.2 over 0.6 ms
+// (absolute over relative), degree 256 6.5 over 21.3.  The estimates, in microseconds,
+// are a fit of the whole calls' times on the MI355X over 10,360 calls (1024 to 262,144
+// vertices, uniform, RMAT, Chung-Lu and ring graphs, degree 4 to 1500, nine trees, 1 to
+// 600 colourings); the relative tables' own constants come first, then the absolute
+// ones'.  They are off by a fifth to a third, so a tenth is asked of the relative
+// tables.  Of the calls of over 150 us, 139 then take over 5% longer than in absolute
+// tables, 0.6 times as fast at worst (906 and 0.22 in relative ones throughout); the mean
+// is 2.08 times faster than absolute ones throughout (2.02 relative ones).  Plans with
+// chunked aggregations were faster in relative tables at every degree measured (4 to
+// 260: 1.2 to 6 times).
+struct TableCost {
+  double rcall, ragg;                           // per call and aggregation
+  double rent, rentcol, rentw, rent1;           // ps per entry and colouring: aggregation, column, weight, histogram
+  double rcol, rrow, rpair;                     // ps per row and colouring: gathered column, row, pair
+  double acall, aagg, achunk;                   // per call, aggregation and pass, column chunk
+  double along, alongw;                         // ns per aggregation, pass and entry of the longest task
+  double achline, achlinew, achent, aent1;      // ps per entry: chunk of 128 bytes, its weights, chunk; colouring
+  double achrow, achrowline, arow, apair;       // ps per row: chunk, 128 bytes of it; row and pair of a colouring
+};
+constexpr TableCost kCost32 = {110, 16, 14, 0.34, 2.7, 0, 3.3, 82, 0.76, 140, 81, 3.5, 12, 7.2, 5.2, 3.8, 3.5, 4.3, 770, 0, 100, 1.9};
+constexpr TableCost kCost64 = {84, 13, 7.6, 0.75, 1.6, 2.7, 5.5, 51, 1.2, 130, 5.8, 0.48, 9.6, 11, 6.5, 3.5, 0, 4.8, 190, 140, 110, 2.2};
+
+bool rel_faster(const Plan &P, const sg2v_graph *g, int dt, int ncol) {
+  if (has_wide(P)) return true;
+  const sg2v_tuning_t tu = tuning();
+  const TableCost &t = dt == DT_F32 ? kCost32 : kCost64;
+  const int N = 16 / esize_of(dt), k = P.k;
+  const int64_t most = abs_batch(P);
+  const int64_t b = std::max<int64_t>(1, std::min<int64_t>(ncol, tu.batch > 0 ? tu.batch : most));
+  const int G = pick_G(dt, 1024 / most * b, g->n);
+  const int64_t full = ncol / b, rest = ncol % b;
+  double agg = 0, cols = 0, chunks = 0, apairs = 0, rpairs = 0;
+  for (auto &nd : P.nodes) {
+    if (nd.size == 1) continue;
+    if (nd.n_passive_uses > 0) {
+      agg += 1;
+      cols += (double)binom(k - 1, nd.size - 1);
+      chunks += (double)(full * ((nd.cols * b + G * N - 1) / (G * N)) + (nd.cols * rest + G * N - 1) / (G * N));
+    }
+    const int ma = P.nodes[nd.active].size;
+    if (ma == 1) continue;
+    apairs += (double)binom(k, nd.size) * binom(nd.size, ma);
+    rpairs += (double)binom(k - 1, nd.size - 1) * binom(nd.size - 1, ma - 1);
+  }
+  // No aggregation: without pairs either, only the neighbour colours are counted (one
+  // edge, 24 colourings of 65,536 vertices, FP64: degree 16 234 over 162 us, 256 equal,
+  // 50,000 of degree 1100 1.2 over 1.9 ms; with weights 65,536 of degree 64 equal; 1500
+  // of degree 1400, 600 colourings 3.3 over 1.9).
+  if (agg == 0) return apairs > 0 || g->n < 4096 || g->nnz < (g->w ? 64 : 256) * g->n;
+  const double n = (double)g->n, nnz = (double)g->nnz, c = ncol, w = g->w ? 1.0 : 0.0, line = G / 8.0;
+  const double passes = (double)(full + (rest > 0)), longest = g->n_tasks > 0 ? g->h_task_len[0] : 0;
+  const double rel = t.rcall + t.ragg * agg + 1e-6 * (nnz * c * ((t.rent + w * t.rentw) * agg + t.rentcol * cols + t.rent1) +
+                                                      n * c * (t.rcol * cols + t.rrow + t.rpair * rpairs));
+  const double abs = t.acall + t.aagg * agg * passes + t.achunk * chunks + 1e-3 * agg * passes * longest * (t.along + w * t.alongw) +
+                     1e-6 * (nnz * (chunks * (line * (t.achline + w * t.achlinew) + t.achent) + c * t.aent1) +
+                             n * (chunks * (t.achrow + line * t.achrowline) + c * (t.arow + t.apair * apairs)));
+  return 1.1 * rel < abs;
+}
+
 int choose_batch(const Plan &P, int ncol, int dt, const sg2v_graph *g) {
   sg2v_tuning_t tu = tuning();
   const int64_t n = g->n;
@@ -2633,8 +2707,8 @@ int choose_batch(const Plan &P, int ncol, int dt, const sg2v_graph *g) {
   int64_t widest_passive = 1;
   for (auto &nd : P.nodes)
     if (nd.n_passive_uses > 0) widest_passive = std::max(widest_passive, nd.size == 1 ? P.k : nd.cols);
-  int64_t most = std::max<int64_t>(1, 1024 / widest_passive);
-  const bool rel = rel_wanted(tu) && rel_ok(P, es, kRelLds);
+  int64_t most = abs_batch(P);
+  const bool rel = rel_wanted(tu) && rel_ok(P, es, kRelLds) && rel_faster(P, g, dt, ncol);
   if (rel) {
     most = std::min(most, std::max<int64_t>(1, kRelRowsMost / n));
     if (widest_passive <= 1024) most = std::max(most, kRelRowsLeast / n);
@@ -2757,7 +2831,8 @@ sg2v_status prepare(Ctx &x, const sg2v_plan *plan, sg2v_graph *g, const sg2v_col
   // above; where the partial rows of long rows make them larger, they are not
   // used.
   x.rel = false;
-  if (opt.keep.empty() && !opt.no_fuse && rel_wanted(tu) && rel_ok(plan->p, x.es, std::min(kRelLds, x.lds_max))) {
+  if (opt.keep.empty() && !opt.no_fuse && rel_wanted(tu) && rel_ok(plan->p, x.es, std::min(kRelLds, x.lds_max)) &&
+      (opt.adjoint || rel_faster(plan->p, g, x.dt, c->count))) {
     build_rel(plan->p, g, b, x.dt, x.rp);
     x.rel = x.rp.arena <= std::max<int64_t>(x.pp.arena, (int64_t)1 << 20) && x.rp.small_bytes <= x.pp.small_bytes + 4096;
   }
@@ -3680,9 +3755,10 @@ sg2v_status rel_grad(const sg2v_plan *plan, sg2v_graph *g, const sg2v_colorings 
   *done = false;
   Ctx x;
   // device properties, plan tables and the shared small buffers
-  PassOpts none;
+  PassOpts opt;
+  opt.adjoint = true;
   if (!rel_wanted(tu) || !rel_grad_ok(P, es, kRelLds)) return SG2V_OK;
-  ST_TRY(prepare(x, plan, g, c, mode, 1, s, none));
+  ST_TRY(prepare(x, plan, g, c, mode, 1, s, opt));
   if (!x.rel || x.lds_max < kRelLds) return SG2V_OK;
   bool ok = false;
   ST_TRY(graph_rev(g, x.ovf, s, &ok));

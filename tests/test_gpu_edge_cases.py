@@ -114,3 +114,27 @@ def test_rows_long_like_the_others_and_longer(deg):
             assert f[j] == pytest.approx(O.count(Gw, par, k, col)[0], rel=1e-5)
         ref = O.grad(Gw, par, k, O.colors(n, k, 2, 0))[1]
         np.testing.assert_allclose(h, ref, rtol=1e-10, atol=1e-10 * np.abs(ref).max())
+
+
+@pytest.mark.parametrize("deg,ncol,absolute", [(4, 24, False), (256, 24, True), (256, 1, False)])
+@pytest.mark.parametrize("mode", ["u64", "fp64", "fp32s"])
+def test_tables_by_estimated_time(deg, ncol, absolute, mode):
+    """Path of 5 on a uniform graph of 6000 vertices: few columns, many colourings and
+    a high degree run in absolute tables (which have one-vertex multiply-adds), the
+    others in relative ones; counts do not depend on it."""
+    n = 6000
+    G = gg.csr(n, *gg.er_edges(n, n * deg // 2, 5))
+    g = sg.Graph.from_csr(G)
+    plan = sg.Plan(gg.PATH5, 5)
+    c = sg.Colorings(g, 5, 2, ncol)
+    say("tables by time", deg, ncol, mode)
+    sg.profile_start()
+    r = sg.count(plan, g, c, mode)
+    prof = sg.profile_stop()
+    assert (prof["ema_single"]["launches"] > 0) == absolute
+    for j in (0, ncol - 1):
+        f, u, _ = O.count(G, gg.PATH5, 5, O.colors(n, 5, 2, j), mode=O.U64 if mode == "u64" else O.FP64)
+        if mode == "u64":
+            assert int(r["colorful_u64"][j]) == u
+        else:
+            assert r["colorful"][j] == pytest.approx(f, rel={"fp64": 1e-12, "fp32s": 1e-5}[mode])
