@@ -2596,6 +2596,9 @@ sg2v_status check_inputs(const sg2v_plan *plan, const sg2v_graph *g, const sg2v_
   return SG2V_OK;
 }
 
+// Not a public flag: absolute tables, for the tuner's timing of their settings.
+constexpr int32_t kTuneAbsolute = 1 << 30;
+
 // Flags that ask for kernels or layouts of the absolute tables keep them; the
 // widths, tile rows and split sizes of the tuning apply to those only.
 bool rel_wanted(const sg2v_tuning_t &t) {
@@ -4636,8 +4639,10 @@ std::map<std::string, sg2v_tuning_t> g_autotune;
 
 std::string tune_key(const Plan &P, const sg2v_graph *g, sg2v_mode mode, int ncol) {
   std::ostringstream k;
+  // t2: settings found when counts without flags run in vertex-relative tables; a
+  // file's earlier ones may hold flags that would keep a caller off those
   k << P.nodes[P.root].canon << "/k" << P.k << "/n" << g->n << "/nnz" << g->nnz << "/m" << mode
-    << "/c" << ncol;
+    << "/c" << ncol << "/t2";
   return k.str();
 }
 
@@ -4725,8 +4730,8 @@ extern "C" sg2v_status sg2v_autotune(const sg2v_plan *plan, const sg2v_graph *g,
     ST_TRY(sg2v_set_tuning(&base));
     cand.swap(uniq);
   }
-  sg2v_tuning_t best = base;
-  double best_ms = 1e300;
+  sg2v_tuning_t best = base, plain = base;  // fastest, and fastest without flags in absolute tables
+  double best_ms = 1e300, plain_ms = 1e300;
   // one untimed count, then the median of three timed ones; a candidate whose
   // untimed count takes over three times the best median so far is dropped
   auto time_one = [&](const sg2v_tuning_t &t, double *ms) -> sg2v_status {
@@ -4749,30 +4754,66 @@ extern "C" sg2v_status sg2v_autotune(const sg2v_plan *plan, const sg2v_graph *g,
     *ms = v[1];
     return SG2V_OK;
   };
+  // Widths and rows are settings of the absolute tables.  Where a count without flags
+  // runs in relative ones they are timed in absolute tables all the same, as other calls
+  // use them (the persistent schedule, flags set by hand).
+  sg2v_tuning_t rel_t = base;
+  rel_t.flags &= ~skipfl;
+  const int es = esize_of(dtype_of(mode));
+  const bool rel = rel_wanted(rel_t) && rel_ok(plan->p, es, kRelLds) && rel_faster(plan->p, g, dtype_of(mode), n_colorings);
   sg2v_status st = SG2V_OK;
-  for (auto &t : cand) {
-    double ms;
-    if ((st = time_one(t, &ms)) != SG2V_OK) break;
-    if (ms < best_ms) {
-      best_ms = ms;
-      best = t;
+  {
+    TuneOr forced(rel ? kTuneAbsolute : 0);
+    for (auto &t : cand) {
+      double ms;
+      if ((st = time_one(t, &ms)) != SG2V_OK) break;
+      const bool flagged = (t.flags & skipfl) != 0;
+      if ((flagged || !rel) && ms < best_ms) {  // without flags the relative tables run
+        best_ms = ms;
+        best = t;
+      }
+      if (!flagged && ms < plain_ms) {
+        plain_ms = ms;
+        plain = t;
+      }
+    }
+  }
+  bool rel_best = false;
+  double rel_ms = 0;
+  if (st == SG2V_OK && rel) {
+    st = time_one(rel_t, &rel_ms);
+    rel_best = rel_ms <= best_ms;
+    if (rel_best) {
+      best = plain;
+      best_ms = plain_ms;
     }
   }
   if (st == SG2V_OK) {
-    // then rows per eMA tile and colourings per pass around the best width
-    std::vector<sg2v_tuning_t> more;
+    // then rows per eMA tile around the best width
+    TuneOr forced(rel ? kTuneAbsolute : 0);
+    const sg2v_tuning_t around = best;
     for (int r : rows) {
-      sg2v_tuning_t t = best;
+      sg2v_tuning_t t = around;
       t.ema_rows = r;
-      more.push_back(t);
+      double ms;
+      if ((st = time_one(t, &ms)) != SG2V_OK) break;
+      if (ms < best_ms) {
+        best_ms = ms;
+        best = t;
+      }
     }
+  }
+  if (st == SG2V_OK) {
+    // and colourings per pass, in the tables of the choice; in relative ones the
+    // automatic number is kept unless another is faster by a twentieth, as it is
+    // another in the calls that run in absolute tables
+    TuneOr forced(rel && !rel_best ? kTuneAbsolute : 0);
+    const sg2v_tuning_t around = best;
+    if (rel_best) best_ms = 0.95 * rel_ms;
     for (int b : {1, 2, 4}) {
       if (b > n_colorings) break;
-      sg2v_tuning_t t = best;
+      sg2v_tuning_t t = around;
       t.batch = b;
-      more.push_back(t);
-    }
-    for (auto &t : more) {
       double ms;
       if ((st = time_one(t, &ms)) != SG2V_OK) break;
       if (ms < best_ms) {
