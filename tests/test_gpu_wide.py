@@ -91,3 +91,94 @@ def test_chunks_inside_the_fixed_area(n, deg):
     got = sg.count_noalloc(plan, g, c, "fp32s")["colorful"]
     assert (np.asarray(ref) > 0).all()
     np.testing.assert_allclose(got, ref, rtol=TOL["fp32s"])
+
+
+@pytest.mark.parametrize("weighted", [False, True])
+def test_last_pass_of_fewer_colourings_sorts_again(weighted):
+    n = 900
+    G = random_graph(n, 12, 4, weighted)
+    g = sg.Graph.from_csr(G)
+    plan = sg.Plan(gg.PATH8, 12)
+    c = sg.Colorings(g, 12, 6, 6)
+    with sg.tuned(batch=4):
+        for mode in ("fp64", "fp32s") + (() if weighted else ("u64",)):
+            print("partial pass, chunks", weighted, mode, flush=True)
+            r = sg.count(plan, g, c, mode)
+            for j in range(6):
+                f, u, _ = O.count(G, gg.PATH8, 12, O.colors(n, 12, 6, j), mode=O.U64 if mode == "u64" else O.FP64)
+                if mode == "u64":
+                    assert int(r["colorful_u64"][j]) == u
+                else:
+                    assert r["colorful"][j] == pytest.approx(f, rel=TOL[mode])
+
+
+@pytest.mark.parametrize("flags", [0, 512])
+def test_chunks_recorded_in_a_batch(flags):
+    """Sorting and chunked aggregations inside the recorded graph, templates as parallel
+    branches and one after another, replayed with eager work in between."""
+    G = random_graph(2000, 10, 8)
+    g = sg.Graph.from_csr(G)
+    plans = [sg.Plan(gg.PATH8, 12), sg.Plan(gg.BINTREE7, 7), sg.Plan(CAT12, 13)]
+    with sg.tuned(flags=flags):
+        for mode in ("u64", "fp32s"):
+            first = None
+            for rep in range(3):
+                print("batch, chunks", flags, mode, rep, flush=True)
+                cf, _ = sg.count_batch(plans, g, 5, 3, mode)
+                first = cf if first is None else first
+                np.testing.assert_array_equal(cf, first)
+                sg.count(plans[2], g, sg.Colorings(g, 13, 40 + rep, 2), mode)
+            for p, plan in enumerate(plans):
+                ref = sg.count(plan, g, sg.Colorings(g, plan.k, 5, 3), "fp64")["colorful"]
+                np.testing.assert_allclose(first[p], ref, rtol=TOL["fp32s"])
+
+
+def test_neighbour_ranges_with_weights():
+    """Long tasks taken once per neighbour range, their weights with them."""
+    G = gg.rmat(18, 25_000_000, seed=5)
+    rows = np.repeat(np.arange(G.n, dtype=np.int64), np.diff(G.row_ptr))
+    G.w = (0.5 + ((rows + G.col_idx) * 2654435761 % 997) / 996.0).astype(np.float32)
+    plan = sg.Plan(gg.PATH8, 12)
+    for relabel in (False, True):
+        g = sg.Graph.from_csr(G, relabel=relabel)
+        c = sg.Colorings(g, 12, 2, 1)
+        print("ranges with weights", relabel, flush=True)
+        f64 = sg.count(plan, g, c, "fp64")["colorful"][0]
+        f32 = sg.count(plan, g, c, "fp32s")["colorful"][0]
+        with sg.tuned(flags=sg.TUNE_NO_COLOR_SKIP):
+            ref = sg.count(plan, g, c, "fp64")["colorful"][0]
+        assert ref > 0
+        assert f64 == pytest.approx(ref, rel=2 * TOL["fp64"])
+        assert f32 == pytest.approx(ref, rel=TOL["fp32s"])
+
+
+def core(size, n):
+    """A complete graph of `size` vertices among n."""
+    ci = np.broadcast_to(np.arange(size, dtype=np.int32), (size, size))[~np.eye(size, dtype=bool)]
+    rp = np.minimum(np.arange(n + 1, dtype=np.int64), size) * (size - 1)
+    return gg.Graph(n, rp, np.ascontiguousarray(ci), None)
+
+
+@pytest.mark.parametrize("par,k,large,small,n", [
+    ([-1] + [0] * 7, 8, 3000, 300, 200_000),           # the root's products
+    ([-1] + [0] * 8, 9, 3000, 200, 200_000),           # a multiply-add before it
+    (gg.PATH8, 8, 3000, 300, 250_000),                 # LDS sums of 8 sets
+    ([-1] + list(range(9)), 10, 1750, 150, 150_000),   # staged rows of 120 sets
+    ([-1] + list(range(11)), 12, 1000, 80, 1000),      # chunks
+])
+def test_sums_past_2_to_64_are_flagged(par, k, large, small, n):
+    """Counts of a complete graph's vertices whose tables pass 2^64, and of a smaller
+    one's whose do not; the isolated others make relative tables the faster ones."""
+    plan = sg.Plan(par, k)
+    for size in (large, small):
+        G = core(size, n)
+        g = sg.Graph.from_csr(G)
+        c = sg.Colorings(g, k, 1, 1)
+        _, u, over = O.count(G, par, k, O.colors(n, k, 1, 0), mode=O.U64)
+        assert over == (size == large)
+        print("overflow", par, k, size, flush=True)
+        sg.profile_start()
+        r = sg.count(plan, g, c, "u64")
+        assert sg.profile_stop()["ema_single"]["launches"] == 0
+        assert int(r["colorful_u64"][0]) == u
+        assert r["overflow"] == over
