@@ -81,6 +81,8 @@ struct RootInfo {
   std::vector<int32_t> parent; // the template as given
 };
 
+constexpr size_t kRelLds = 64 * 1024;  // LDS of a vertex-relative multiply-add tile
+
 struct Plan {
   // The first (or only) template: t, parent, root, alpha, P and the root_*
   // fields below describe it.  A plan of several templates (treelet
@@ -103,6 +105,9 @@ struct Plan {
   std::vector<char> fused;
   std::vector<RootInfo> roots;   // one per template, roots[0] = the fields above
   std::vector<int> root_index;   // per node: index into roots, or -1
+  // rel_ok for tables of 4-byte and of 8-byte elements with tiles of kRelLds, and
+  // whether some aggregation goes in chunks: asked on every call
+  bool rel32 = false, rel64 = false, any_wide = false;
 
   // device copies of the tables, uploaded on first use per device
   struct DeviceTables {
@@ -177,6 +182,7 @@ void rel_wide_nodes(const Plan &P, std::vector<char> &wide_m, std::vector<char> 
 // whether every table of the plan has a vertex-relative form, with elements of
 // es bytes and multiply-add tiles of at most `lds` bytes
 bool rel_ok(const Plan &P, int es, size_t lds);
+inline bool rel_ok(const Plan &P, int es) { return es == 4 ? P.rel32 : P.rel64; }  // tiles of kRelLds
 // maps of the aggregation of an m-vertex passive child, m >= 2, not wide
 RelMap rel_map(int k, int m);
 // pairs [np][ws] (x | y << 16) of a split (m vertices, ma of them active, 1 < ma < m)
@@ -190,7 +196,7 @@ std::vector<uint32_t> rel_root_list(int k, int t, int ma, const RelLayout &X, co
 RelMap rel_map_back(int k, int m);
 std::vector<uint32_t> rel_pairs_back(int k, int m, int ma, bool active);
 // whether the adjoint of the plan runs in vertex-relative tables
-bool rel_grad_ok(const Plan &P, int es, size_t lds);
+bool rel_grad_ok(const Plan &P, int es);
 
 sg2v_status plan_build(const int32_t *parent, int t, int k, Plan &out);
 // Several templates over the same k, sharing isomorphic rooted sub-templates.

@@ -527,7 +527,6 @@ struct RelHistBackArgs {
   double *grad;
   double scale;
   const int *e;
-  const unsigned *mx;
   int32_t R, tlong;
   const int32_t *seg_row, *seg_len;
   const int64_t *seg_beg;

@@ -492,6 +492,9 @@ sg2v_status plan_build_multi(const int32_t *const *parents, const int32_t *ts, i
   P->root_list = R0.list;
   P->alpha = R0.alpha;
   P->P = R0.P;
+  for (auto &nd : P->nodes) P->any_wide |= nd.n_passive_uses > 0 && rel_wide(k, nd.size);
+  P->rel32 = rel_ok(*P, 4, kRelLds);
+  P->rel64 = rel_ok(*P, 8, kRelLds);
   return SG2V_OK;
 }
 
@@ -644,12 +647,16 @@ bool rel_ok(const Plan &P, int es, size_t lds) {
     const int ma = A.size, mp = P.nodes[nd.passive].size;
     // columns fit 16 bits; the pair lists stay below 2^26 entries
     const int64_t ws = binom(P.k - 1, nd.size - 1), wp = binom(P.k - 1, mp), wx = binom(P.k - 1, ma - 1);
-    // a table gathered in chunks pads each choice of high colours to whole lines:
-    // with many small ones the absolute table's chunks move less
-    if (wb[q] && rel_layout(P.k, nd.size, true).width * 5 > binom(P.k - 1, nd.size) * 8) return false;
-    if (wm[q] && rel_layout(P.k, nd.size - 1, true).width * 5 > binom(P.k - 1, nd.size - 1) * 8) return false;
     if (ws > 40000 || wp > 40000 || wx > 40000 || (double)ws * binom(nd.size - 1, ma - 1) > (double)(1 << 26))
       return false;
+    // A table gathered in chunks pads each choice of high colours to whole lines; with
+    // many small ones the absolute table's chunks move less.  Wider by the padding, and
+    // absolute over relative time of the count: 1.55 times (path of 12, k = 12) 1.2 to
+    // 4.5; 2.35 times (path of 10, k = 14) 0.9 (FP32, 300,000 vertices of degree 30) to
+    // 2.8 (65,536 of degree 4); 7 times (binary tree of 7, k = 16) 1.0 to 1.3; 8.9 times
+    // (path of 5, k = 18) 0.07 to 0.45.  The line is where no measured plan loses.
+    if (wb[q] && rel_layout(P.k, nd.size, true).width * 5 > binom(P.k - 1, nd.size) * 8) return false;
+    if (wm[q] && rel_layout(P.k, nd.size - 1, true).width * 5 > binom(P.k - 1, nd.size - 1) * 8) return false;
     if (ma == 1) continue;
     const bool xw = P.nodes[A.active >= 0 ? A.active : 0].size == 1 ? wb[A.passive] : wm[nd.active];
     const int64_t wa = rel_layout(P.k, ma - 1, xw).width, wy = rel_layout(P.k, mp, wb[nd.passive]).width;
@@ -767,8 +774,9 @@ std::vector<uint32_t> rel_pairs_back(int k, int m, int ma, bool active) {
   return out;
 }
 
-bool rel_grad_ok(const Plan &P, int es, size_t lds) {
-  if (P.roots.size() != 1 || P.root_kind == ROOT_VERTEX || !rel_ok(P, es, lds)) return false;
+bool rel_grad_ok(const Plan &P, int es) {
+  const size_t lds = kRelLds;
+  if (P.roots.size() != 1 || P.root_kind == ROOT_VERTEX || !rel_ok(P, es)) return false;
   const int pad = 16 / es;
   for (size_t q = 0; q < P.nodes.size(); ++q) {
     const Node &nd = P.nodes[q];

@@ -15,7 +15,7 @@
 namespace sg2v {
 
 // Reverse entry of every entry: a binary search in the (sorted) row of its
-// neighbour.  A wave takes eight rows, or one long one with stride.
+// neighbour.  A lane takes an entry, whose row it searches first.
 __global__ void __launch_bounds__(BLOCK) k_rel_rev(RelRevArgs a) {
   const int lane = threadIdx.x & (WAVE - 1);
   const int64_t wave = ((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE;

@@ -108,8 +108,6 @@ int64_t fl_launch_chunks() {
   return tu.launch_chunks > 0 ? std::min<int64_t>(tu.launch_chunks, 65535) : 65535;
 }
 
-constexpr size_t kRelLds = 64 * 1024;  // LDS of a vertex-relative multiply-add tile
-
 int dtype_of(sg2v_mode m) { return m == SG2V_FP32S ? DT_F32 : (m == SG2V_FP64 ? DT_F64 : DT_U64); }
 int esize_of(int dt) { return dt == DT_F32 ? 4 : 8; }
 
@@ -1032,14 +1030,12 @@ sg2v_status plan_device(const Plan &P, int device, hipStream_t s, DevPlan *out) 
     }
     if (fits) pk.add(std::move(l16), &D.root_list16[r]);
   }
-  if (rel_ok(P, 4, kRelLds)) {
+  if (rel_ok(P, 4)) {
     for (auto *v : {&D.rel_pairs, &D.rel_map, &D.rel_mpos, &D.rel_bpos, &D.rel_tab, &D.rel_hdr, &D.rel_info})
       v->assign(nn, nullptr);
     D.rel_root.assign(P.roots.size(), nullptr);
     std::vector<char> wm, wb;
     rel_wide_nodes(P, wm, wb);
-    bool any_wide = false;
-    for (auto &nd : P.nodes) any_wide |= nd.n_passive_uses > 0 && rel_wide(P.k, nd.size);
     auto u16 = [](const std::vector<int32_t> &x) { return std::vector<uint16_t>(x.begin(), x.end()); };
     auto lay_b = [&](int p) { return rel_layout(P.k, P.nodes[p].size, wb[p]); };
     auto lay_m = [&](int q) {
@@ -1052,7 +1048,7 @@ sg2v_status plan_device(const Plan &P, int device, hipStream_t s, DevPlan *out) 
       if (wb[i]) pk.add(u16(lay_b((int)i).pos), &D.rel_bpos[i]);
       if (wm[i]) pk.add(u16(lay_m((int)i).pos), &D.rel_mpos[i]);
       if (nd.size == 1) continue;
-      if (nd.n_passive_uses > 0 && (rel_wide(P.k, nd.size) || (any_wide && !wb[i] && rel_sorted(P.k, nd.size)))) {
+      if (nd.n_passive_uses > 0 && (rel_wide(P.k, nd.size) || (P.any_wide && !wb[i] && rel_sorted(P.k, nd.size)))) {
         RelWide w = rel_wide_tables(P.k, nd.size, wb[i]);
         pk.add(std::move(w.hdr), &D.rel_hdr[i]);
         pk.add(std::move(w.info), &D.rel_info[i]);
@@ -2563,7 +2559,7 @@ sg2v_status run_rel(Ctx &x, void *result, int *Eout, int stop = INT_MAX) {
     switch (st.kind) {
       case S_HIST: ST_TRY(rel_hist(x, st.node)); break;
       case S_SPMM: ST_TRY(rel_spmm(x, st.node)); break;
-      case S_EMA_SINGLE: break;  // the passive child's aggregation is its table
+      case S_EMA_SINGLE: break;  // never a step here: the passive child's aggregation is the table
       case S_EMA_GENERAL: ST_TRY(rel_ema(x, st.node)); break;
       case S_ROOT: ST_TRY(rel_root(x, st.node, result, Eout)); break;
     }
@@ -2652,12 +2648,6 @@ WideNeed rel_wide_need(const sg2v_graph *g, const RelPass &rp, int b, int es, bo
   return w;
 }
 
-bool has_wide(const Plan &P) {
-  for (auto &nd : P.nodes)
-    if (nd.n_passive_uses > 0 && rel_wide(P.k, nd.size)) return true;
-  return false;
-}
-
 // Colourings of a pass in absolute tables, where they are columns side by side.
 int64_t abs_batch(const Plan &P) {
   int64_t widest = 1;
@@ -2695,7 +2685,7 @@ constexpr TableCost kCost32 = {110, 16, 14, 0.34, 2.7, 0, 3.3, 82, 0.76, 140, 81
 constexpr TableCost kCost64 = {84, 13, 7.6, 0.75, 1.6, 2.7, 5.5, 51, 1.2, 130, 5.8, 0.48, 9.6, 11, 6.5, 3.5, 0, 4.8, 190, 140, 110, 2.2};
 
 bool rel_faster(const Plan &P, const sg2v_graph *g, int dt, int ncol) {
-  if (has_wide(P)) return true;
+  if (P.any_wide) return true;
   const sg2v_tuning_t tu = tuning();
   const TableCost &t = dt == DT_F32 ? kCost32 : kCost64;
   const int N = 16 / esize_of(dt), k = P.k;
@@ -2739,7 +2729,7 @@ int choose_batch(const Plan &P, int ncol, int dt, const sg2v_graph *g) {
   for (auto &nd : P.nodes)
     if (nd.n_passive_uses > 0) widest_passive = std::max(widest_passive, nd.size == 1 ? P.k : nd.cols);
   int64_t most = abs_batch(P);
-  const bool rel = rel_wanted(tu) && rel_ok(P, es, kRelLds) && rel_faster(P, g, dt, ncol);
+  const bool rel = rel_wanted(tu) && rel_ok(P, es) && rel_faster(P, g, dt, ncol);
   if (rel) {
     most = std::min(most, std::max<int64_t>(1, kRelRowsMost / n));
     if (widest_passive <= 1024) most = std::max(most, kRelRowsLeast / n);
@@ -2754,7 +2744,7 @@ int choose_batch(const Plan &P, int ncol, int dt, const sg2v_graph *g) {
     PassPlan pp;
     build_pass(P, n, b, dt, pick_G(dt, widest_passive * b, n), g->n_slots, pp, PassOpts());
     bool fits = pp.arena <= budget;
-    if (fits && rel && has_wide(P)) {
+    if (fits && rel && P.any_wide) {
       RelPass rp;
       build_rel(P, g, b, dt, rp);
       fits = rp.arena + (int64_t)rel_wide_need(g, rp, b, es, false).sort <= budget;
@@ -2862,7 +2852,7 @@ sg2v_status prepare(Ctx &x, const sg2v_plan *plan, sg2v_graph *g, const sg2v_col
   // above; where the partial rows of long rows make them larger, they are not
   // used.
   x.rel = false;
-  if (opt.keep.empty() && !opt.no_fuse && rel_wanted(tu) && rel_ok(plan->p, x.es, std::min(kRelLds, x.lds_max)) &&
+  if (opt.keep.empty() && !opt.no_fuse && rel_wanted(tu) && (x.lds_max >= kRelLds ? rel_ok(plan->p, x.es) : rel_ok(plan->p, x.es, x.lds_max)) &&
       (opt.adjoint || rel_faster(plan->p, g, x.dt, c->count))) {
     build_rel(plan->p, g, b, x.dt, x.rp);
     x.rel = x.rp.arena <= std::max<int64_t>(x.pp.arena, (int64_t)1 << 20) && x.rp.small_bytes <= x.pp.small_bytes + 4096;
@@ -3483,7 +3473,7 @@ extern "C" sg2v_status sg2v_count_batch(const sg2v_plan *const *plans, int32_t n
         if (nd.n_passive_uses > 0) widest = std::max(widest, nd.size == 1 ? plans[p]->p.k : nd.cols);
       build_pass(plans[p]->p, g->n, bs[p], dt, pick_G(dt, widest * bs[p], g->n), g->n_slots, pp, PassOpts());
       need += (double)pp.arena + pp.small_bytes + (double)bs[p] * (g->nnz + 4.0 * g->n + 64.0);
-      if (rel_wanted(tune) && has_wide(plans[p]->p) && rel_ok(plans[p]->p, esize_of(dt), kRelLds)) {
+      if (rel_wanted(tune) && plans[p]->p.any_wide && rel_ok(plans[p]->p, esize_of(dt))) {
         RelPass rp;
         build_rel(plans[p]->p, g, bs[p], dt, rp);
         const WideNeed w = rel_wide_need(g, rp, bs[p], esize_of(dt), true);
@@ -3788,7 +3778,7 @@ sg2v_status rel_grad(const sg2v_plan *plan, sg2v_graph *g, const sg2v_colorings 
   // device properties, plan tables and the shared small buffers
   PassOpts opt;
   opt.adjoint = true;
-  if (!rel_wanted(tu) || !rel_grad_ok(P, es, kRelLds)) return SG2V_OK;
+  if (!rel_wanted(tu) || !rel_grad_ok(P, es)) return SG2V_OK;
   ST_TRY(prepare(x, plan, g, c, mode, 1, s, opt));
   if (!x.rel || x.lds_max < kRelLds) return SG2V_OK;
   bool ok = false;
@@ -3847,7 +3837,6 @@ sg2v_status rel_grad(const sg2v_plan *plan, sg2v_graph *g, const sg2v_colorings 
   int *Eres = (int *)((char *)res + (size_t)c->count * 8);
   const std::vector<Step> steps = x.rp.steps;
   const int ns = (int)steps.size();
-  const bool sc = dt == DT_F32;
   auto forward = [&](const std::vector<std::pair<int, int>> &keep, int stop) -> sg2v_status {
     build_rel(P, g, 1, dt, x.rp, keep);
     ST_TRY(ws.arena.ensure(x.rp.arena));
@@ -3936,7 +3925,6 @@ sg2v_status rel_grad(const sg2v_plan *plan, sg2v_graph *g, const sg2v_colorings 
         a.grad = grad_w;
         a.scale = grad_colorful[j];
         a.e = ev + H.ver;
-        a.mx = mv + H.ver;
         a.R = rel_rows(x, 32, 1);
         a.tlong = x.g->rlong;
         a.seg_row = g->seg_row;
@@ -4031,7 +4019,6 @@ sg2v_status rel_grad(const sg2v_plan *plan, sg2v_graph *g, const sg2v_colorings 
       HIP_TRY(hipGetLastError());
     }
   }
-  (void)sc;
   HIP_TRY(hipStreamSynchronize(s));
   *done = true;
   return SG2V_OK;
@@ -4788,7 +4775,7 @@ extern "C" sg2v_status sg2v_autotune(const sg2v_plan *plan, const sg2v_graph *g,
   sg2v_tuning_t rel_t = base;
   rel_t.flags &= ~skipfl;
   const int es = esize_of(dtype_of(mode));
-  const bool rel = rel_wanted(rel_t) && rel_ok(plan->p, es, kRelLds) && rel_faster(plan->p, g, dtype_of(mode), n_colorings);
+  const bool rel = rel_wanted(rel_t) && rel_ok(plan->p, es) && rel_faster(plan->p, g, dtype_of(mode), n_colorings);
   sg2v_status st = SG2V_OK;
   {
     TuneOr forced(rel ? kTuneAbsolute : 0);
