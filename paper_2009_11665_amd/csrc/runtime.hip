@@ -2686,6 +2686,8 @@ constexpr TableCost kCost64 = {84, 13, 7.6, 0.75, 1.6, 2.7, 5.5, 51, 1.2, 130, 5
 
 bool rel_faster(const Plan &P, const sg2v_graph *g, int dt, int ncol) {
   if (P.any_wide) return true;
+  // few entries: launches decide, of which the relative tables have fewer
+  if (g->nnz * ncol < (int64_t)1 << 18) return true;
   const sg2v_tuning_t tu = tuning();
   const TableCost &t = dt == DT_F32 ? kCost32 : kCost64;
   const int N = 16 / esize_of(dt), k = P.k;
