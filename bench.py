@@ -1,5 +1,5 @@
 #!/usr/bin/env python3
-"""Benchmark: colourings/s of the FP32 (per-column scaled) count of
+"""Benchmark: colourings/s of the FP32 (power-of-two scaled) count of
 the 15-vertex complete binary tree on an RMAT graph with 2^20 vertices and
 200,000,000 directed edges (k = 15, 4 colourings per step), next to the plain
 one-colouring-per-pass FP64 path and the CPU oracle.
@@ -163,7 +163,7 @@ def write_traffic(spmm_fetch, spmm_write, copy_fetch, copy_write, gather_fetch, 
 def treelet_workload(sg, gg, torch, G=None, ncol=8, reps=2):
     """Treelet distribution: the 47 non-isomorphic nine-vertex trees (k = 9)
     x ncol colourings on Chung-Lu n = 500,000, mean degree 20, gamma 2.1 (a
-    synthetic stand-in for the paper's protein networks), FP32 with per-column
+    synthetic stand-in for the paper's protein networks), FP32 with power-of-two
     exponents: one sg2v_count_multi call sharing isomorphic sub-templates
     across the 47 trees, against the same counts template by template."""
     G = G if G is not None else gg.chung_lu_500k()
@@ -511,7 +511,7 @@ def main():
         c = sg.Colorings(g, k, args.seed, ncol, first=first)
         return sg.count(plan, g, c, mode)
 
-    # FP32 with per-column exponents
+    # FP32 with power-of-two exponents
     if args.tune_flags or args.spmm_width or args.xsplit_min:
         cur = sg.get_tuning()
         cur.flags |= args.tune_flags

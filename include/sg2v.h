@@ -48,7 +48,8 @@ typedef int32_t sg2v_status;
 /* Arithmetic of the count tables. */
 typedef int32_t sg2v_mode;
 #define SG2V_FP64 0  /* IEEE double tables */
-#define SG2V_FP32S 1 /* float mantissas with a power-of-two exponent per column;
+#define SG2V_FP32S 1 /* float mantissas with power-of-two exponents (one per table and
+                        colouring; one per column in absolute tables, see sg2v_tuning_t);
                         final vertex reduction in double */
 #define SG2V_U64 2   /* unsigned 64-bit, exact modulo 2^64; overflow is flagged */
 
@@ -230,13 +231,17 @@ sg2v_status sg2v_colorings_download(const sg2v_colorings *c, uint8_t *out, void 
  * colorful_u64 (nullable): the exact count modulo 2^64, SG2V_U64 mode only.
  * overflow (nullable): set to 1 if a U64 intermediate exceeded 2^64 - 1.
  * All output pointers are host pointers with n_colorings entries (nullable).
- * Colourings are processed in passes of b colourings that sit side by side
- * as extra columns of the same tables (column j * C(k, m) + I_C), so that one
- * SpMM launch over A_G serves all b of them; b = 1024 / (columns of the
- * widest aggregated table), at least 1 (the tuning's batch overrides it) and
- * halved until the pass fits the device memory.  Tables of 1024 or more
- * columns run one colouring per pass: their column chunks each hold one
- * colouring's columns.
+ * Tables are vertex-relative (a row holds the sets of the k - 1 colours other
+ * than the vertex's own: C(k-1, q) columns) where the plan has such tables and
+ * a count in them is estimated to take less time, else absolute (C(k, m)
+ * columns); counts are the same.  Colourings are processed in passes of b.
+ * Relative tables hold a plane per colouring: b = 1024 / (absolute columns of
+ * the widest aggregated table), at most 1,600,000 / n and, up to 1024 columns,
+ * at least 262,144 / n.  Absolute tables hold the b colourings side by side as
+ * extra columns (column j * C(k, m) + I_C), so that one SpMM launch over A_G
+ * serves all of them: b = 1024 / (columns of the widest aggregated table).  b is
+ * at least 1, at most 65,535 (the tuning's batch overrides it) and halved until
+ * the pass fits the device memory.
  * Errors: EINVAL (k of c differs from the plan's, U64 with weights, a plan
  *         of several templates: see sg2v_count_multi), ENOMEM, EDEVICE. */
 sg2v_status sg2v_count(const sg2v_plan *plan, const sg2v_graph *g, const sg2v_colorings *c,
@@ -245,8 +250,11 @@ sg2v_status sg2v_count(const sg2v_plan *plan, const sg2v_graph *g, const sg2v_co
 
 /* sg2v_count for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc).
- * Same arguments, results and errors as sg2v_count, with the same kernels; it
- * calls no hipMalloc, hipFree or other allocating routine.  Every buffer of
+ * Same arguments, results and errors as sg2v_count; it calls no hipMalloc,
+ * hipFree or other allocating routine.  Kernels are those of sg2v_count, but
+ * where the sorted entries of a wide relative table do not fit the area beside
+ * the tables the count runs in absolute ones, and long rows are not split by
+ * neighbour range on a graph that no sg2v_count has split yet.  Every buffer of
  * the count (tables, partial sums, colour-skip masks, results) is taken from
  * one scratch area of SG2V_NOALLOC_SCRATCH_BYTES in the library's device
  * memory, one area per device, held from the first call on that device until
@@ -393,9 +401,12 @@ sg2v_status sg2v_profile_start(void);
 sg2v_status sg2v_profile_stop(sg2v_prof_entry_t *out);
 
 /* Tuning knobs (0 = automatic).  Without flags, counts run in vertex-relative
- * tables (C(k-1, q) columns per row) where every table of the plan has one;
- * any flag but BATCH_SERIAL and GRAD_RECOMPUTE keeps the absolute tables, to
- * which the widths, tile rows and split sizes below apply.  spmm_width: columns per SpMM chunk (row
+ * tables (C(k-1, q) columns per row) where every table of the plan has one and
+ * they are estimated to take less time than absolute ones, gradients wherever
+ * the plan has them; any flag but BATCH_SERIAL and GRAD_RECOMPUTE keeps the
+ * absolute tables, to which the widths, tile rows and split sizes below apply.
+ * budget_bytes covers the tables and, of relative ones, the sorted entries and
+ * range partials of wide aggregations.  spmm_width: columns per SpMM chunk (row
  * segments of 2 to 32 lanes of 16 bytes: up to 128 FP32 or 64 FP64 columns);
  * ema_rows: rows per eMA tile; batch: colourings per pass; flags:
  * SG2V_TUNE_NO_COLOR_SKIP disables the colour-based skipping of SpMM row
@@ -469,8 +480,11 @@ sg2v_status sg2v_get_tuning(sg2v_tuning_t *t);
  * row-panel SpMM, eMA rows per tile,
  * colourings per pass; widths that give the same row segments are tried once;
  * each candidate runs once untimed, then the median of three timed runs
- * counts -- and install the fastest
- * with sg2v_set_tuning.  Results are cached per (template, n, nnz, mode,
+ * counts -- and install the fastest with sg2v_set_tuning.  Widths, tile rows
+ * and flags are timed in absolute tables, which alone use them; where a count
+ * without flags runs in vertex-relative tables, those are timed beside the
+ * fastest flagged setting, and flags are installed only if that is faster.
+ * Results are cached per (template, n, nnz, mode,
  * n_colorings) in the process and, if the environment variable
  * SG2V_TUNE_CACHE names a file, in that file (one line per key).
  *   out : nullable; receives the chosen settings.

@@ -1,7 +1,7 @@
 // Host runtime of libsg2v: graph registration with degree-sorted row tasks,
 // colourings, the per-pass step schedule of the dynamic programme (Alg. 5:
 // neighbour aggregation then multiply-add per split, root reduction last),
-// a liveness-packed device workspace, FP32 per-column exponent bookkeeping,
+// a liveness-packed device workspace, FP32 exponent bookkeeping,
 // and the C ABI entry points declared in include/sg2v.h.
 #include <hip/hip_runtime.h>
 
