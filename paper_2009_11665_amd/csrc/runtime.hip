@@ -2661,7 +2661,7 @@ int64_t abs_batch(const Plan &P) {
 // aggregation, however few columns it has.  In absolute tables the colourings of a pass
 // share the lines, but every row of every 128-byte column chunk has a fixed cost.  So
 // few columns, many colourings and a high degree favour the absolute ones: path of 5
-// with 5 colours, 24 colourings of 65,536 vertices, FP32: degree 4 2.2 over 0.6 ms
+// with 5 colours, 24 colourings of 65,536 vertices, FP32: degree 4 1.8 over 0.5 ms
 // (absolute over relative), degree 256 6.5 over 21.3.  The estimates, in microseconds,
 // are a fit of the whole calls' times on the MI355X over 10,360 calls (1024 to 262,144
 // vertices, uniform, RMAT, Chung-Lu and ring graphs, degree 4 to 1500, nine trees, 1 to
