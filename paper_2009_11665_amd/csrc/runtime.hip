@@ -2667,11 +2667,11 @@ int64_t abs_batch(const Plan &P) {
 // vertices, uniform, RMAT, Chung-Lu and ring graphs, degree 4 to 1500, nine trees, 1 to
 // 600 colourings); the relative tables' own constants come first, then the absolute
 // ones'.  They are off by a fifth to a third, so a tenth is asked of the relative
-// tables.  Of the calls of over 150 us, 139 then take over 5% longer than in absolute
-// tables, 0.6 times as fast at worst (906 and 0.22 in relative ones throughout); the mean
-// is 2.08 times faster than absolute ones throughout (2.02 relative ones).  Plans with
-// chunked aggregations were faster in relative tables at every degree measured (4 to
-// 260: 1.2 to 6 times).
+// tables (not of their root's products).  Of 11,187 measured calls of over 150 us, 131
+// then take over 5% longer than in absolute tables, 0.67 times as fast at worst (959 and
+// 0.22 in relative ones throughout); the mean is 2.14 times faster than absolute ones
+// throughout (2.08 relative ones).  Plans with chunked aggregations were faster in
+// relative tables at every degree measured (4 to 260: 1.2 to 6 times).
 struct TableCost {
   double rcall, ragg;                           // per call and aggregation
   double rent, rentcol, rentw, rent1;           // ps per entry and colouring: aggregation, column, weight, histogram
@@ -2680,14 +2680,17 @@ struct TableCost {
   double along, alongw;                         // ns per aggregation, pass and entry of the longest task
   double achline, achlinew, achent, aent1;      // ps per entry: chunk of 128 bytes, its weights, chunk; colouring
   double achrow, achrowline, arow, apair;       // ps per row: chunk, 128 bytes of it; row and pair of a colouring
+  // Pairs of the root reduction, which with many more colours than vertices decide:
+  // ps per row, colouring and pair, and us per pair of one row's chain.  Binary tree of
+  // 7, k = 14 (34,320 pairs), 8 colourings of 100,000 vertices, FP64: 22.4 over 37.0 ms,
+  // k = 12 (9240) 10.0 over 7.7; one of 1000 vertices, k = 14, 0.55 times as fast.
+  double rroot, rchain, aroot;
 };
-constexpr TableCost kCost32 = {110, 16, 14, 0.34, 2.7, 0, 3.3, 82, 0.76, 140, 81, 3.5, 12, 7.2, 5.2, 3.8, 3.5, 4.3, 770, 0, 100, 1.9};
-constexpr TableCost kCost64 = {84, 13, 7.6, 0.75, 1.6, 2.7, 5.5, 51, 1.2, 130, 5.8, 0.48, 9.6, 11, 6.5, 3.5, 0, 4.8, 190, 140, 110, 2.2};
+constexpr TableCost kCost32 = {110, 16, 14, 0.34, 2.7, 0, 3.3, 82, 0.76, 140, 81, 3.5, 12, 7.2, 5.2, 3.8, 3.5, 4.3, 770, 0, 100, 1.9, 0.5, 0.0055, 0.5};
+constexpr TableCost kCost64 = {84, 13, 7.6, 0.75, 1.6, 2.7, 5.5, 51, 1.2, 130, 5.8, 0.48, 9.6, 11, 6.5, 3.5, 0, 4.8, 190, 140, 110, 2.2, 1.0, 0.0055, 0.5};
 
 bool rel_faster(const Plan &P, const sg2v_graph *g, int dt, int ncol) {
   if (P.any_wide) return true;
-  // few entries: launches decide, of which the relative tables have fewer
-  if (g->nnz * ncol < (int64_t)1 << 18) return true;
   const sg2v_tuning_t tu = tuning();
   const TableCost &t = dt == DT_F32 ? kCost32 : kCost64;
   const int N = 16 / esize_of(dt), k = P.k;
@@ -2695,8 +2698,9 @@ bool rel_faster(const Plan &P, const sg2v_graph *g, int dt, int ncol) {
   const int64_t b = std::max<int64_t>(1, std::min<int64_t>(ncol, tu.batch > 0 ? tu.batch : most));
   const int G = pick_G(dt, 1024 / most * b, g->n);
   const int64_t full = ncol / b, rest = ncol % b;
-  double agg = 0, cols = 0, chunks = 0, apairs = 0, rpairs = 0;
-  for (auto &nd : P.nodes) {
+  double agg = 0, cols = 0, chunks = 0, apairs = 0, rpairs = 0, root = 0;
+  for (size_t q = 0; q < P.nodes.size(); ++q) {
+    const Node &nd = P.nodes[q];
     if (nd.size == 1) continue;
     if (nd.n_passive_uses > 0) {
       agg += 1;
@@ -2705,22 +2709,32 @@ bool rel_faster(const Plan &P, const sg2v_graph *g, int dt, int ncol) {
     }
     const int ma = P.nodes[nd.active].size;
     if (ma == 1) continue;
+    const double pairs = (double)binom(k - 1, nd.size - 1) * binom(nd.size - 1, ma - 1);
+    if (P.root_index[q] >= 0) {
+      root += pairs;
+      continue;
+    }
     apairs += (double)binom(k, nd.size) * binom(nd.size, ma);
-    rpairs += (double)binom(k - 1, nd.size - 1) * binom(nd.size - 1, ma - 1);
+    rpairs += pairs;
   }
+  // few entries: launches decide, of which the relative tables have fewer
+  if (g->nnz * ncol < (int64_t)1 << 18 && root < 4096) return true;
+  const double longest = g->n_tasks > 0 ? g->h_task_len[0] : 0;
   // No aggregation: without pairs either, only the neighbour colours are counted (one
   // edge, 24 colourings of 65,536 vertices, FP64: degree 16 234 over 162 us, 256 equal,
   // 50,000 of degree 1100 1.2 over 1.9 ms; with weights 65,536 of degree 64 equal; 1500
-  // of degree 1400, 600 colourings 3.3 over 1.9).
-  if (agg == 0) return apairs > 0 || g->n < 4096 || g->nnz < (g->w ? 64 : 256) * g->n;
+  // of degree 1400, 600 colourings 3.3 over 1.9; RMAT, 8192 of degree 512, 0.39 over 0.23).
+  if (agg == 0)
+    return apairs + root > 0 || g->n < 4096 || g->nnz < (g->w ? 64 : 256) * g->n || longest * g->n >= 4.0 * g->nnz;
   const double n = (double)g->n, nnz = (double)g->nnz, c = ncol, w = g->w ? 1.0 : 0.0, line = G / 8.0;
-  const double passes = (double)(full + (rest > 0)), longest = g->n_tasks > 0 ? g->h_task_len[0] : 0;
+  const double passes = (double)(full + (rest > 0));
+  const double rroot = t.rchain * root + 1e-6 * n * c * t.rroot * root, aroot = 1e-6 * n * c * t.aroot * root;
   const double rel = t.rcall + t.ragg * agg + 1e-6 * (nnz * c * ((t.rent + w * t.rentw) * agg + t.rentcol * cols + t.rent1) +
                                                       n * c * (t.rcol * cols + t.rrow + t.rpair * rpairs));
   const double abs = t.acall + t.aagg * agg * passes + t.achunk * chunks + 1e-3 * agg * passes * longest * (t.along + w * t.alongw) +
                      1e-6 * (nnz * (chunks * (line * (t.achline + w * t.achlinew) + t.achent) + c * t.aent1) +
                              n * (chunks * (t.achrow + line * t.achrowline) + c * (t.arow + t.apair * apairs)));
-  return 1.1 * rel < abs;
+  return 1.1 * rel + rroot < abs + aroot;
 }
 
 int choose_batch(const Plan &P, int ncol, int dt, const sg2v_graph *g) {

@@ -138,3 +138,26 @@ def test_tables_by_estimated_time(deg, ncol, absolute, mode):
             assert int(r["colorful_u64"][j]) == u
         else:
             assert r["colorful"][j] == pytest.approx(f, rel={"fp64": 1e-12, "fp32s": 1e-5}[mode])
+
+
+@pytest.mark.parametrize("mode", ["u64", "fp64", "fp32s"])
+def test_tables_by_estimated_time_of_the_root(mode):
+    """Binary tree of 7 with 14 colours: 34,320 products a vertex at the root, which the
+    absolute tables' root takes faster; with 9 colours (560) relative ones are."""
+    n = 3000
+    G = gg.csr(n, *gg.er_edges(n, 3 * n, 5))
+    g = sg.Graph.from_csr(G)
+    for k, absolute in ((14, True), (9, False)):
+        plan = sg.Plan(gg.BINTREE7, k)
+        c = sg.Colorings(g, k, 2, 6)
+        say("root's pairs", k, mode)
+        sg.profile_start()
+        r = sg.count(plan, g, c, mode)
+        prof = sg.profile_stop()
+        if mode != "fp32s":
+            assert (prof["ema_single"]["launches"] > 0) == absolute
+        f, u, _ = O.count(G, gg.BINTREE7, k, O.colors(n, k, 2, 5), mode=O.U64 if mode == "u64" else O.FP64)
+        if mode == "u64":
+            assert int(r["colorful_u64"][5]) == u
+        else:
+            assert r["colorful"][5] == pytest.approx(f, rel={"fp64": 1e-12, "fp32s": 1e-5}[mode])
